@@ -11,14 +11,12 @@
 // cells) or one lane per particle from global memory.
 //
 // Device work (one stream, no host synchronisation in between):
-//   fill        zero the work counters
 //   grouping    cell and Morton bucket of every particle (all items at once),
-//               grouped by bucket without global atomics (gather.hpp): bucket
-//               table, binned permutation and binned copy of the positions
-//   compact     list of the non-empty buckets of the tiled items, one list
-//               per (order, components) class
+//               grouped by bucket without global atomics (gather.hpp): binned
+//               particles, and the work items of the tiled items (runs of one
+//               tile, cut into pieces), (order, components) class by class
 //   gather      per class present: a persistent grid of resident one-wavefront
-//               workgroups striding over the class's non-empty tiles, and a
+//               workgroups taking the class's work items, and a
 //               plain grid with one wavefront per group of 64 consecutive
 //               binned particles of the class's direct items.  One kernel per
 //               class and path keeps each kernel's registers and LDS to what
@@ -34,6 +32,7 @@ namespace bsi {
 namespace {
 
 constexpr int BATCH_B = 64;        // threads per workgroup of the persistent tile gather
+constexpr uint32_t BATCH_CHUNK = 256;  // most particles per work item
 constexpr int UNIT = 64;           // particles per direct unit (one wavefront)
 constexpr int DIRECT_B = 256;      // threads per workgroup of the direct gather
 constexpr int BLK = 256;           // threads per workgroup of the binning kernels
@@ -43,14 +42,13 @@ constexpr int class_of(int N, int C) { return (N == 6 ? 2 : 0) + (C == 3 ? 1 : 0
 enum : int32_t { MODE_DIRECT = 0, MODE_TILE8 = 2 };
 
 struct BatchItem {
-    GatherArgs ga;       // hist/offs at the item's buckets; perm/pos_sorted are the batch-wide arrays
+    GatherArgs ga;       // perm/binned are the batch-wide arrays
     int32_t N, C, mode, tile;
     int32_t cls;         // class_of(N, C)
     uint32_t pbase;      // first particle slot of the item in the batch
     uint32_t bbase;      // first bucket of the item in the batch
     uint32_t nb;         // buckets of the item, the non-finite bucket included
     uint32_t pblk;       // first binning workgroup of the item
-    uint32_t bblk;       // first compaction workgroup of the item (tiled items)
     uint32_t ubase;      // first direct unit of the item (direct items; units are grouped by class)
     uint32_t cbase;      // first coarse grouping range of the item
     int32_t cshift;      // item bucket b lies in coarse range cbase + (b >> cshift)
@@ -59,32 +57,17 @@ struct BatchItem {
 struct BatchArgs {
     const BatchItem* items;
     const uint16_t* pblock_item;  // item of each binning workgroup
-    const uint16_t* bblock_item;  // item of each compaction workgroup
+    const uint16_t* range_item;   // item of each coarse grouping range
     const uint16_t* dunit_item;   // item of each direct unit
-    uint32_t* hist;
-    uint32_t* offs;
     uint32_t* perm;
-    double* pos_sorted;
+    void* binned;
     const uint32_t* cstart;       // first bucket of every coarse grouping range (+ end)
-    uint2* tile_list;             // (item, bucket) of every non-empty tile, class by class
-    uint32_t* ctr;                // [1 + class] non-empty tiles of the class ([0] unused)
-    uint32_t lbase[NCLASS];       // first tile-list slot of each class
+    u32x4* work;                  // work items (tag = batch item) of the tiled items
+    const u32x4* desc;            // chunk descriptors of the grouping
+    uint32_t* ctl;                // [class][ITEM_CTL_WORDS] take counters
+    uint32_t* start;              // first chunk of each class (+ end)
+    uint32_t units;               // units per chunk
 };
-
-// cell -> item-local Morton bucket, or the item's non-finite bucket
-__device__ __forceinline__ uint32_t item_bucket(const BatchItem& it, const double* x) {
-    const int n[3] = {it.ga.n0, it.ga.n1, it.ga.n2};
-    const double ih[3] = {it.ga.ih0, it.ga.ih1, it.ga.ih2};
-    int c[3];
-    double t[3];
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) ok = cell_of(x[d], ih[d], n[d], c[d], t[d]) && ok;
-    if (!ok) return it.nb - 1;
-    const uint32_t T = uint32_t(it.tile);
-    return (spread3(uint32_t(c[0]) / T) << 2) | (spread3(uint32_t(c[1]) / T) << 1) |
-           spread3(uint32_t(c[2]) / T);
-}
 
 // Grouping slots of a batch: item i owns the slots [pblk * BLK, (pblk +
 // ceil(P / BLK)) * BLK), slot pblk * BLK + p holding its particle p; the
@@ -92,33 +75,32 @@ __device__ __forceinline__ uint32_t item_bucket(const BatchItem& it, const doubl
 struct BatchSlots {
     const BatchItem* items;
     const uint16_t* pblock_item;
-    __device__ __forceinline__ const BatchItem& item_of(long i, long& p) const {
-        const BatchItem& it = items[pblock_item[i / BLK]];
-        p = i - long(it.pblk) * BLK;
-        return it;
+    struct Slot {
+        double x[3];
+        uint32_t local;
+        const BatchItem* it;
+    };
+    __device__ __forceinline__ bool fetch(long i, Slot& s) const {
+        s.it = items + pblock_item[i / BLK];
+        const long at = i - long(s.it->pblk) * BLK;
+        const long p = min(at, s.it->ga.P - 1);
+        s.local = uint32_t(p);
+        s.x[0] = s.it->ga.pos[3 * p];
+        s.x[1] = s.it->ga.pos[3 * p + 1];
+        s.x[2] = s.it->ga.pos[3 * p + 2];
+        return at == p;
     }
-    __device__ __forceinline__ bool key(long i, uint32_t& k, uint32_t& c) const {
-        long p;
-        const BatchItem& it = item_of(i, p);
-        if (p >= it.ga.P) return false;
-        const double x[3] = {it.ga.pos[3 * p], it.ga.pos[3 * p + 1], it.ga.pos[3 * p + 2]};
-        const uint32_t lk = item_bucket(it, x);
-        k = it.bbase + lk;
-        c = it.cbase + (lk >> it.cshift);
-        return true;
-    }
-    __device__ __forceinline__ uint32_t coarse(long i, uint32_t k) const {
-        long p;
-        const BatchItem& it = item_of(i, p);
-        return it.cbase + ((k - it.bbase) >> it.cshift);
-    }
-    __device__ __forceinline__ void fetch(long i, uint32_t& local, double* x) const {
-        long p;
-        const BatchItem& it = item_of(i, p);
-        local = uint32_t(p);
-        x[0] = it.ga.pos[3 * p];
-        x[1] = it.ga.pos[3 * p + 1];
-        x[2] = it.ga.pos[3 * p + 2];
+    __device__ __forceinline__ void place(const Slot& s, GrpPlace& pl) const {
+        const BatchItem& it = *s.it;
+        const int n[3] = {it.ga.n0, it.ga.n1, it.ga.n2};
+        const double ih[3] = {it.ga.ih0, it.ga.ih1, it.ga.ih2};
+        pl.ok = locate<double>(s.x, n, ih, pl.cell, pl.t);
+        const uint32_t T = uint32_t(it.tile);
+        const uint32_t lk = pl.ok ? (spread3(uint32_t(pl.cell[0]) / T) << 2) |
+                                        (spread3(uint32_t(pl.cell[1]) / T) << 1) | spread3(uint32_t(pl.cell[2]) / T)
+                                  : it.nb - 1;
+        pl.key = it.bbase + lk;
+        pl.coarse = it.cbase + (lk >> it.cshift);
     }
 };
 
@@ -132,14 +114,27 @@ struct TableCoarse {
     }
 };
 
-__global__ __launch_bounds__(BLK) void k_batch_compact(BatchArgs b) {
-    const uint32_t item = b.bblock_item[blockIdx.x];
-    const BatchItem& it = b.items[item];
-    const uint32_t k = (blockIdx.x - it.bblk) * BLK + threadIdx.x;
-    if (k >= it.nb) return;
-    if (b.hist[it.bbase + k] != 0u)
-        b.tile_list[b.lbase[it.cls] + atomicAdd(&b.ctr[1 + it.cls], 1u)] = make_uint2(item, k);
-}
+// The work items of a batch: those of the tiled items.  The batch's items are
+// laid out class by class, the direct ones last, so that the chunks of a class
+// are consecutive: [start[cls], start[cls + 1]).
+struct BatchLists {
+    const BatchItem* items;
+    const uint16_t* range_item;
+    uint32_t* start;
+    __device__ __forceinline__ const BatchItem& of(uint32_t c) const { return items[range_item[c]]; }
+    __device__ __forceinline__ int slot(uint32_t c) const { return of(c).mode == MODE_DIRECT ? NCLASS : of(c).cls; }
+    __device__ __forceinline__ bool wanted(uint32_t c) const { return of(c).mode != MODE_DIRECT; }
+    __device__ __forceinline__ uint32_t bias(uint32_t c) const { return of(c).bbase; }
+    __device__ __forceinline__ uint32_t tag(uint32_t c) const { return range_item[c]; }
+    __device__ __forceinline__ void begin(uint32_t c, uint32_t g) const {
+        for (int k = c == 0 ? 0 : slot(c - 1) + 1; k <= slot(c); ++k) start[k] = g;
+    }
+    // after the last range: classes past it are empty
+    __device__ __forceinline__ void end(uint32_t nch) const {
+        for (int k = last + 1; k <= NCLASS; ++k) start[k] = nch;
+    }
+    int last;   // slot of the last range
+};
 
 template <int N, typename CT, int C, int T>
 constexpr bool batch_tile_ok() {
@@ -147,22 +142,30 @@ constexpr bool batch_tile_ok() {
            TileGeom<N, CT, C, T>::SLOTS < 3072;
 }
 
-// Tiles of class (N, C): workgroup g takes the class's tiles g, g + G, g + 2G,
-// ... (G = grid size); the tile index is the same in every lane, so the loop
-// is scalar and every wavefront of the workgroup meets the same barriers.
+// Work items of class (N, C), taken as by the single-field tiled gather.
 template <typename CT, bool GRAD, int N, int C>
 __global__ __launch_bounds__(BATCH_B) void k_batch_tiles(BatchArgs b) {
     if constexpr (batch_tile_ok<N, CT, C, 8>()) {
         extern __shared__ u32x4 lds[];
         constexpr int cls = class_of(N, C);
-        const uint32_t ntile = __builtin_amdgcn_readfirstlane(b.ctr[1 + cls]);
-        const uint2* list = b.tile_list + b.lbase[cls];
-        for (uint32_t u = blockIdx.x; u < ntile; u += gridDim.x) {
-            const uint2 e = list[u];
-            const uint32_t item = __builtin_amdgcn_readfirstlane(e.x);
-            const uint32_t bucket = __builtin_amdgcn_readfirstlane(e.y);
-            tile_eval<N, CT, C, GRAD, 8, BATCH_B>(b.items[item].ga, bucket, lds);
+        ItemQueue<BATCH_B> q;
+        const ItemSource src{b.work, b.desc, b.start + cls, b.start + cls + 1, b.ctl + cls * ITEM_CTL_WORDS,
+                             b.units};
+        bool more = q.begin(src, nullptr, uint32_t(blockIdx.x) % ITEM_RANGES);
+        while (more) {
+            uint32_t next = q.m == 0 ? q.issue() : 0u;
+            for (uint32_t k = 0; k < q.m; ++k) {
+                const u32x4 e = src.items[q.i + k];
+                const uint32_t bucket = __builtin_amdgcn_readfirstlane(e.x);
+                const uint32_t start = __builtin_amdgcn_readfirstlane(e.y);
+                const uint32_t count = __builtin_amdgcn_readfirstlane(e.z);
+                const uint32_t item = __builtin_amdgcn_readfirstlane(e.w);
+                if (k + 1 == q.m) next = q.issue();
+                bucket_eval<N, CT, C, GRAD, 8, BATCH_B>(b.items[item].ga, bucket, count, start, lds);
+            }
+            more = q.settle(next);
         }
+        item_take_end(src.ctl);
     }
 }
 
@@ -261,11 +264,11 @@ struct bsi_batch {
     bool grad = true;
     int nitems = 0;                      // items with P > 0
     uint64_t Ptot = 0, Btot = 0;
-    uint32_t nbblocks = 0;
     uint32_t dbeg[NCLASS] = {}, dend[NCLASS] = {};  // direct units of each class
-    uint32_t tbound[NCLASS] = {};   // buckets of the class's tiled items (bound on its tiles)
+    uint64_t tbound[NCLASS] = {};   // bound on the class's work items
     unsigned tgrid[NCLASS] = {};    // persistent tile grid of each class
     size_t tlds[NCLASS] = {};       // LDS of the class's tile workgroups
+    int last_slot = 0;                   // BatchLists::last
     GrpPlan grp;                         // grouping of the particle slots by bucket
     GrpBuffers gbuf{};
     void* ws = nullptr;
@@ -300,14 +303,17 @@ static bsi_status enqueue(bsi_batch* b, hipStream_t s) {
     bsi_ctx* ctx = b->ctx;
     if (b->nitems == 0) return BSI_OK;
     const BatchArgs& a = b->args;
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, a.ctr, long(1 + NCLASS), 0u);
     {
         StageTimer tm(ctx, "batch_bin", s);
         const BatchSlots slots{a.items, a.pblock_item};
-        grp_count(slots, b->grp, b->gbuf, s);
+        const TableCoarse cm{a.cstart};
+        const BatchLists ls{a.items, a.range_item, a.start, b->last_slot};
+        grp_count(slots, b->grp, b->gbuf, a.ctl, NCLASS * ITEM_CTL_WORDS, s);
         grp_scan(b->grp, b->gbuf, s);
-        grp_scatter(slots, TableCoarse{a.cstart}, b->grp, b->gbuf, a.hist, a.offs, a.perm, a.pos_sorted, s);
-        if (b->nbblocks) hipLaunchKernelGGL(k_batch_compact, dim3(b->nbblocks), dim3(BLK), 0, s, a);
+        if (b->coef == BSI_F64)
+            grp_scatter<false>(slots, cm, ls, b->grp, b->gbuf, BATCH_CHUNK, a.perm, a.binned, a.work, s);
+        else
+            grp_scatter<true>(slots, cm, ls, b->grp, b->gbuf, BATCH_CHUNK, a.perm, a.binned, a.work, s);
     }
     {
         StageTimer tm(ctx, "batch_gather", s);
@@ -384,8 +390,10 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     b->grad = grad;
     b->cfgs.resize(count);
     std::vector<BatchItem> hi;
-    std::vector<uint16_t> pblock, bblock, dunit_cls[NCLASS];
+    std::vector<int> order;  // the caller's items, tiled classes first
+    std::vector<uint16_t> pblock, range_item, dunit_cls[NCLASS];
     uint64_t Btot = 0, pbase = 0;
+    std::vector<int> slot_of(count, 0);
     for (int i = 0; i < count; ++i) {
         const bsi_eval_item& it = items[i];
         bsi_field* f = it.field;
@@ -401,6 +409,16 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
         item_mode(f, c, &mode, &tile);
         b->cfgs[i].variant = mode == MODE_DIRECT ? 1 : 0;
         b->cfgs[i].sort_tile = tile;
+        slot_of[i] = mode == MODE_DIRECT ? NCLASS : class_of(f->N, f->C);
+        order.push_back(i);
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return slot_of[a] < slot_of[c]; });
+    if (!order.empty()) b->last_slot = slot_of[order.back()];
+    for (const int i : order) {
+        const bsi_eval_item& it = items[i];
+        bsi_field* f = it.field;
+        const int mode = b->cfgs[i].variant == 1 ? MODE_DIRECT : MODE_TILE8;
+        const int tile = b->cfgs[i].sort_tile;
         BatchItem x{};
         GatherArgs& g = x.ga;
         g.grid = f->grid;
@@ -419,7 +437,6 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
         g.ih1 = f->inv_h[1];
         g.ih2 = f->inv_h[2];
         g.xcd_remap = 0;
-        g.tiles_per_group = 1;
         g.basis = BSI_BASIS_BSPLINE;
         g.cs = 1;
         const size_t nbf = bin_bucket_count(f, tile);
@@ -440,9 +457,6 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
             x.ubase = uint32_t(du.size());  // class-local until the classes are laid end to end
             du.insert(du.end(), size_t((it.P + UNIT - 1) / UNIT), id);
         } else {
-            x.bblk = uint32_t(bblock.size());
-            bblock.insert(bblock.end(), size_t((x.nb + BLK - 1) / BLK), id);
-            b->tbound[x.cls] += x.nb;
             b->tlds[x.cls] = size_t(batch_tile_lds(coef, f->N, f->C, tile));
         }
         hi.push_back(x);
@@ -475,18 +489,25 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     }
     for (auto& x : hi)
         if (x.mode == MODE_DIRECT) x.ubase += b->dbeg[x.cls];
-    uint32_t lbase[NCLASS];
-    {
-        uint64_t l = 0;
-        for (int c = 0; c < NCLASS; ++c) {
-            lbase[c] = uint32_t(l);
-            l += b->tbound[c];
-        }
-    }
     uint32_t fine_max = 1;
-    for (const auto& x : hi) {
-        for (uint64_t lo = 0; lo < x.nb; lo += uint64_t(1) << x.cshift) cstart.push_back(uint32_t(x.bbase + lo));
-        fine_max = std::max(fine_max, std::min<uint32_t>(x.nb, uint32_t(1) << x.cshift));
+    uint64_t nwork = 0;   // item slots the chunk plan reserves at most (direct items too)
+    for (size_t i = 0; i < hi.size(); ++i) {
+        const BatchItem& x = hi[i];
+        for (uint64_t lo = 0; lo < x.nb; lo += uint64_t(1) << x.cshift) {
+            cstart.push_back(uint32_t(x.bbase + lo));
+            range_item.push_back(uint16_t(i));
+        }
+        const uint32_t fine = std::min<uint32_t>(x.nb, uint32_t(1) << x.cshift);
+        fine_max = std::max(fine_max, fine);
+        if (x.mode != MODE_DIRECT) {
+            GrpPlan own;
+            own.nbuckets = x.nb;
+            own.nvalid = uint32_t(x.ga.P);
+            own.fine_max = fine;
+            const size_t cap = grp_item_cap(own, BATCH_CHUNK);
+            b->tbound[x.cls] += cap;
+            nwork += cap;
+        }
     }
     cstart.push_back(uint32_t(Btot));
     if (Btot >= (uint64_t(1) << 32)) {
@@ -499,13 +520,12 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     b->nitems = int(hi.size());
     b->Ptot = pbase;
     b->Btot = Btot;
-    b->nbblocks = uint32_t(bblock.size());
     if (b->nitems == 0) {
         *out = b;
         return BSI_OK;
     }
-    // workspace: tables, bucket table (counts, offsets), grouping scratch,
-    // perm, binned positions, tile list, counters
+    // workspace: tables, grouping scratch, perm, binned particles, work items,
+    // counters
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off;
@@ -514,16 +534,15 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     };
     const size_t o_items = take(hi.size() * sizeof(BatchItem));
     const size_t o_pblock = take(pblock.size() * sizeof(uint16_t));
-    const size_t o_bblock = take(std::max<size_t>(bblock.size(), 1) * sizeof(uint16_t));
+    const size_t o_range = take(range_item.size() * sizeof(uint16_t));
     const size_t o_dunit = take(std::max<size_t>(dunit.size(), 1) * sizeof(uint16_t));
-    const size_t o_hist = take(Btot * sizeof(uint32_t));
-    const size_t o_offs = take(Btot * sizeof(uint32_t));
     const size_t o_grp = take(grp_scratch_words(b->grp) * sizeof(uint32_t));
     const size_t o_cstart = take(cstart.size() * sizeof(uint32_t));
     const size_t o_perm = take(pbase * sizeof(uint32_t));
-    const size_t o_pos = take(3 * pbase * sizeof(double));
-    const size_t o_list = take(std::max<uint64_t>(Btot, 1) * sizeof(uint2));
-    const size_t o_ctr = take((1 + NCLASS) * sizeof(uint32_t));
+    const size_t o_pos = take(pbase * (coef == BSI_F64 ? 24 : 16));
+    const size_t o_work = take(std::max<uint64_t>(nwork, 1) * sizeof(u32x4));
+    const size_t o_ctl = take(NCLASS * ITEM_CTL_WORDS * sizeof(uint32_t));
+    const size_t o_start = take((NCLASS + 1) * sizeof(uint32_t));
     b->ws_bytes = off;
     if (hipMalloc(&b->ws, off) != hipSuccess) {
         (void)hipGetLastError();
@@ -535,22 +554,20 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     BatchArgs& a = b->args;
     a.items = reinterpret_cast<const BatchItem*>(base + o_items);
     a.pblock_item = reinterpret_cast<const uint16_t*>(base + o_pblock);
-    a.bblock_item = reinterpret_cast<const uint16_t*>(base + o_bblock);
+    a.range_item = reinterpret_cast<const uint16_t*>(base + o_range);
     a.dunit_item = reinterpret_cast<const uint16_t*>(base + o_dunit);
-    a.hist = reinterpret_cast<uint32_t*>(base + o_hist);
-    a.offs = reinterpret_cast<uint32_t*>(base + o_offs);
     b->gbuf = grp_buffers(b->grp, reinterpret_cast<uint32_t*>(base + o_grp));
     a.cstart = reinterpret_cast<const uint32_t*>(base + o_cstart);
     a.perm = reinterpret_cast<uint32_t*>(base + o_perm);
-    a.pos_sorted = reinterpret_cast<double*>(base + o_pos);
-    a.tile_list = reinterpret_cast<uint2*>(base + o_list);
-    a.ctr = reinterpret_cast<uint32_t*>(base + o_ctr);
-    for (int c = 0; c < NCLASS; ++c) a.lbase[c] = lbase[c];
+    a.binned = base + o_pos;
+    a.work = reinterpret_cast<u32x4*>(base + o_work);
+    a.desc = b->gbuf.desc;
+    a.units = item_units(b->grp.mmax);
+    a.ctl = reinterpret_cast<uint32_t*>(base + o_ctl);
+    a.start = reinterpret_cast<uint32_t*>(base + o_start);
     for (auto& x : hi) {
-        x.ga.hist = a.hist + x.bbase;
-        x.ga.offs = a.offs + x.bbase;
         x.ga.perm = a.perm;
-        x.ga.pos_sorted = a.pos_sorted;
+        x.ga.binned = a.binned;
     }
     bsi_status st = BSI_OK;
     auto up = [&](size_t o, const void* src, size_t bytes) {
@@ -562,11 +579,11 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     };
     up(o_items, hi.data(), hi.size() * sizeof(BatchItem));
     up(o_pblock, pblock.data(), pblock.size() * sizeof(uint16_t));
-    up(o_bblock, bblock.data(), bblock.size() * sizeof(uint16_t));
+    up(o_range, range_item.data(), range_item.size() * sizeof(uint16_t));
     up(o_dunit, dunit.data(), dunit.size() * sizeof(uint16_t));
     up(o_cstart, cstart.data(), cstart.size() * sizeof(uint32_t));
     // persistent tile grids: as many one-wavefront workgroups as stay
-    // resident, at most one per bucket of the class's tiled items
+    // resident, at most one per work item the class can have
     for (int c = 0; c < NCLASS && st == BSI_OK; ++c) {
         if (b->tbound[c] == 0) continue;
         int per_cu = 0;

@@ -278,14 +278,25 @@ bsi_status debug_cells_run(bsi_field* f, const double* pos, int64_t P, int32_t* 
                            hipStream_t s);
 // the evaluation's binning alone, results copied to caller buffers
 size_t bin_bucket_count(const bsi_field* f, int tile);
-// byte offsets of the binning's arrays in its workspace (grouping scratch
-// first, 16-byte aligned), and the binning itself
+// byte offsets of the binning's arrays in its 16-byte aligned workspace, the
+// arrays, and the binning itself; ichunk = most particles per work item of a
+// tiled gather (0: no items)
 struct BinLayout {
-    size_t grp, pos, perm, hist, offs, bytes;
+    size_t grp, binned, perm, items, ctl, bytes;
+    uint32_t ichunk;
 };
-BinLayout bin_layout(const bsi_field* f, long P, int tile);
-bsi_status bin_run(bsi_field* f, const double* pos, long P, int tile, void* scratch, uint32_t* perm,
-                   double* pos_sorted, uint32_t* hist, uint32_t* offs, hipStream_t s);
+struct BinArrays {
+    void* binned;
+    uint32_t* perm;
+    void* items;
+    const void* desc;         // chunk descriptors and their number
+    const uint32_t* nchunks;
+    uint32_t* ctl;
+    uint32_t units;           // units per chunk the gather takes its items in
+};
+BinLayout bin_layout(const bsi_field* f, long P, int tile, uint32_t ichunk);
+BinArrays bin_arrays(const bsi_field* f, long P, int tile, const BinLayout& l, void* ws);
+bsi_status bin_run(bsi_field* f, const double* pos, long P, int tile, const BinLayout& l, void* ws, hipStream_t s);
 // u, grad u and the six second derivatives per component (hessian.hip)
 bsi_status hessian_run(bsi_field* f, const double* pos, int64_t P, void* u, void* grad, void* hess,
                        hipStream_t s);

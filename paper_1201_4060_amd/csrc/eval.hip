@@ -32,29 +32,108 @@ struct MortonKey {
     int tile;
     uint32_t nbuckets_finite;
     int shift;
-    __device__ __forceinline__ uint32_t coarse(long, uint32_t k) const { return k >> shift; }
-    __device__ __forceinline__ void fetch(long p, uint32_t& local, double* x) const {
-        local = uint32_t(p);
-        x[0] = a.pos[3 * p];
-        x[1] = a.pos[3 * p + 1];
-        x[2] = a.pos[3 * p + 2];
-    }
-    __device__ __forceinline__ bool key(long p, uint32_t& k, uint32_t& cr) const {
-        const int n[3] = {a.n0, a.n1, a.n2};
-        const double ih[3] = {a.ih0, a.ih1, a.ih2};
-        int c[3];
-        double tt[3];
-        bool ok = true;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) ok = cell_of(a.pos[3 * p + d], ih[d], n[d], c[d], tt[d]) && ok;
-        k = nbuckets_finite;
-        if (ok)
-            k = (spread3(uint32_t(c[0] / tile)) << 2) | (spread3(uint32_t(c[1] / tile)) << 1) |
-                spread3(uint32_t(c[2] / tile));
-        cr = k >> shift;
+    struct Slot {
+        double x[3];
+        uint32_t local;
+    };
+    __device__ __forceinline__ bool fetch(long p, Slot& s) const {
+        s.local = uint32_t(p);
+        s.x[0] = a.pos[3 * p];
+        s.x[1] = a.pos[3 * p + 1];
+        s.x[2] = a.pos[3 * p + 2];
         return true;
     }
+    __device__ __forceinline__ void place(const Slot& s, GrpPlace& pl) const {
+        const int n[3] = {a.n0, a.n1, a.n2};
+        const double ih[3] = {a.ih0, a.ih1, a.ih2};
+        pl.ok = locate<double>(s.x, n, ih, pl.cell, pl.t);
+        pl.key = nbuckets_finite;
+        if (pl.ok)
+            pl.key = (spread3(uint32_t(pl.cell[0]) / uint32_t(tile)) << 2) |
+                     (spread3(uint32_t(pl.cell[1]) / uint32_t(tile)) << 1) |
+                     spread3(uint32_t(pl.cell[2]) / uint32_t(tile));
+        pl.coarse = pl.key >> shift;
+    }
 };
+
+// The grouping finished as one table over all buckets (bsi_debug_bins): the
+// chunks' keys are counted into per-key counters, one workgroup per coarse
+// range turns them into the bucket table and per-key cursors, and every chunk
+// reserves its keys' slots there.
+
+__device__ __forceinline__ bool table_chunk(const ShiftCoarse& cm, const u32x4* desc, const uint32_t* nchunks,
+                                            const GrpRec* __restrict__ rec, uint32_t* lh, uint32_t& klo, uint32_t& nf,
+                                            uint32_t& j0, uint32_t& n) {
+    if (blockIdx.x >= __builtin_amdgcn_readfirstlane(*nchunks)) return false;
+    const u32x4 d = desc[blockIdx.x];
+    uint32_t khi;
+    cm.range(d.x, klo, khi);
+    nf = khi - klo;
+    j0 = d.y;
+    n = d.z;
+    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK) lh[f] = 0;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n; j += GRP_FINE_BLOCK) atomicAdd(&lh[rec[j0 + j].key - klo], 1u);
+    __syncthreads();
+    return true;
+}
+
+__global__ __launch_bounds__(GRP_FINE_BLOCK) void k_table_count(ShiftCoarse cm, const GrpRec* __restrict__ rec,
+                                                               const u32x4* __restrict__ desc,
+                                                               const uint32_t* __restrict__ nchunks,
+                                                               uint32_t* __restrict__ kcount) {
+    extern __shared__ uint32_t lh[];
+    uint32_t klo, nf, j0, n;
+    if (!table_chunk(cm, desc, nchunks, rec, lh, klo, nf, j0, n)) return;
+    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK)
+        if (lh[f]) atomicAdd(&kcount[klo + f], lh[f]);
+}
+
+__global__ __launch_bounds__(GRP_FINE_BLOCK) void k_table_offsets(ShiftCoarse cm, const uint32_t* __restrict__ base,
+                                                                 uint32_t* __restrict__ kcount,
+                                                                 uint32_t* __restrict__ hist,
+                                                                 uint32_t* __restrict__ offs) {
+    __shared__ uint32_t sh[GRP_FINE_BLOCK / 64];
+    uint32_t klo, khi;
+    cm.range(blockIdx.x, klo, khi);
+    const uint32_t nf = khi - klo;
+    const uint32_t per = (nf + GRP_FINE_BLOCK - 1) / GRP_FINE_BLOCK;
+    const uint32_t f0 = threadIdx.x * per;
+    uint32_t sum = 0;
+    for (uint32_t q = 0; q < per; ++q)
+        if (f0 + q < nf) sum += kcount[klo + f0 + q];
+    uint32_t total;
+    uint32_t run = block_scan<GRP_FINE_BLOCK>(sum, sh, &total) + base[blockIdx.x];
+    for (uint32_t q = 0; q < per; ++q) {
+        const uint32_t f = f0 + q;
+        if (f < nf) {
+            const uint32_t cnt = kcount[klo + f];
+            hist[klo + f] = cnt;
+            offs[klo + f] = run;
+            kcount[klo + f] = run;
+            run += cnt;
+        }
+    }
+}
+
+__global__ __launch_bounds__(GRP_FINE_BLOCK) void k_table_scatter(ShiftCoarse cm, const GrpRec* __restrict__ rec,
+                                                                 const u32x4* __restrict__ desc,
+                                                                 const uint32_t* __restrict__ nchunks,
+                                                                 uint32_t* __restrict__ kcursor,
+                                                                 uint32_t* __restrict__ perm,
+                                                                 double* __restrict__ pos_sorted) {
+    extern __shared__ uint32_t lh[];
+    uint32_t klo, nf, j0, n;
+    if (!table_chunk(cm, desc, nchunks, rec, lh, klo, nf, j0, n)) return;
+    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK)
+        if (lh[f]) lh[f] = atomicAdd(&kcursor[klo + f], lh[f]);
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n; j += GRP_FINE_BLOCK) {
+        const u32x4* r = reinterpret_cast<const u32x4*>(rec + j0 + j);
+        const u32x4 a = load_global16(r), b = load_global16(r + 1);
+        grp_put<false>(pos_sorted, perm, atomicAdd(&lh[a.x - klo], 1u), a, b);
+    }
+}
 
 // ----------------------------------------------------------------- gather ---
 
@@ -67,11 +146,11 @@ __global__ __launch_bounds__(256) void k_gather(GatherArgs a) {
 }
 
 // LDS-tiled variant: persistent workgroups of B threads evaluate work items
-// (pieces of Morton tiles of T^3 cells, k_items).  A workgroup takes the items
-// of its home range in order, ITEM_TAKE at a time through the range's
-// counter, then those of the other ranges, and ends when every range is
-// exhausted; the next take is requested before the last item of the current
-// one is evaluated.  Home range: blockIdx % ITEM_RANGES with xcd_remap
+// (pieces of Morton tiles of T^3 cells, k_grp_fine).  A workgroup takes the
+// items of its home range in order, a unit at a time (ItemQueue), then those of
+// the other ranges, and ends when every range is exhausted; the next unit is
+// requested before the last item of the current one is evaluated.  Home
+// range: blockIdx % ITEM_RANGES with xcd_remap
 // (workgroups are dispatched to the XCDs in turn), 0 for every workgroup
 // without.  Consecutive items of one tile reuse the tile's block in LDS.
 // (the LDS block limits FP64 and padded FP32 blocks to about one wavefront
@@ -80,32 +159,26 @@ template <int N, typename CT, int C, bool GRAD, int T, int B>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
     sizeof(CT) == 8 || padded_points<CT, C>() ? 1 : 2))) void k_gather_tiled(GatherArgs a) {
     __shared__ u32x4 tile_v[tile_lds_bytes<N, CT, C, T, B>() / 16];
-    __shared__ uint32_t taken;
+    __shared__ uint32_t taken[2];
     // every value that steers a loop or branch holding a barrier is made
     // wave-uniform explicitly, so that those loops are scalar
-    const uint32_t W = __builtin_amdgcn_readfirstlane(a.ctl[0]);
-    const uint32_t home = a.xcd_remap ? uint32_t(blockIdx.x) % ITEM_RANGES : 0u;
+    ItemQueue<B> q;
     uint32_t prev = 0xffffffffu;  // bucket whose block the LDS holds
-    for (uint32_t r = 0; r < ITEM_RANGES; ++r) {
-        const uint32_t x = (home + r) % ITEM_RANGES;
-        const uint32_t lo = item_range_begin(W, x);
-        const uint32_t hi = item_range_begin(W, x + 1);
-        uint32_t i = item_take_finish<B>(item_take_issue(a.ctl, x), &taken);
-        while (lo + i < hi) {
-            const uint32_t m = min(ITEM_TAKE, hi - lo - i);
-            uint32_t next = 0;
-            for (uint32_t k = 0; k < m; ++k) {
-                const u32x4 it = a.items[lo + i + k];
-                const uint32_t cur = __builtin_amdgcn_readfirstlane(it.x);
-                const uint32_t start = __builtin_amdgcn_readfirstlane(it.y);
-                const uint32_t count = __builtin_amdgcn_readfirstlane(it.z);
-                if (k + 1 == m) next = item_take_issue(a.ctl, x);
-                bucket_eval<N, CT, C, GRAD, T, B>(a, cur, count, start, tile_v, cur != prev);
-                prev = cur;
-            }
-            i = item_take_finish<B>(next, &taken);
+    bool more = q.begin(a.src, taken, a.xcd_remap ? uint32_t(blockIdx.x) % ITEM_RANGES : 0u);
+    while (more) {
+        uint32_t next = q.m == 0 ? q.issue() : 0u;
+        for (uint32_t k = 0; k < q.m; ++k) {
+            const u32x4 it = a.src.items[q.i + k];
+            const uint32_t cur = __builtin_amdgcn_readfirstlane(it.x);
+            const uint32_t start = __builtin_amdgcn_readfirstlane(it.y);
+            const uint32_t count = __builtin_amdgcn_readfirstlane(it.z);
+            if (k + 1 == q.m) next = q.issue();
+            bucket_eval<N, CT, C, GRAD, T, B>(a, cur, count, start, tile_v, cur != prev);
+            prev = cur;
         }
+        more = q.settle(next);
     }
+    item_take_end(a.src.ctl);
 }
 
 // ------------------------------------------------------------- launchers ---
@@ -294,32 +367,52 @@ static GrpPlan bin_plan(const bsi_field* f, long P, int tile, int* shift) {
 }
 
 // Workspace of a binned evaluation (16-byte aligned): the grouping scratch,
-// then the binned positions (3P doubles), the permutation (P), the bucket
-// counts and first slots (nb each).
-BinLayout bin_layout(const bsi_field* f, long P, int tile) {
+// the binned particles (16 bytes each, FP64 fields 24), the permutation, and
+// with work items of at most `ichunk` particles (0: none) the items and their
+// control words.
+BinLayout bin_layout(const bsi_field* f, long P, int tile, uint32_t ichunk) {
     int shift = 0;
-    const size_t nb = bin_bucket_count(f, tile) + 1;
+    const GrpPlan g = bin_plan(f, P, tile, &shift);
     BinLayout l;
+    l.ichunk = ichunk;
     l.grp = 0;
-    l.pos = (grp_scratch_words(bin_plan(f, P, tile, &shift)) * sizeof(uint32_t) + 15) / 16 * 16;
-    l.perm = l.pos + 3 * size_t(P) * sizeof(double);
-    l.hist = l.perm + size_t(P) * sizeof(uint32_t);
-    l.offs = l.hist + nb * sizeof(uint32_t);
-    l.bytes = l.offs + nb * sizeof(uint32_t);
+    l.binned = (grp_scratch_words(g) * sizeof(uint32_t) + 15) / 16 * 16;
+    l.perm = l.binned + size_t(P) * (f->desc.coef == BSI_F64 ? 24 : 16);
+    l.items = (l.perm + size_t(P) * sizeof(uint32_t) + 15) / 16 * 16;
+    l.ctl = l.items + (ichunk ? grp_item_cap(g, ichunk) * sizeof(u32x4) : 0);
+    l.bytes = l.ctl + (ichunk ? ITEM_CTL_WORDS * sizeof(uint32_t) : 0);
     return l;
 }
 
-bsi_status bin_run(bsi_field* f, const double* pos, long P, int tile, void* scratch, uint32_t* perm,
-                   double* pos_sorted, uint32_t* hist, uint32_t* offs, hipStream_t s) {
-    const size_t nbf = bin_bucket_count(f, tile);
-    const size_t nb = nbf + 1;
+BinArrays bin_arrays(const bsi_field* f, long P, int tile, const BinLayout& l, void* ws) {
+    char* w = static_cast<char*>(ws);
     int shift = 0;
     const GrpPlan g = bin_plan(f, P, tile, &shift);
-    const GrpBuffers gb = grp_buffers(g, static_cast<uint32_t*>(scratch));
+    const GrpBuffers gb = grp_buffers(g, reinterpret_cast<uint32_t*>(w + l.grp));
+    BinArrays b;
+    b.units = item_units(g.mmax);
+    b.desc = gb.desc;
+    b.nchunks = gb.nchunks;
+    b.binned = w + l.binned;
+    b.perm = reinterpret_cast<uint32_t*>(w + l.perm);
+    b.items = l.ichunk ? w + l.items : nullptr;
+    b.ctl = l.ichunk ? reinterpret_cast<uint32_t*>(w + l.ctl) : nullptr;
+    return b;
+}
+
+bsi_status bin_run(bsi_field* f, const double* pos, long P, int tile, const BinLayout& l, void* ws, hipStream_t s) {
+    const size_t nbf = bin_bucket_count(f, tile);
+    int shift = 0;
+    const GrpPlan g = bin_plan(f, P, tile, &shift);
+    const GrpBuffers gb = grp_buffers(g, reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + l.grp));
+    const BinArrays b = bin_arrays(f, P, tile, l, ws);
     const MortonKey mk{cell_args(f, pos, P), tile, uint32_t(nbf), shift};
+    const ShiftCoarse cm{shift, uint32_t(nbf + 1)};
+    const OneField ls{b.ctl != nullptr};
+    const uint32_t ichunk = l.ichunk ? l.ichunk : GRP_CHUNK;
     {
         StageTimer tm(f->ctx, "bin_count", s);
-        grp_count(mk, g, gb, s);
+        grp_count(mk, g, gb, b.ctl, b.ctl ? ITEM_CTL_WORDS : 0, s);
     }
     {
         StageTimer tm(f->ctx, "bin_scan", s);
@@ -327,7 +420,9 @@ bsi_status bin_run(bsi_field* f, const double* pos, long P, int tile, void* scra
     }
     {
         StageTimer tm(f->ctx, "bin_scatter", s);
-        grp_scatter(mk, ShiftCoarse{shift, uint32_t(nb)}, g, gb, hist, offs, perm, pos_sorted, s);
+        u32x4* items = static_cast<u32x4*>(b.items);
+        if (f->desc.coef == BSI_F64) grp_scatter<false>(mk, cm, ls, g, gb, ichunk, b.perm, b.binned, items, s);
+        else grp_scatter<true>(mk, cm, ls, g, gb, ichunk, b.perm, b.binned, items, s);
     }
     BSI_HIP(hipGetLastError());
     return BSI_OK;
@@ -359,33 +454,15 @@ static int tiled_block(const bsi_field* f, int tile, const bsi_eval_config& cfg)
     return tiled_block_ct<uint16_t>(f->N, f->C, tile, wide);
 }
 
-// Work items of the tiled gather after the binning's arrays: at most one per
-// non-empty bucket plus one per `chunk` particles, 16 bytes each, then the
-// control words and the per-group item sums.
-struct ItemLayout {
-    size_t items, ctl, sums, bytes;
-    uint32_t chunk;
-};
-
-static ItemLayout item_layout(const bsi_field* f, long P, int tile, const bsi_eval_config& cfg, size_t base) {
-    ItemLayout l{};
-    const int B = tiled_block(f, tile, cfg);
-    l.items = l.ctl = l.bytes = base;
-    if (B == 0) return l;
-    l.chunk = uint32_t(B) * uint32_t(cfg.item_rounds > 0 ? cfg.item_rounds : 4);
-    const size_t nb = bin_bucket_count(f, tile) + 1;
-    const size_t cap = nb + size_t(P) / l.chunk + 1;
-    l.items = (base + 15) / 16 * 16;
-    l.ctl = l.items + cap * 16;
-    l.sums = l.ctl + ITEM_CTL_WORDS * sizeof(uint32_t);
-    l.bytes = l.sums + (nb + SCAN_CHUNK - 1) / SCAN_CHUNK * sizeof(uint32_t);
-    return l;
+// Particles per work item of the tiled gather (0: the direct gather runs).
+static uint32_t item_chunk(const bsi_field* f, int tile, const bsi_eval_config& cfg) {
+    return uint32_t(tiled_block(f, tile, cfg)) * uint32_t(cfg.item_rounds > 0 ? cfg.item_rounds : 4);
 }
 
 size_t eval_ws_bytes(const bsi_field* f, int64_t P, const bsi_eval_config& cfg) {
     const int tile = effective_tile(f, cfg);
     if (tile == 0 || P == 0) return 0;
-    return item_layout(f, P, tile, cfg, bin_layout(f, P, tile).bytes).bytes;
+    return bin_layout(f, P, tile, item_chunk(f, tile, cfg)).bytes;
 }
 
 bsi_status eval_check_config(const bsi_eval_config& cfg) {
@@ -407,26 +484,7 @@ bsi_status eval_bin_ws(bsi_field* f, const double* pos, int64_t P, const bsi_eva
     if (P == 0 || tile == 0) return BSI_OK;
     BSI_CHECK(ws != nullptr && reinterpret_cast<uintptr_t>(ws) % 16 == 0, BSI_E_INVAL,
               "binned evaluation needs a 16-byte aligned workspace");
-    const BinLayout l = bin_layout(f, P, tile);
-    char* w = static_cast<char*>(ws);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(w + l.hist);
-    uint32_t* offs = reinterpret_cast<uint32_t*>(w + l.offs);
-    BSI_TRY(bin_run(f, pos, P, tile, w + l.grp, reinterpret_cast<uint32_t*>(w + l.perm),
-                    reinterpret_cast<double*>(w + l.pos), hist, offs, s));
-    const ItemLayout il = item_layout(f, P, tile, cfg, l.bytes);
-    if (il.chunk > 0) {
-        StageTimer tm(f->ctx, "bin_items", s);
-        uint32_t* ctl = reinterpret_cast<uint32_t*>(w + il.ctl);
-        const long nb = long(bin_bucket_count(f, tile)) + 1;
-        const unsigned ng = unsigned((nb + SCAN_CHUNK - 1) / SCAN_CHUNK);
-        uint32_t* sums = reinterpret_cast<uint32_t*>(w + il.sums);
-        hipLaunchKernelGGL(k_item_sums, dim3(ng), dim3(SCAN_BLOCK), 0, s, hist, nb, il.chunk, sums);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_BLOCK), 0, s, sums, int(ng));
-        hipLaunchKernelGGL(k_items, dim3(ng), dim3(SCAN_BLOCK), 0, s, hist, offs, nb, il.chunk, sums,
-                           reinterpret_cast<u32x4*>(w + il.items), ctl);
-    }
-    BSI_HIP(hipGetLastError());
-    return BSI_OK;
+    return bin_run(f, pos, P, tile, bin_layout(f, P, tile, item_chunk(f, tile, cfg)), ws, s);
 }
 
 // The gather half: reads the binning eval_bin_ws left in ws for the same
@@ -440,28 +498,17 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
     ga.grid = f->grid;
     ga.pos = pos;
     ga.perm = nullptr;
-    ga.pos_sorted = nullptr;
-    ga.hist = nullptr;
-    ga.offs = nullptr;
-    ga.items = nullptr;
-    ga.ctl = nullptr;
+    ga.binned = nullptr;
+    ga.src = ItemSource{};
     size_t nbf = 0;
-    ItemLayout il{};
     if (tile > 0) {
         BSI_CHECK(ws != nullptr && reinterpret_cast<uintptr_t>(ws) % 16 == 0, BSI_E_INVAL,
                   "binned evaluation needs a 16-byte aligned workspace");
-        const BinLayout l = bin_layout(f, P, tile);
-        char* w = static_cast<char*>(ws);
-        ga.pos_sorted = reinterpret_cast<const double*>(w + l.pos);
-        ga.perm = reinterpret_cast<const uint32_t*>(w + l.perm);
-        ga.hist = reinterpret_cast<const uint32_t*>(w + l.hist);
-        ga.offs = reinterpret_cast<const uint32_t*>(w + l.offs);
+        const BinArrays b = bin_arrays(f, P, tile, bin_layout(f, P, tile, item_chunk(f, tile, cfg)), ws);
+        ga.perm = b.perm;
+        ga.binned = b.binned;
+        ga.src = item_source(b);
         nbf = bin_bucket_count(f, tile);
-        il = item_layout(f, P, tile, cfg, l.bytes);
-        if (il.chunk > 0) {
-            ga.items = reinterpret_cast<const u32x4*>(w + il.items);
-            ga.ctl = reinterpret_cast<uint32_t*>(w + il.ctl);
-        }
     }
     ga.u = u;
     ga.grad = grad;
@@ -473,7 +520,6 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
     ga.P1 = f->P[1];
     ga.P2 = f->P[2];
     ga.pitch2 = f->pitch2;
-    ga.tiles_per_group = uint32_t(cfg.tiles_per_group > 0 ? cfg.tiles_per_group : 4);
     ga.ih0 = f->inv_h[0];
     ga.ih1 = f->inv_h[1];
     ga.ih2 = f->inv_h[2];
@@ -482,14 +528,8 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
     ga.basis = f->basis;
     ga.cs = f->cs;
     const bool g = grad != nullptr;
-    if (ga.items) {
-        // the ranges' counters start at zero for every run over one binning
-        StageTimer tm(f->ctx, "bin_items", s);
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, ga.ctl + ITEM_CTL_STRIDE,
-                           long(ITEM_CTL_WORDS - ITEM_CTL_STRIDE), 0u);
-    }
     StageTimer tm(f->ctx, "gather", s);
-    if (ga.items) {
+    if (ga.src.items) {
         bool ok = false;
         // tile_block 256 asks for four wavefronts per 8^3 tile (dense tiles)
         const bool wide = cfg.tile_block == 256;
@@ -542,17 +582,27 @@ bsi_status debug_bins_run(bsi_field* f, const double* pos, int64_t P, int tile, 
         BSI_HIP(hipMemsetAsync(offs, 0, nb * sizeof(uint32_t), s));
         return BSI_OK;
     }
-    const BinLayout l = bin_layout(f, P, tile);
+    int shift = 0;
+    const GrpPlan g = bin_plan(f, P, tile, &shift);
+    const size_t words = (grp_scratch_words(g) + 3) / 4 * 4;
     void* ws = nullptr;
-    BSI_TRY(get_workspace(f->ctx->eval_ws, s, l.bytes, &ws));
-    char* w = static_cast<char*>(ws);
-    BSI_TRY(bin_run(f, pos, P, tile, w + l.grp, reinterpret_cast<uint32_t*>(w + l.perm),
-                    reinterpret_cast<double*>(w + l.pos), reinterpret_cast<uint32_t*>(w + l.hist),
-                    reinterpret_cast<uint32_t*>(w + l.offs), s));
-    BSI_HIP(hipMemcpyAsync(hist, w + l.hist, nb * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    BSI_HIP(hipMemcpyAsync(offs, w + l.offs, nb * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    BSI_HIP(hipMemcpyAsync(perm, w + l.perm, size_t(P) * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    BSI_HIP(hipMemcpyAsync(pos_sorted, w + l.pos, size_t(P) * 3 * sizeof(double), hipMemcpyDeviceToDevice, s));
+    BSI_TRY(get_workspace(f->ctx->eval_ws, s, (words + nb) * sizeof(uint32_t), &ws));
+    uint32_t* kcount = static_cast<uint32_t*>(ws) + words;
+    const GrpBuffers gb = grp_buffers(g, static_cast<uint32_t*>(ws));
+    const MortonKey mk{cell_args(f, pos, P), tile, uint32_t(nb - 1), shift};
+    const ShiftCoarse cm{shift, uint32_t(nb)};
+    const size_t lf = size_t(g.fine_max) * sizeof(uint32_t);
+    grp_count(mk, g, gb, nullptr, 0, s);
+    grp_scan(g, gb, s);
+    grp_coarse<false>(mk, cm, OneField{false}, g, gb, GRP_CHUNK, s);
+    hipLaunchKernelGGL(k_fill_u32, dim3(unsigned(std::min<size_t>((nb + 255) / 256, 4096))), dim3(256), 0, s, kcount,
+                       long(nb), 0u);
+    hipLaunchKernelGGL(k_table_count, dim3(g.mmax), dim3(GRP_FINE_BLOCK), lf, s, cm, gb.rec, gb.desc, gb.nchunks,
+                       kcount);
+    hipLaunchKernelGGL(k_table_offsets, dim3(g.ncoarse), dim3(GRP_FINE_BLOCK), 0, s, cm, gb.base, kcount, hist, offs);
+    hipLaunchKernelGGL(k_table_scatter, dim3(g.mmax), dim3(GRP_FINE_BLOCK), lf, s, cm, gb.rec, gb.desc, gb.nchunks,
+                       kcount, perm, pos_sorted);
+    BSI_HIP(hipGetLastError());
     return BSI_OK;
 }
 

@@ -52,10 +52,8 @@ __device__ __forceinline__ void bspline_weights2(AT t, AT* wdd) {
 
 struct HessArgs {
     const void* grid;
-    const double* pos_sorted;  // positions in binned order
+    const void* binned;        // the particles in binned order (RawParticle)
     const uint32_t* perm;      // particle of every binned slot
-    const uint32_t* hist;      // particles per Morton tile (tiled kernel)
-    const uint32_t* offs;      // first binned slot per Morton tile (tiled kernel)
     uint32_t nbf;              // finite tiles; tile nbf holds the particles without a cell
     long P;
     int n0, n1, n2, P1;
@@ -65,9 +63,32 @@ struct HessArgs {
     void* grad;  // or nullptr
     void* hess;
     unsigned long long* nonfinite;
-    const u32x4* items;        // work items (bucket, first slot, count) in bucket order (tiled kernel)
-    uint32_t* ctl;             // item count and per-range counters (tiled kernel)
+    ItemSource src;            // work items (tiled kernel)
 };
+
+// Cell and weights (value, first and second derivative, chain factors
+// included) of a binned particle; false when it has no cell.
+template <int N, typename AT>
+__device__ __forceinline__ bool hess_setup(const HessArgs& a, const RawParticle<AT>& raw, int* cell, AT (*w)[N],
+                                           AT (*wd)[N], AT (*wdd)[N]) {
+    const int n[3] = {a.n0, a.n1, a.n2};
+    const double ih[3] = {a.ih0, a.ih1, a.ih2};
+    AT t[3];
+    if (!locate(raw, n, ih, cell, t)) return false;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        bspline_weights<N, AT>(t[d], w[d], wd[d]);
+        bspline_weights2<N, AT>(t[d], wdd[d]);
+        const AT s = AT(ih[d]);
+        const AT s2 = AT(ih[d] * ih[d]);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            wd[d][k] *= s;
+            wdd[d][k] *= s2;
+        }
+    }
+    return true;
+}
 
 // One lane per binned slot j; results are written at the particle's index.
 template <int N, typename CT, int C>
@@ -76,14 +97,11 @@ __global__ __launch_bounds__(HESS_B) void k_gather_hess(HessArgs a) {
     const long j = long(blockIdx.x) * HESS_B + threadIdx.x;
     if (j >= a.P) return;
     const long p = long(a.perm[j]);
-    const double x[3] = {a.pos_sorted[3 * j], a.pos_sorted[3 * j + 1], a.pos_sorted[3 * j + 2]};
-    const int n[3] = {a.n0, a.n1, a.n2};
-    const double ih[3] = {a.ih0, a.ih1, a.ih2};
+    RawParticle<AT> raw;
+    raw.load(a.binned, j);
     int cell[3];
-    double t[3];
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) ok = cell_of(x[d], ih[d], n[d], cell[d], t[d]) && ok;
+    AT w[3][N], wd[3][N], wdd[3][N];
+    const bool ok = hess_setup<N, AT>(a, raw, cell, w, wd, wdd);
     AT* u = static_cast<AT*>(a.u) + p * C;
     AT* g = a.grad ? static_cast<AT*>(a.grad) + p * C * 3 : nullptr;
     AT* h = static_cast<AT*>(a.hess) + p * C * 6;
@@ -95,19 +113,6 @@ __global__ __launch_bounds__(HESS_B) void k_gather_hess(HessArgs a) {
         for (int c = 0; c < 6 * C; ++c) h[c] = nan;
         atomicAdd(a.nonfinite, 1ull);
         return;
-    }
-    AT w[3][N], wd[3][N], wdd[3][N];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        bspline_weights<N, AT>(AT(t[d]), w[d], wd[d]);
-        bspline_weights2<N, AT>(AT(t[d]), wdd[d]);
-        const AT s = AT(ih[d]);
-        const AT s2 = AT(ih[d] * ih[d]);
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            wd[d][k] *= s;
-            wdd[d][k] *= s2;
-        }
     }
     const CT* base = static_cast<const CT*>(a.grid) + (long(cell[0]) * a.P1 + cell[1]) * a.pitch2 +
                      long(cell[2]) * C;
@@ -185,33 +190,6 @@ __global__ __launch_bounds__(HESS_B) void k_gather_hess(HessArgs a) {
         h[6 * c + 4] = H12[c];
         h[6 * c + 5] = H22[c];
     }
-}
-
-// Cell and weights (value, first and second derivative, chain factors
-// included) of the particle at x; false when it has no cell.
-template <int N, typename AT>
-__device__ __forceinline__ bool hess_setup(const HessArgs& a, const double* x, int* cell, AT (*w)[N],
-                                           AT (*wd)[N], AT (*wdd)[N]) {
-    const int n[3] = {a.n0, a.n1, a.n2};
-    const double ih[3] = {a.ih0, a.ih1, a.ih2};
-    double t[3];
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) ok = cell_of(x[d], ih[d], n[d], cell[d], t[d]) && ok;
-    if (!ok) return false;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        bspline_weights<N, AT>(AT(t[d]), w[d], wd[d]);
-        bspline_weights2<N, AT>(AT(t[d]), wdd[d]);
-        const AT s = AT(ih[d]);
-        const AT s2 = AT(ih[d] * ih[d]);
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            wd[d][k] *= s;
-            wdd[d][k] *= s2;
-        }
-    }
-    return true;
 }
 
 // Sums over axis-0 planes: u, the three first and six second derivatives.
@@ -382,11 +360,11 @@ __device__ __forceinline__ void hess_piece(const HessArgs& a, uint32_t cur, uint
         const bool active = jj < count;
         const uint32_t slot = start + (active ? jj : 0u);
         const long p = long(a.perm[slot]);
-        const double x[3] = {a.pos_sorted[3 * long(slot)], a.pos_sorted[3 * long(slot) + 1],
-                             a.pos_sorted[3 * long(slot) + 2]};
+        RawParticle<AT> raw;
+        raw.load(a.binned, long(slot));
         int cell[3];
         AT w[3][N], wd[3][N], wdd[3][N];
-        hess_setup<N, AT>(a, x, cell, w, wd, wdd);  // finite by construction of the tile
+        hess_setup<N, AT>(a, raw, cell, w, wd, wdd);  // finite by construction of the tile
         const CT* base = tile + ((cell[0] - o0) * G::R1 + (cell[1] - o1)) * G::LROW + (cell[2] - o2) * C;
         auto rows = [base](int ia, int ib) { return base + (ia * G::R1 + ib) * G::LROW; };
         if (pair) {
@@ -421,7 +399,7 @@ __device__ __forceinline__ void hess_piece(const HessArgs& a, uint32_t cur, uint
 // rounds, so that a crowded tile, a dense cluster of particles, is shared by
 // several CUs).  As in the tiled gather, the items are split into one range per
 // XCD; a workgroup takes the items of its home range (blockIdx % ITEM_RANGES:
-// workgroups are dealt to the XCDs in turn) ITEM_TAKE at a time, then those of
+// workgroups are dealt to the XCDs in turn) a unit at a time, then those of
 // the other ranges, and consecutive items of one tile reuse its block in LDS.
 template <int N, typename CT, int C>
 __global__ __launch_bounds__(HESS_TB) void k_gather_hess_tiled(HessArgs a) {
@@ -429,30 +407,24 @@ __global__ __launch_bounds__(HESS_TB) void k_gather_hess_tiled(HessArgs a) {
     static_assert(sizeof(CT) != 2 || bf16_rows_fit<N, C, 8, G::LROW>(), "BF16 row reads would leave the LDS row");
     __shared__ u32x4 lds[G::SLOTS];
     // wave-uniform values steer every loop that holds a barrier
-    const uint32_t W = __builtin_amdgcn_readfirstlane(a.ctl[0]);
-    const uint32_t home = uint32_t(blockIdx.x) % ITEM_RANGES;
+    ItemQueue<HESS_TB> q;
     uint32_t prev = 0xffffffffu;  // tile whose block the LDS holds
-    for (uint32_t r = 0; r < ITEM_RANGES; ++r) {
-        const uint32_t x = (home + r) % ITEM_RANGES;
-        const uint32_t lo = item_range_begin(W, x);
-        const uint32_t hi = item_range_begin(W, x + 1);
-        uint32_t i = item_take_finish<HESS_TB>(item_take_issue(a.ctl, x), nullptr);
-        while (lo + i < hi) {
-            const uint32_t m = min(ITEM_TAKE, hi - lo - i);
-            uint32_t next = 0;
-            for (uint32_t k = 0; k < m; ++k) {
-                const u32x4 it = a.items[lo + i + k];
-                const uint32_t cur = __builtin_amdgcn_readfirstlane(it.x);
-                const uint32_t start = __builtin_amdgcn_readfirstlane(it.y);
-                const uint32_t count = __builtin_amdgcn_readfirstlane(it.z);
-                if (k + 1 == m) next = item_take_issue(a.ctl, x);
-                hess_piece<N, CT, C, G>(a, cur, start, count, lds, cur != prev);
-                if (cur != a.nbf) prev = cur;
-                lds_barrier();  // every LDS read done before a later piece refills it
-            }
-            i = item_take_finish<HESS_TB>(next, nullptr);
+    bool more = q.begin(a.src, nullptr, uint32_t(blockIdx.x) % ITEM_RANGES);
+    while (more) {
+        uint32_t next = q.m == 0 ? q.issue() : 0u;
+        for (uint32_t k = 0; k < q.m; ++k) {
+            const u32x4 it = a.src.items[q.i + k];
+            const uint32_t cur = __builtin_amdgcn_readfirstlane(it.x);
+            const uint32_t start = __builtin_amdgcn_readfirstlane(it.y);
+            const uint32_t count = __builtin_amdgcn_readfirstlane(it.z);
+            if (k + 1 == q.m) next = q.issue();
+            hess_piece<N, CT, C, G>(a, cur, start, count, lds, cur != prev);
+            if (cur != a.nbf) prev = cur;
+            lds_barrier();  // every LDS read done before a later piece refills it
         }
+        more = q.settle(next);
     }
+    item_take_end(a.src.ctl);
 }
 
 template <typename CT>
@@ -512,33 +484,19 @@ bsi_status hessian_run(bsi_field* f, const double* pos, int64_t P, void* u, void
     // table has at most 2^24 entries), for locality of the stencil reads
     const int nmax = std::max(f->n[0], std::max(f->n[1], f->n[2]));
     const int tile = std::max(8, (nmax + 255) / 256);
-    const BinLayout l = bin_layout(f, long(P), tile);
     const int coef = f->desc.coef;
     const bool tiled = tile == 8 && (coef == BSI_F64   ? hess_tiled_ok<double>(f->N, f->C)
                                      : coef == BSI_F32 ? hess_tiled_ok<float>(f->N, f->C)
                                                        : hess_tiled_ok<uint16_t>(f->N, f->C));
-    // work items of the tiled kernel after the binning's arrays: at most one
-    // per non-empty tile plus one per `chunk` particles, then the control
-    // words and the per-group item sums
-    const uint32_t chunk = uint32_t(HESS_TB) * HESS_ROUNDS;
-    const size_t nb = bin_bucket_count(f, tile) + 1;
-    const size_t o_items = (l.bytes + 15) / 16 * 16;
-    const size_t o_ctl = o_items + (nb + size_t(P) / chunk + 1) * 16;
-    const size_t o_sums = o_ctl + ITEM_CTL_WORDS * sizeof(uint32_t);
-    const size_t bytes = tiled ? o_sums + (nb + SCAN_CHUNK - 1) / SCAN_CHUNK * sizeof(uint32_t) : l.bytes;
+    const BinLayout l = bin_layout(f, long(P), tile, tiled ? uint32_t(HESS_TB) * HESS_ROUNDS : 0u);
     void* ws = nullptr;
-    BSI_TRY(get_workspace(f->ctx->eval_ws, s, bytes, &ws));
-    char* w = static_cast<char*>(ws);
-    uint32_t* perm = reinterpret_cast<uint32_t*>(w + l.perm);
-    double* pos_sorted = reinterpret_cast<double*>(w + l.pos);
-    BSI_TRY(bin_run(f, pos, long(P), tile, w + l.grp, perm, pos_sorted, reinterpret_cast<uint32_t*>(w + l.hist),
-                    reinterpret_cast<uint32_t*>(w + l.offs), s));
+    BSI_TRY(get_workspace(f->ctx->eval_ws, s, l.bytes, &ws));
+    BSI_TRY(bin_run(f, pos, long(P), tile, l, ws, s));
+    const BinArrays b = bin_arrays(f, long(P), tile, l, ws);
     HessArgs a;
     a.grid = f->grid;
-    a.pos_sorted = pos_sorted;
-    a.perm = perm;
-    a.hist = reinterpret_cast<const uint32_t*>(w + l.hist);
-    a.offs = reinterpret_cast<const uint32_t*>(w + l.offs);
+    a.binned = b.binned;
+    a.perm = b.perm;
     a.nbf = uint32_t(bin_bucket_count(f, tile));
     a.P = long(P);
     a.n0 = f->n[0];
@@ -553,24 +511,7 @@ bsi_status hessian_run(bsi_field* f, const double* pos, int64_t P, void* u, void
     a.grad = grad;
     a.hess = hess;
     a.nonfinite = f->counters;
-    a.items = nullptr;
-    a.ctl = nullptr;
-    if (tiled) {
-        StageTimer tm(f->ctx, "hess_items", s);
-        const uint32_t* hist = a.hist;
-        const unsigned ng = unsigned((nb + SCAN_CHUNK - 1) / SCAN_CHUNK);
-        uint32_t* sums = reinterpret_cast<uint32_t*>(w + o_sums);
-        u32x4* items = reinterpret_cast<u32x4*>(w + o_items);
-        uint32_t* ctl = reinterpret_cast<uint32_t*>(w + o_ctl);
-        hipLaunchKernelGGL(k_item_sums, dim3(ng), dim3(SCAN_BLOCK), 0, s, hist, long(nb), chunk, sums);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_BLOCK), 0, s, sums, int(ng));
-        hipLaunchKernelGGL(k_items, dim3(ng), dim3(SCAN_BLOCK), 0, s, hist, a.offs, long(nb), chunk, sums, items,
-                           ctl);
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, s, ctl + ITEM_CTL_STRIDE,
-                           long(ITEM_CTL_STRIDE * ITEM_RANGES), 0u);
-        a.items = items;
-        a.ctl = ctl;
-    }
+    a.src = item_source(b);
     {
         StageTimer tm(f->ctx, "gather_hess", s);
         if (tiled) {
