@@ -66,7 +66,7 @@ struct BatchArgs {
     const u32x4* desc;            // chunk descriptors of the grouping
     uint32_t* ctl;                // [class][ITEM_CTL_WORDS] take counters
     uint32_t* start;              // first chunk of each class (+ end)
-    uint32_t units;               // units per chunk
+    uint32_t ulog;                // 2^ulog units per chunk
 };
 
 // Grouping slots of a batch: item i owns the slots [pblk * BLK, (pblk +
@@ -96,8 +96,8 @@ struct BatchSlots {
         const double ih[3] = {it.ga.ih0, it.ga.ih1, it.ga.ih2};
         pl.ok = locate<double>(s.x, n, ih, pl.cell, pl.t);
         const uint32_t T = uint32_t(it.tile);
-        const uint32_t lk = pl.ok ? (spread3(uint32_t(pl.cell[0]) / T) << 2) |
-                                        (spread3(uint32_t(pl.cell[1]) / T) << 1) | spread3(uint32_t(pl.cell[2]) / T)
+        const uint32_t lk = pl.ok ? tile_key(uint32_t(pl.cell[0]) / T, uint32_t(pl.cell[1]) / T,
+                                             uint32_t(pl.cell[2]) / T)
                                   : it.nb - 1;
         pl.key = it.bbase + lk;
         pl.coarse = it.cbase + (lk >> it.cshift);
@@ -124,7 +124,11 @@ struct BatchLists {
     __device__ __forceinline__ const BatchItem& of(uint32_t c) const { return items[range_item[c]]; }
     __device__ __forceinline__ int slot(uint32_t c) const { return of(c).mode == MODE_DIRECT ? NCLASS : of(c).cls; }
     __device__ __forceinline__ bool wanted(uint32_t c) const { return of(c).mode != MODE_DIRECT; }
-    __device__ __forceinline__ uint32_t bias(uint32_t c) const { return of(c).bbase; }
+    __device__ __forceinline__ uint32_t origin(uint32_t c, uint32_t key) const {
+        const BatchItem& it = of(c);
+        const uint32_t k = key - it.bbase;
+        return k == it.nb - 1 ? NO_CELL : tile_origin(k, uint32_t(it.tile));
+    }
     __device__ __forceinline__ uint32_t tag(uint32_t c) const { return range_item[c]; }
     __device__ __forceinline__ void begin(uint32_t c, uint32_t g) const {
         for (int k = c == 0 ? 0 : slot(c - 1) + 1; k <= slot(c); ++k) start[k] = g;
@@ -148,24 +152,12 @@ __global__ __launch_bounds__(BATCH_B) void k_batch_tiles(BatchArgs b) {
     if constexpr (batch_tile_ok<N, CT, C, 8>()) {
         extern __shared__ u32x4 lds[];
         constexpr int cls = class_of(N, C);
-        ItemQueue<BATCH_B> q;
         const ItemSource src{b.work, b.desc, b.start + cls, b.start + cls + 1, b.ctl + cls * ITEM_CTL_WORDS,
-                             b.units};
-        bool more = q.begin(src, nullptr, uint32_t(blockIdx.x) % ITEM_RANGES);
-        while (more) {
-            uint32_t next = q.m == 0 ? q.issue() : 0u;
-            for (uint32_t k = 0; k < q.m; ++k) {
-                const u32x4 e = src.items[q.i + k];
-                const uint32_t bucket = __builtin_amdgcn_readfirstlane(e.x);
-                const uint32_t start = __builtin_amdgcn_readfirstlane(e.y);
-                const uint32_t count = __builtin_amdgcn_readfirstlane(e.z);
-                const uint32_t item = __builtin_amdgcn_readfirstlane(e.w);
-                if (k + 1 == q.m) next = q.issue();
-                bucket_eval<N, CT, C, GRAD, 8, BATCH_B>(b.items[item].ga, bucket, count, start, lds);
-            }
-            more = q.settle(next);
-        }
-        item_take_end(src.ctl);
+                             b.ulog};
+        using K = ValueGather<N, CT, C, GRAD, 8, BATCH_B / 64>;
+        __shared__ __align__(16) typename K::Shared shared;
+        tiled_gather<K, BATCH_B>([&](uint32_t tag, GatherArgs& a) { a = b.items[tag].ga; }, src,
+                                 uint32_t(blockIdx.x) % ITEM_RANGES, lds, &shared, nullptr);
     }
 }
 
@@ -228,7 +220,7 @@ template <typename CT>
 int tile_lds_ct(int N, int C, int T) {
     auto one = [&](auto n_, auto c_, auto t_) -> int {
         constexpr int n = decltype(n_)::value, c = decltype(c_)::value, t = decltype(t_)::value;
-        return tile_lds_bytes<n, CT, c, t, BATCH_B>();
+        return tile_lds_bytes<ValueGather<n, CT, c, true, t, BATCH_B / 64>>();
     };
     using I4 = std::integral_constant<int, 4>;
     using I6 = std::integral_constant<int, 6>;
@@ -297,7 +289,6 @@ static void item_mode(const bsi_field* f, const bsi_eval_config& c, int* mode, i
     *tile = std::max(c.sort_tile > 0 ? c.sort_tile : 8, tmin);
 }
 
-size_t bin_bucket_count(const bsi_field* f, int tile);  // eval.hip
 
 static bsi_status enqueue(bsi_batch* b, hipStream_t s) {
     bsi_ctx* ctx = b->ctx;
@@ -439,7 +430,7 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
         g.xcd_remap = 0;
         g.basis = BSI_BASIS_BSPLINE;
         g.cs = 1;
-        const size_t nbf = bin_bucket_count(f, tile);
+        const size_t nbf = bin_key_count(f, tile);
         g.nbuckets_finite = uint32_t(nbf);
         x.N = f->N;
         x.C = f->C;
@@ -562,7 +553,7 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     a.binned = base + o_pos;
     a.work = reinterpret_cast<u32x4*>(base + o_work);
     a.desc = b->gbuf.desc;
-    a.units = item_units(b->grp.mmax);
+    a.ulog = item_units_log2(b->grp.mmax, ITEM_UNITS_BATCH);
     a.ctl = reinterpret_cast<uint32_t*>(base + o_ctl);
     a.start = reinterpret_cast<uint32_t*>(base + o_start);
     for (auto& x : hi) {

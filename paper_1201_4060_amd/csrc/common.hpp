@@ -278,6 +278,8 @@ bsi_status debug_cells_run(bsi_field* f, const double* pos, int64_t P, int32_t* 
                            hipStream_t s);
 // the evaluation's binning alone, results copied to caller buffers
 size_t bin_bucket_count(const bsi_field* f, int tile);
+// keys of the evaluation's binning (whole bricks of 4^3 tiles)
+size_t bin_key_count(const bsi_field* f, int tile);
 // byte offsets of the binning's arrays in its 16-byte aligned workspace, the
 // arrays, and the binning itself; ichunk = most particles per work item of a
 // tiled gather (0: no items)
@@ -292,7 +294,7 @@ struct BinArrays {
     const void* desc;         // chunk descriptors and their number
     const uint32_t* nchunks;
     uint32_t* ctl;
-    uint32_t units;           // units per chunk the gather takes its items in
+    uint32_t units_log2;      // units per chunk the gather takes its items in
 };
 BinLayout bin_layout(const bsi_field* f, long P, int tile, uint32_t ichunk);
 BinArrays bin_arrays(const bsi_field* f, long P, int tile, const BinLayout& l, void* ws);

@@ -25,9 +25,11 @@ __global__ void k_debug_cells(CellArgs a, int32_t* cell, double* t) {
 
 // ---------------------------------------------------------------- binning ---
 
-// Key of a particle: the Morton index of its sort tile, or nbuckets_finite
-// for a non-finite position; its coarse range is key >> shift.
-struct MortonKey {
+// Key of a particle: that of its sort tile (MORTON: the tile's Morton index,
+// else tile_key), or nbuckets_finite for a non-finite position; its coarse range
+// is key >> shift.
+template <bool MORTON>
+struct TileKey {
     CellArgs a;
     int tile;
     uint32_t nbuckets_finite;
@@ -48,10 +50,11 @@ struct MortonKey {
         const double ih[3] = {a.ih0, a.ih1, a.ih2};
         pl.ok = locate<double>(s.x, n, ih, pl.cell, pl.t);
         pl.key = nbuckets_finite;
-        if (pl.ok)
-            pl.key = (spread3(uint32_t(pl.cell[0]) / uint32_t(tile)) << 2) |
-                     (spread3(uint32_t(pl.cell[1]) / uint32_t(tile)) << 1) |
-                     spread3(uint32_t(pl.cell[2]) / uint32_t(tile));
+        if (pl.ok) {
+            const uint32_t T = uint32_t(tile);
+            const uint32_t i = uint32_t(pl.cell[0]) / T, j = uint32_t(pl.cell[1]) / T, k = uint32_t(pl.cell[2]) / T;
+            pl.key = MORTON ? (spread3(i) << 2) | (spread3(j) << 1) | spread3(k) : tile_key(i, j, k);
+        }
         pl.coarse = pl.key >> shift;
     }
 };
@@ -145,40 +148,27 @@ __global__ __launch_bounds__(256) void k_gather(GatherArgs a) {
     direct_eval<N, CT, C, GRAD>(a, j);
 }
 
+// Wavefronts per SIMD that a tiled instance is compiled for: as many as its
+// registers allow without spilling (its LDS blocks may allow fewer).
+template <int N, typename CT, int C>
+constexpr int tiled_waves() {
+    if (sizeof(CT) == 8) return N == 6 || C == 3 ? 1 : 2;
+    return N < 6 && C == 1 ? 3 : 2;
+}
+
 // LDS-tiled variant: persistent workgroups of B threads evaluate work items
-// (pieces of Morton tiles of T^3 cells, k_grp_fine).  A workgroup takes the
-// items of its home range in order, a unit at a time (ItemQueue), then those of
-// the other ranges, and ends when every range is exhausted; the next unit is
-// requested before the last item of the current one is evaluated.  Home
-// range: blockIdx % ITEM_RANGES with xcd_remap
-// (workgroups are dispatched to the XCDs in turn), 0 for every workgroup
-// without.  Consecutive items of one tile reuse the tile's block in LDS.
-// (the LDS block limits FP64 and padded FP32 blocks to about one wavefront
-// per SIMD: the registers are not the limit there)
+// (pieces of Morton tiles of T^3 cells, k_grp_fine), with xcd_remap those of the
+// range blockIdx % ITEM_RANGES first (workgroups are dispatched to the XCDs in
+// turn).
 template <int N, typename CT, int C, bool GRAD, int T, int B>
-__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
-    sizeof(CT) == 8 || padded_points<CT, C>() ? 1 : 2))) void k_gather_tiled(GatherArgs a) {
-    __shared__ u32x4 tile_v[tile_lds_bytes<N, CT, C, T, B>() / 16];
-    __shared__ uint32_t taken[2];
-    // every value that steers a loop or branch holding a barrier is made
-    // wave-uniform explicitly, so that those loops are scalar
-    ItemQueue<B> q;
-    uint32_t prev = 0xffffffffu;  // bucket whose block the LDS holds
-    bool more = q.begin(a.src, taken, a.xcd_remap ? uint32_t(blockIdx.x) % ITEM_RANGES : 0u);
-    while (more) {
-        uint32_t next = q.m == 0 ? q.issue() : 0u;
-        for (uint32_t k = 0; k < q.m; ++k) {
-            const u32x4 it = a.src.items[q.i + k];
-            const uint32_t cur = __builtin_amdgcn_readfirstlane(it.x);
-            const uint32_t start = __builtin_amdgcn_readfirstlane(it.y);
-            const uint32_t count = __builtin_amdgcn_readfirstlane(it.z);
-            if (k + 1 == q.m) next = q.issue();
-            bucket_eval<N, CT, C, GRAD, T, B>(a, cur, count, start, tile_v, cur != prev);
-            prev = cur;
-        }
-        more = q.settle(next);
-    }
-    item_take_end(a.src.ctl);
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(tiled_waves<N, CT, C>()))) void
+k_gather_tiled(GatherArgs a) {
+    using K = ValueGather<N, CT, C, GRAD, T, B / 64>;
+    __shared__ u32x4 tile_v[tile_lds_bytes<K>() / 16];
+    __shared__ __align__(16) typename K::Shared shared;
+    __shared__ uint32_t taken[3];
+    tiled_gather<K, B>([&](uint32_t, GatherArgs& x) { x = a; }, a.src,
+                       a.xcd_remap ? uint32_t(blockIdx.x) % ITEM_RANGES : 0u, tile_v, &shared, taken);
 }
 
 // ------------------------------------------------------------- launchers ---
@@ -228,10 +218,17 @@ constexpr bool tile_ok() {
     return TileGeom<N, CT, C, T>::BYTES <= TILE_LDS_LIMIT && TileGeom<N, CT, C, T>::ALIGNED;
 }
 
-// 64 threads for small tiles, 256 for tiles whose block fills the LDS budget
+// Threads per workgroup: 64 for small blocks, 128 where at most five blocks of
+// 64 would fit a CU's LDS (5 * 10^6 particles at 512^3, FP32 order 6: 1382 us,
+// with 64 threads 1443; BF16, 14 KB blocks: 64 threads 1665, 128 1924; FP32
+// order 4, 21 KB: 165 and 171 at 256^3), 256 for blocks that fill the LDS budget.
+// FP64 instances hold up to 376 registers, one wavefront a SIMD: 128, so that two
+// workgroups share a CU and one copies while the other evaluates (300007 particles
+// at 192 x 128 x 256, order 6: 270 us; with 64 threads 287, with 256 364).
 template <int N, typename CT, int C, int T>
 constexpr int tile_block() {
-    return TileGeom<N, CT, C, T>::SLOTS >= 3072 ? 256 : 64;
+    if (sizeof(CT) == 8) return 128;
+    return TileGeom<N, CT, C, T>::SLOTS >= 3072 ? 256 : TileGeom<N, CT, C, T>::SLOTS >= 2048 ? 128 : 64;
 }
 
 // The tiled gather runs as many workgroups as can be resident at once (its
@@ -255,7 +252,7 @@ bool launch_tiled_T(const GatherArgs& ga, bool grad, bool wide, int num_cus, hip
         return false;
     } else {
         constexpr int B = tile_block<N, CT, C, T>();
-        if constexpr (T == 8 && B == 64) {
+        if constexpr (T == 8 && B < 256) {
             // dense 8^3 tiles: four wavefronts share one LDS block
             if (wide) {
                 if (grad) launch_tiled_kernel<N, CT, C, true, T, 256>(ga, num_cus, s);
@@ -274,7 +271,7 @@ bool launch_tiled_T(const GatherArgs& ga, bool grad, bool wide, int num_cus, hip
 template <int N, typename CT, int C, int T>
 constexpr int tiled_block_T(bool wide) {
     if constexpr (!tile_ok<N, CT, C, T>()) return 0;
-    else return (T == 8 && tile_block<N, CT, C, T>() == 64 && wide) ? 256 : tile_block<N, CT, C, T>();
+    else return (T == 8 && tile_block<N, CT, C, T>() < 256 && wide) ? 256 : tile_block<N, CT, C, T>();
 }
 
 template <int N, typename CT, int C>
@@ -358,9 +355,17 @@ size_t bin_bucket_count(const bsi_field* f, int tile) {
     return size_t(1) << (3 * bits);
 }
 
+size_t bin_key_count(const bsi_field* f, int tile) {
+    // whole bricks of 4^3 tiles, as many along every axis (a power of two)
+    int bits = 0;
+    for (int d = 0; d < 3; ++d)
+        while (((4 * tile) << bits) < f->n[d]) ++bits;
+    return size_t(64) << (3 * bits);
+}
+
 // At most 2^24 + 1 keys (effective_tile).
-static GrpPlan bin_plan(const bsi_field* f, long P, int tile, int* shift) {
-    const uint64_t nb = bin_bucket_count(f, tile) + 1;
+static GrpPlan bin_plan(size_t keys, long P, int* shift) {
+    const uint64_t nb = keys + 1;
     *shift = grp_shift(nb, P);
     const uint32_t ncoarse = uint32_t((nb + (uint64_t(1) << *shift) - 1) >> *shift);
     return grp_plan(P, uint32_t(P), uint32_t(nb), ncoarse, uint32_t(std::min<uint64_t>(nb, uint64_t(1) << *shift)));
@@ -372,7 +377,7 @@ static GrpPlan bin_plan(const bsi_field* f, long P, int tile, int* shift) {
 // control words.
 BinLayout bin_layout(const bsi_field* f, long P, int tile, uint32_t ichunk) {
     int shift = 0;
-    const GrpPlan g = bin_plan(f, P, tile, &shift);
+    const GrpPlan g = bin_plan(bin_key_count(f, tile), P, &shift);
     BinLayout l;
     l.ichunk = ichunk;
     l.grp = 0;
@@ -387,10 +392,10 @@ BinLayout bin_layout(const bsi_field* f, long P, int tile, uint32_t ichunk) {
 BinArrays bin_arrays(const bsi_field* f, long P, int tile, const BinLayout& l, void* ws) {
     char* w = static_cast<char*>(ws);
     int shift = 0;
-    const GrpPlan g = bin_plan(f, P, tile, &shift);
+    const GrpPlan g = bin_plan(bin_key_count(f, tile), P, &shift);
     const GrpBuffers gb = grp_buffers(g, reinterpret_cast<uint32_t*>(w + l.grp));
     BinArrays b;
-    b.units = item_units(g.mmax);
+    b.units_log2 = item_units_log2(g.mmax, ITEM_UNITS);
     b.desc = gb.desc;
     b.nchunks = gb.nchunks;
     b.binned = w + l.binned;
@@ -401,14 +406,14 @@ BinArrays bin_arrays(const bsi_field* f, long P, int tile, const BinLayout& l, v
 }
 
 bsi_status bin_run(bsi_field* f, const double* pos, long P, int tile, const BinLayout& l, void* ws, hipStream_t s) {
-    const size_t nbf = bin_bucket_count(f, tile);
+    const size_t nbf = bin_key_count(f, tile);
     int shift = 0;
-    const GrpPlan g = bin_plan(f, P, tile, &shift);
+    const GrpPlan g = bin_plan(nbf, P, &shift);
     const GrpBuffers gb = grp_buffers(g, reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + l.grp));
     const BinArrays b = bin_arrays(f, P, tile, l, ws);
-    const MortonKey mk{cell_args(f, pos, P), tile, uint32_t(nbf), shift};
+    const TileKey<false> mk{cell_args(f, pos, P), tile, uint32_t(nbf), shift};
     const ShiftCoarse cm{shift, uint32_t(nbf + 1)};
-    const OneField ls{b.ctl != nullptr};
+    const OneField ls{b.ctl != nullptr, uint32_t(tile), uint32_t(nbf)};
     const uint32_t ichunk = l.ichunk ? l.ichunk : GRP_CHUNK;
     {
         StageTimer tm(f->ctx, "bin_count", s);
@@ -508,7 +513,7 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
         ga.perm = b.perm;
         ga.binned = b.binned;
         ga.src = item_source(b);
-        nbf = bin_bucket_count(f, tile);
+        nbf = bin_key_count(f, tile);
     }
     ga.u = u;
     ga.grad = grad;
@@ -583,18 +588,18 @@ bsi_status debug_bins_run(bsi_field* f, const double* pos, int64_t P, int tile, 
         return BSI_OK;
     }
     int shift = 0;
-    const GrpPlan g = bin_plan(f, P, tile, &shift);
+    const GrpPlan g = bin_plan(nb - 1, P, &shift);
     const size_t words = (grp_scratch_words(g) + 3) / 4 * 4;
     void* ws = nullptr;
     BSI_TRY(get_workspace(f->ctx->eval_ws, s, (words + nb) * sizeof(uint32_t), &ws));
     uint32_t* kcount = static_cast<uint32_t*>(ws) + words;
     const GrpBuffers gb = grp_buffers(g, static_cast<uint32_t*>(ws));
-    const MortonKey mk{cell_args(f, pos, P), tile, uint32_t(nb - 1), shift};
+    const TileKey<true> mk{cell_args(f, pos, P), tile, uint32_t(nb - 1), shift};
     const ShiftCoarse cm{shift, uint32_t(nb)};
     const size_t lf = size_t(g.fine_max) * sizeof(uint32_t);
     grp_count(mk, g, gb, nullptr, 0, s);
     grp_scan(g, gb, s);
-    grp_coarse<false>(mk, cm, OneField{false}, g, gb, GRP_CHUNK, s);
+    grp_coarse<false>(mk, cm, OneField{}, g, gb, GRP_CHUNK, s);
     hipLaunchKernelGGL(k_fill_u32, dim3(unsigned(std::min<size_t>((nb + 255) / 256, 4096))), dim3(256), 0, s, kcount,
                        long(nb), 0u);
     hipLaunchKernelGGL(k_table_count, dim3(g.mmax), dim3(GRP_FINE_BLOCK), lf, s, cm, gb.rec, gb.desc, gb.nchunks,

@@ -74,6 +74,22 @@ static __global__ void k_fill_u32(uint32_t* p, long n, uint32_t v) {
         p[i] = v;
 }
 
+// Key of the tile with coordinates (a, b, c) in the evaluation's binning: bricks
+// of 4^3 tiles in Morton order, in a brick four tiles along axis 0 in a row (a
+// tiled gather slides its block from one to the next), the rows in 2D Morton order.
+__device__ __forceinline__ uint32_t tile_key(uint32_t a, uint32_t b, uint32_t c) {
+    const uint32_t brick = (spread3(a >> 2) << 2) | (spread3(b >> 2) << 1) | spread3(c >> 2);
+    return (brick << 6) | ((b & 2u) << 4) | ((c & 2u) << 3) | ((b & 1u) << 3) | ((c & 1u) << 2) | (a & 3u);
+}
+// First cell of that tile (T cells an edge), packed as pack_cell does.
+__device__ __forceinline__ uint32_t tile_origin(uint32_t key, uint32_t T) {
+    const uint32_t brick = key >> 6;
+    const uint32_t a = (compact3(brick >> 2) << 2) | (key & 3u);
+    const uint32_t b = (compact3(brick >> 1) << 2) | ((key >> 4) & 2u) | ((key >> 3) & 1u);
+    const uint32_t c = (compact3(brick) << 2) | ((key >> 3) & 2u) | ((key >> 2) & 1u);
+    return (a * T << 20) | (b * T << 10) | (c * T);
+}
+
 // 16 bytes as a native vector (loads and stores of it are single instructions,
 // never aggregate copies) and a load of it from global memory.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -249,17 +265,26 @@ static __global__ __launch_bounds__(1024) void k_grp_scan(uint32_t* __restrict__
 }
 
 // ---- work items -----------------------------------------------------------
-// (bucket, first binned slot, count, tag): a piece of a run of one bucket.
+// (first cell of the tile or NO_CELL, first binned slot, count, tag): a piece of a
+// run of one bucket.
 // A chunk's items stand together, in key order, at slots reserved for it by the
 // chunk plan (descriptor word 3; the fine pass puts their count in word 2).
-// The tiled gathers take item_units-ths of a chunk's items, so that no list of
-// all items is needed: one kept in order costs another launch, one appended to
-// by the chunks as they finish loses the order (512^3 with 10^7 particles:
-// gather 2138 instead of 1990 us, neighbouring tiles no longer meet in L2) and
-// its counters serialise.
-// Units of about four items where there are many chunks (fewer atomics per
-// item), down to single items where there are few, so that every CU gets some.
-inline uint32_t item_units(uint32_t chunks) { return std::min(64u, std::max(8u, 8192u / std::max(chunks, 1u))); }
+// The tiled gathers take them in units, equal parts of a chunk's items, so that
+// no list of all items is needed: one kept in order costs another launch, one
+// appended to by the chunks as they finish loses the order.  Eight units a
+// chunk where there are many chunks (a unit is then mostly a row of four tiles),
+// more where there are few, so that every CU gets some: `target` units at least.
+// One field: 8192 (10^6 particles at 256^3, order 6 / FP64 at 192 x 128 x 256: 217 /
+// 299 us, with 16384 230 / 287, with 32768 254 / 286 -- the next unit's loads
+// are hidden behind four items).  A batch, whose fields differ in what an item
+// costs: 32768 (31 fields of up to 128^3, orders 4 and 6: 119 + 230 us with 8192,
+// 129 + 188 with 32768, 150 + 212 with 65536).
+constexpr uint32_t ITEM_UNITS = 8192, ITEM_UNITS_BATCH = 32768;
+inline uint32_t item_units_log2(uint32_t chunks, uint32_t target) {
+    uint32_t l = 3;
+    while (l < 6 && (uint64_t(chunks) << l) < target) ++l;
+    return l;
+}
 // The chunks are split into ITEM_RANGES contiguous ranges, one per XCD
 // (neighbouring tiles, whose blocks overlap, meet in the same L2); the next
 // unit of range x is counted at ITEM_CTL_STRIDE * x, each counter on a 128-byte
@@ -277,8 +302,11 @@ __host__ __device__ inline uint32_t item_range_begin(uint32_t x, uint32_t nch) {
 // The items of a single evaluation.
 struct OneField {
     bool items;
+    uint32_t tile, nbuckets_finite;
     __device__ __forceinline__ bool wanted(uint32_t) const { return items; }
-    __device__ __forceinline__ uint32_t bias(uint32_t) const { return 0; }
+    __device__ __forceinline__ uint32_t origin(uint32_t, uint32_t key) const {
+        return key == nbuckets_finite ? NO_CELL : tile_origin(key, tile);
+    }
     __device__ __forceinline__ uint32_t tag(uint32_t) const { return 0; }
     // the chunk plan tells that the chunks of range c start at chunk g
     __device__ __forceinline__ void begin(uint32_t, uint32_t) const {}
@@ -422,24 +450,13 @@ __device__ __forceinline__ void grp_put(void* out, uint32_t* perm, uint32_t d, c
     }
 }
 
-template <typename Coarse, typename Lists, bool PACK>
-static __global__ __launch_bounds__(GRP_FINE_BLOCK) void k_grp_fine(
-    Coarse cm, Lists ls, const GrpRec* __restrict__ rec, u32x4* __restrict__ desc,
-    const uint32_t* __restrict__ nchunks, uint32_t ichunk, uint32_t* __restrict__ perm, void* __restrict__ out,
-    u32x4* __restrict__ items) {
-    extern __shared__ uint32_t lh[];
-    __shared__ uint32_t sh[GRP_FINE_BLOCK / 64];
-    constexpr int PER = int(GRP_CHUNK) / GRP_FINE_BLOCK;
-    const uint32_t g = blockIdx.x;
-    if (g >= __builtin_amdgcn_readfirstlane(*nchunks)) return;
-    const u32x4 de = desc[g];
-    const uint32_t c = __builtin_amdgcn_readfirstlane(de.x);
-    const uint32_t j0 = __builtin_amdgcn_readfirstlane(de.y);
-    const uint32_t n = __builtin_amdgcn_readfirstlane(de.z);
-    uint32_t klo, khi;
-    cm.range(c, klo, khi);
-    klo = __builtin_amdgcn_readfirstlane(klo);
-    const uint32_t nf = __builtin_amdgcn_readfirstlane(khi) - klo;
+// The chunk of n <= PER * GRP_FINE_BLOCK records from slot j0, keys [klo, klo +
+// nf).  All its loads are issued at once.
+template <int PER, bool PACK, typename Lists>
+__device__ __forceinline__ void grp_sort_chunk(const Lists& ls, const GrpRec* __restrict__ rec, u32x4* desc, uint32_t c,
+                                               uint32_t j0, uint32_t n, uint32_t slot, uint32_t klo, uint32_t nf,
+                                               uint32_t ichunk, uint32_t* __restrict__ perm, void* __restrict__ out,
+                                               u32x4* __restrict__ items, uint32_t* lh, uint32_t* sh) {
     u32x4 a[PER], b[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -469,8 +486,8 @@ static __global__ __launch_bounds__(GRP_FINE_BLOCK) void k_grp_fine(
     uint32_t run = block_scan<GRP_FINE_BLOCK>(sum, sh, &total);
     uint32_t at = 0;
     if (emit) {
-        at = block_scan<GRP_FINE_BLOCK>(pieces, sh, &total) + de.w;
-        if (threadIdx.x == 0) reinterpret_cast<uint32_t*>(desc + g)[2] = total;
+        at = block_scan<GRP_FINE_BLOCK>(pieces, sh, &total) + slot;
+        if (threadIdx.x == 0) reinterpret_cast<uint32_t*>(desc)[2] = total;
     }
     for (uint32_t q = 0; q < per; ++q) {
         const uint32_t f = f0 + q;
@@ -479,13 +496,39 @@ static __global__ __launch_bounds__(GRP_FINE_BLOCK) void k_grp_fine(
         lh[f] = j0 + run;
         if (emit)
             for (uint32_t k = 0; k < cnt; k += ichunk)
-                items[at++] = u32x4{klo + f - ls.bias(c), j0 + run + k, min(ichunk, cnt - k), ls.tag(c)};
+                items[at++] = u32x4{ls.origin(c, klo + f), j0 + run + k, min(ichunk, cnt - k), ls.tag(c)};
         run += cnt;
     }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < PER; ++q)
         if (q * GRP_FINE_BLOCK + threadIdx.x < n) grp_put<PACK>(out, perm, lh[a[q].x - klo] + rank[q], a[q], b[q]);
+}
+
+template <typename Coarse, typename Lists, bool PACK>
+static __global__ __launch_bounds__(GRP_FINE_BLOCK) void k_grp_fine(
+    Coarse cm, Lists ls, const GrpRec* __restrict__ rec, u32x4* __restrict__ desc,
+    const uint32_t* __restrict__ nchunks, uint32_t ichunk, uint32_t* __restrict__ perm, void* __restrict__ out,
+    u32x4* __restrict__ items) {
+    extern __shared__ uint32_t lh[];
+    __shared__ uint32_t sh[GRP_FINE_BLOCK / 64];
+    const uint32_t g = blockIdx.x;
+    if (g >= __builtin_amdgcn_readfirstlane(*nchunks)) return;
+    const u32x4 de = desc[g];
+    const uint32_t c = __builtin_amdgcn_readfirstlane(de.x);
+    const uint32_t j0 = __builtin_amdgcn_readfirstlane(de.y);
+    const uint32_t n = __builtin_amdgcn_readfirstlane(de.z);
+    uint32_t klo, khi;
+    cm.range(c, klo, khi);
+    klo = __builtin_amdgcn_readfirstlane(klo);
+    const uint32_t nf = __builtin_amdgcn_readfirstlane(khi) - klo;
+    auto sort = [&](auto per) {
+        grp_sort_chunk<decltype(per)::value, PACK>(ls, rec, desc + g, c, j0, n, de.w, klo, nf, ichunk, perm, out, items,
+                                                   lh, sh);
+    };
+    // half as many records a thread where the range is an evenly filled one
+    if (n <= 4 * GRP_FINE_BLOCK) sort(std::integral_constant<int, 4>{});
+    else sort(std::integral_constant<int, int(GRP_CHUNK) / GRP_FINE_BLOCK>{});
 }
 
 // Coarse ranges of a single key space: range c = [c << s, min((c + 1) << s, nb)).
@@ -630,6 +673,12 @@ __device__ __forceinline__ AT widen(CT v) {
     else return AT(v);
 }
 
+// a * b + c with one rounding, written out where the compiler would otherwise
+// fuse in one kernel and not in another (products that two methods' weights have
+// in common are moved out of the branch between them).
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // w_j(t) = sum_i M[j][i] t^i and w'_j(t) = sum_i M1[j][i] t^i (Horner), with
 // the matrices of a compile-time table (M from the Section 7 general formula
 // for the B-spline).
@@ -640,11 +689,11 @@ __device__ __forceinline__ void bspline_weights(AT t, AT* w, AT* wd) {
     for (int j = 0; j < N; ++j) {
         AT acc = AT(B.M[j][N - 1]);
 #pragma unroll
-        for (int i = N - 2; i >= 0; --i) acc = acc * t + AT(B.M[j][i]);
+        for (int i = N - 2; i >= 0; --i) acc = fused(acc, t, AT(B.M[j][i]));
         w[j] = acc;
         AT dacc = AT(B.M1[j][N - 2]);
 #pragma unroll
-        for (int i = N - 3; i >= 0; --i) dacc = dacc * t + AT(B.M1[j][i]);
+        for (int i = N - 3; i >= 0; --i) dacc = fused(dacc, t, AT(B.M1[j][i]));
         wd[j] = dacc;
     }
 }
@@ -674,12 +723,12 @@ struct ItemSource {
     const u32x4* desc;
     const uint32_t *g0, *g1;
     uint32_t* ctl;       // take counters (ITEM_CTL_WORDS)
-    uint32_t units;      // units per chunk
+    uint32_t ulog;       // 2^ulog units per chunk
 };
 
 inline ItemSource item_source(const BinArrays& b) {
     return ItemSource{static_cast<const u32x4*>(b.items), static_cast<const u32x4*>(b.desc), nullptr, b.nchunks, b.ctl,
-                      b.units};
+                      b.units_log2};
 }
 
 struct GatherArgs {
@@ -736,6 +785,8 @@ struct RawParticle {
     __device__ __forceinline__ void load(const void* binned, long j) {
         r = load_global16(static_cast<const u32x4*>(binned) + j);
     }
+    // the compiler waits here for the loads of this particle and its index
+    __device__ __forceinline__ void settle(uint32_t& p) { asm volatile("" : "+v"(r), "+v"(p)); }
 };
 template <>
 struct RawParticle<double> {
@@ -746,6 +797,9 @@ struct RawParticle<double> {
         x[0] = p[0];
         x[1] = p[1];
         x[2] = p[2];
+    }
+    __device__ __forceinline__ void settle(uint32_t& p) {
+        asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(p));
     }
 };
 
@@ -1091,16 +1145,6 @@ __device__ __forceinline__ void store_sum(const GatherArgs& a, long p, const Par
     }
 }
 
-template <int N, typename CT, typename AT, int C, bool GRAD, bool FENCE = false, typename RowFn>
-__device__ __forceinline__ void contract_and_store(const GatherArgs& a, long p, const AT (*w)[N],
-                                                   const AT (*wd)[N], RowFn row) {
-    Partial<AT, C> lo, hi;
-    contract_planes<N, CT, AT, C, GRAD, N / 2, FENCE>(w[0], wd[0], w, wd, row, lo);
-    contract_planes<N, CT, AT, C, GRAD, N / 2, FENCE>(
-        w[0] + N / 2, wd[0] + N / 2, w, wd, [&](int k, int ib) { return row(N / 2 + k, ib); }, hi);
-    store_sum<AT, C, GRAD>(a, p, lo, hi);
-}
-
 // FP32 three-component blocks hold one grid point per 16-byte LDS slot (the
 // fourth float is spare): a stencil row is then N aligned 16-byte LDS reads
 // wherever it starts, where densely packed 12-byte points need 4-byte reads.
@@ -1109,46 +1153,45 @@ constexpr bool padded_points() {
     return sizeof(CT) == 4 && C == 3;
 }
 
-// Lanes per particle for sparse boxes (0: none): order 6 -> three lanes of
-// two axis-0 planes each, order 4 -> four lanes of one plane each.
-template <int N>
-constexpr int split_lanes() {
-    return N == 6 ? 3 : (N == 4 ? 4 : 0);
-}
-
-// LDS copy of the (T0+N-1) x (T1+N-1) x (T2+N-1) block of grid points that
-// the particles of a T0 x T1 x T2 cell box read: rows along axis 2, either
-// packed densely and padded to whole 16-byte chunks (PAD false), or one
-// 16-byte slot per point (PAD true).
-template <int N, typename CT, int C, int T0, int T1, int T2, bool PAD = padded_points<CT, C>()>
-struct BlockGeom {
+// LDS copy of the (T+N-1)^3 block of grid points that the particles of a tile of T^3
+// cells read: rows along axis 2, either packed densely and padded to whole
+// 16-byte chunks (PAD false), or one 16-byte slot per point (PAD true).
+template <int N, typename CT, int C, int T, bool PAD = padded_points<CT, C>()>
+struct TileGeom {
     static_assert(!PAD || padded_points<CT, C>(), "padded points: FP32, three components");
     static constexpr bool PADDED = PAD;
-    static constexpr int R0 = T0 + N - 1;
-    static constexpr int R1 = T1 + N - 1;
-    static constexpr int R2 = T2 + N - 1;
+    static constexpr int R0 = T + N - 1;
+    static constexpr int R1 = T + N - 1;
+    static constexpr int R2 = T + N - 1;
     static constexpr int VEC = 16 / int(sizeof(CT));                // elements per 16-byte slot
     static constexpr int PS = PAD ? VEC : C;                        // LDS pitch of a point (elements)
     static constexpr int CH = PAD ? R2 : (R2 * C + VEC - 1) / VEC;  // 16-byte slots per row
     static constexpr int LROW = CH * VEC;                           // LDS row pitch (elements)
-    static constexpr int ROWS = R0 * R1;
-    static constexpr int SLOTS = ROWS * CH;
+    static constexpr int PLANE = R1 * CH;                           // 16-byte slots per axis-0 plane
+    static constexpr int SLOTS = R0 * PLANE;
     static constexpr int BYTES = SLOTS * 16;
     // packed rows are copied in 16-byte chunks from the block origin, which
     // must then start on a 16-byte boundary inside a grid row; padded points
     // are copied one point (4-byte aligned) per slot
-    static constexpr bool ALIGNED = PAD || (T2 * C * int(sizeof(CT))) % 16 == 0;
+    static constexpr bool ALIGNED = PAD || (T * C * int(sizeof(CT))) % 16 == 0;
 };
 
-// Cubic Morton tiles of T^3 cells.
-template <int N, typename CT, int C, int T, bool PAD = padded_points<CT, C>()>
-using TileGeom = BlockGeom<N, CT, C, T, T, T, PAD>;
-
-
-template <typename AT>
-__device__ __forceinline__ AT shfl_xor1(AT v) {
-    return __shfl_xor(v, 1, 64);
+// v of the lane that the DPP quad permutation CTRL names (lanes of one group of
+// four): a vector instruction, where a shuffle goes through the LDS pipe that
+// the stencil reads already fill.
+template <int CTRL, typename AT>
+__device__ __forceinline__ AT quad_lane(AT v) {
+    if constexpr (sizeof(AT) == 8) {
+        const unsigned long long b = __double_as_longlong(v);
+        const uint32_t lo = __builtin_amdgcn_mov_dpp(int(uint32_t(b)), CTRL, 0xf, 0xf, true);
+        const uint32_t hi = __builtin_amdgcn_mov_dpp(int(uint32_t(b >> 32)), CTRL, 0xf, 0xf, true);
+        return __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
+    } else {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+    }
 }
+constexpr int QUAD_XOR1 = 0xb1;  // lanes 1 0 3 2
+constexpr int QUAD_XOR2 = 0x4e;  // lanes 2 3 0 1
 
 // Barrier for LDS only: orders the wavefront's LDS accesses without waiting for
 // outstanding global loads (the next tile's prefetch stays in flight).
@@ -1158,43 +1201,125 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Requests the LDS copy of the block of geometry G with cell origin (o0, o1,
-// o2) in the ghost-padded grid (row pitch pitch2 elements, P1 rows per plane):
-// slots tid, tid + B, ... are copied global -> LDS by the DMA path of the load
-// unit (no registers hold the data), each wavefront's instruction q filling 64
-// consecutive 16-byte slots from its wave-uniform LDS base; only the last step
-// can reach past the block, and its lanes there are masked off.  A packed slot
-// is the row's next 16-byte chunk; a padded slot is the 16 bytes from its
-// point's first element (the point and the first element of the next one).
-// Rows outside the padded grid (partial blocks only; never read by a
-// particle) load the block origin instead; reads past a row's end land in the
-// next row, its pitch padding or the allocation's slack.  Does not wait for
-// the loads.
-template <int N, typename CT, int C, typename G, int B>
-__device__ __forceinline__ void block_dma(const CT* grid, int n0, int n1, int P1, long pitch2, int o0, int o1,
-                                          int o2, u32x4* lds) {
-    constexpr int PERB = (G::SLOTS + B - 1) / B;
-    const int tid = threadIdx.x;
-    const int lim0 = n0 + N - 1 - o0;
-    const int lim1 = n1 + N - 1 - o1;
-    const CT* g = grid + (long(o0) * P1 + o1) * pitch2 + long(o2) * C;
-    // offsets inside a block stay < 2^31 elements
-    const int p1e = int(pitch2);
-    const int p0e = P1 * p1e;
-    const int wbase = __builtin_amdgcn_readfirstlane(tid & ~63);
+// Steps of 64 slots that copy one plane of a block.
+template <typename G>
+constexpr int plane_steps() {
+    return (G::PLANE + 63) / 64;
+}
+
+// Byte offsets, from DMA_BIAS before a plane's origin in the grid, of the 16 bytes
+// that this lane copies to slot k * 64 + lane of the plane, less the k * 1024 that
+// the copy adds to both of its addresses: for a packed block the row's next
+// 16-byte chunk, for padded points the 16 bytes from the point's first element
+// (the point and the first element of the next one).
+constexpr uint32_t DMA_BIAS = 8192;
+template <typename CT, int C, typename G>
+__device__ __forceinline__ void plane_offsets(int pitch2, uint32_t* off) {
 #pragma unroll
-    for (int q = 0; q < PERB; ++q) {
-        const int sl = q * B + tid;
-        const int row = sl / G::CH;
-        const int ch = sl - row * G::CH;
-        const int r0 = row / G::R1;
-        const int r1 = row - r0 * G::R1;
-        const bool ok = r0 < lim0 && r1 < lim1;
-        const int e = ok ? r0 * p0e + r1 * p1e + ch * (G::PADDED ? C : G::VEC) : 0;
-        if (q < PERB - 1 || sl < G::SLOTS)
-            __builtin_amdgcn_global_load_lds((global_u32x4*)(g + e),
-                                             (__attribute__((address_space(3))) void*)(lds + q * B + wbase),
-                                             16, 0, 0);
+    for (int k = 0; k < plane_steps<G>(); ++k) {
+        const uint32_t sl = k * 64 + (threadIdx.x & 63u);
+        off[k] = (sl / G::CH * uint32_t(pitch2) + sl % G::CH * (G::PADDED ? C : G::VEC)) * uint32_t(sizeof(CT)) +
+                 DMA_BIAS - k % 4 * 1024u;
+    }
+}
+
+// The block in LDS: its R0 axis-0 planes stand in a ring, plane i of the tile at
+// place (s + i) mod R0, so that the block slides to the next tile along axis 0 by
+// replacing only the planes that it does not share.  All members are uniform.
+template <typename G, int T>
+struct BlockRing {
+    uint32_t held = NO_CELL;   // packed first cell of the tile whose block the LDS holds
+    int s = 0;
+    __device__ __forceinline__ static int wrap(int v) { return v < G::R0 ? v : v - G::R0; }
+    // Moves on to the tile at `origin`; the first of its planes that has to be
+    // loaded (R0: none).
+    __device__ __forceinline__ int advance(uint32_t origin) {
+        if (origin == held) return G::R0;
+        const bool slide = held != NO_CELL && origin == held + (uint32_t(T) << 20);
+        s = slide ? wrap(s + T) : 0;
+        held = origin;
+        return slide ? G::R0 - T : 0;
+    }
+};
+
+// Copies 64 consecutive 16-byte slots, global -> LDS, by the DMA path of the load
+// unit: from base + off (per lane) + 1024 k to LDS address lds + 1024 k + 16 lane,
+// for k < K (at most four).  Written as instructions: for the compiler's builtin
+// every later LDS read, of other arrays too, would wait for the copies, and each
+// would set the LDS address anew.  They write no register; wait_loads() waits for
+// them.  (s_nop: an address that a vector instruction has just written takes five
+// wait states.)
+template <int K>
+__device__ __forceinline__ void copy_slots(const char* base, const uint32_t* off, uint32_t lds) {
+    static_assert(K >= 1 && K <= 4, "one to four steps");
+    if constexpr (K == 1)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :: "s"(lds), "v"(off[0]), "s"(base) : "memory", "m0");
+    else if constexpr (K == 2)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+                     "global_load_lds_dwordx4 %2, %3 offset:1024"
+                     :: "s"(lds), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "m0");
+    else if constexpr (K == 3)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %4\n\t"
+                     "global_load_lds_dwordx4 %2, %4 offset:1024\n\tglobal_load_lds_dwordx4 %3, %4 offset:2048"
+                     :: "s"(lds), "v"(off[0]), "v"(off[1]), "v"(off[2]), "s"(base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
+                     "global_load_lds_dwordx4 %2, %5 offset:1024\n\tglobal_load_lds_dwordx4 %3, %5 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %4, %5 offset:3072"
+                     :: "s"(lds), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "m0");
+}
+// The same for the step k = K alone (in the lanes that are active).
+template <int K>
+__device__ __forceinline__ void copy_slots_last(const char* base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+                 :: "s"(lds), "v"(off), "s"(base), "n"(K * 1024) : "memory", "m0");
+}
+// Every load of this wavefront has come in (stores have gone out).
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// p, known to be the same in every lane, in scalar registers.
+__device__ __forceinline__ const char* uniform(const char* p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
+    return reinterpret_cast<const char*>((uint64_t(hi) << 32) | lo);
+}
+
+// Requests the LDS copy of planes [i0, R0) of the block with cell origin (o0, o1,
+// o2) in the ghost-padded grid, the wavefronts taking planes in turn.  Planes
+// outside the padded grid (partial blocks only; never read by a particle) are
+// left out, rows outside it load the plane's origin instead; reads past a row's
+// end land in the next row, its pitch padding or the allocation's slack.
+template <int N, typename CT, int C, typename G, int T, int B>
+__device__ __forceinline__ void block_dma(const void* grid, int n0, int n1, int P1, int pitch2, int o0, int o1,
+                                          int o2, const BlockRing<G, T>& ring, int i0, const uint32_t* off,
+                                          u32x4* lds) {
+    constexpr int Q = plane_steps<G>();
+    static_assert(Q <= 8, "a plane is copied in at most two groups of four steps");
+    const int lane = threadIdx.x & 63;
+    const long plane_bytes = long(P1) * pitch2 * long(sizeof(CT));
+    const char* g = static_cast<const char*>(grid) - DMA_BIAS +
+                    ((long(o0) * P1 + o1) * pitch2 + long(o2) * C) * long(sizeof(CT));
+    const int last = min(n0 + N - 1 - o0, G::R0);
+    const int lim1 = n1 + N - 1 - o1;
+    const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) u32x4*)lds));
+    uint32_t e[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) e[k] = off[k];
+    if (lim1 < G::R1) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) e[k] = (k * 64 + lane) / G::CH < lim1 ? e[k] : DMA_BIAS - k % 4 * 1024u;
+    }
+    for (int i = i0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < last; i += B / 64) {
+        const char* gi = uniform(g + i * plane_bytes);
+        const uint32_t dst =
+            __builtin_amdgcn_readfirstlane(lds0 + uint32_t(BlockRing<G, T>::wrap(ring.s + i) * G::PLANE * 16));
+        constexpr int FULL = G::PLANE / 64;   // steps without masked lanes
+        if constexpr (FULL >= 4) copy_slots<4>(gi, e, dst);
+        if constexpr (FULL % 4 != 0) copy_slots<FULL % 4>(gi, e + FULL / 4 * 4, dst + FULL / 4 * 4096u);
+        if constexpr (Q > FULL)
+            if (FULL * 64 + lane < G::PLANE) copy_slots_last<FULL % 4>(gi, e[FULL], dst + FULL / 4 * 4096u);
     }
 }
 
@@ -1250,177 +1375,157 @@ constexpr bool bf16_rows_fit() {
     return true;
 }
 
-// LDS bytes one workgroup of B threads needs for the block geometry G: the
-// block itself (lanes past its last slot load nothing), so that as many blocks
-// as possible fit a CU (six of 27 KB for order 6 with 8^3 tiles).
-template <typename G, int B>
-constexpr int block_lds_bytes() {
-    return G::SLOTS * 16;
-}
-
-template <int N, typename CT, int C, int T, int B>
-constexpr int tile_lds_bytes() {
-    return block_lds_bytes<TileGeom<N, CT, C, T>, B>();
-}
-
-// The `count` particles from binned slot `start`, all with cells inside the
-// box of geometry G at cell origin (o0, o1, o2), evaluated by one workgroup
-// of B threads from an LDS copy of the box's block of the grid.  All 16-byte
-// loads of the block are issued at once (one memory round trip) straight into
-// `lds` (block_lds_bytes() of it); with `fill` false the LDS already holds the
-// block (the previous call was for the same box).  Lanes per particle: three
-// (order 6; four for order 4) when a round holds all the particles, each lane
-// summing its axis-0 planes and the lanes of planes 0 and N/2 gathering the
-// rest of their half by lane shuffles; else two (one half of the axis-0 sum
-// each) up to B/2 particles; else one.  Every mode adds the same terms in the
-// same order.  Every thread of the workgroup calls this with the same
-// arguments.
-template <int N, typename CT, int C, bool GRAD, typename G, int B>
-__device__ __forceinline__ void block_eval_cells(const GatherArgs& a, int o0, int o1, int o2, uint32_t count,
-                                                 uint32_t start, u32x4* lds, bool fill = true) {
-    using AT = typename Acc<CT>::type;
-    static_assert(sizeof(CT) != 2 || bf16_rows_fit<N, C, G::R2 - N + 1, G::LROW>(),
-                  "BF16 row reads would leave the LDS row");
-    const CT* tile = reinterpret_cast<const CT*>(lds);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    // a sparse box is split: SL lanes per particle (split_lanes), else two
-    // lanes per particle up to half a workgroup of particles, else one
-    constexpr int SL = split_lanes<N>();
-    constexpr int SPW = SL > 0 ? 64 / SL : 1;  // particles per wavefront when split
-    const bool split = SL > 0 && count <= uint32_t(SPW * (B / 64));
-    const bool pair = !split && count <= uint32_t(B / 2);
-    const int ppw = split ? SPW : (pair ? 32 : 64);  // particles per wavefront and round
-    const int stride = ppw * (B / 64);
-    const uint32_t jlane = split ? uint32_t((tid >> 6) * SPW + lane / (SL > 0 ? SL : 1))
-                                 : (pair ? uint32_t(tid >> 1) : uint32_t(tid));
-    const int part = split ? lane % (SL > 0 ? SL : 1) : (pair ? (tid & 1) : 0);
-    const int half = part;
-    const bool lane_ok = !split || lane < SPW * SL;  // the spare lane of a split wavefront
-    if (count == 0) return;  // uniform: no barrier is skipped by part of the workgroup
-    // per-lane particle state of one round: slot, position, stencil origin
-    // in the block and the weights
-    const int n[3] = {a.n0, a.n1, a.n2};
-    const double ih[3] = {a.ih0, a.ih1, a.ih2};
-    long p;
-    bool active;
-    RawParticle<AT> raw;
-    int cell[3];
-    AT w[3][N], wd[3][N];
-    auto fetch_round = [&](uint32_t j0) {
-        const uint32_t j = j0 + jlane;
-        active = j < count && lane_ok;
-        const uint32_t jj = start + (active ? j : 0u);
-        p = long(a.perm[jj]);
-        raw.load(a.binned, long(jj));
-    };
-    // finite by construction of the bucket
-    auto setup_round = [&]() {
-        AT t[3];
-        locate(raw, n, ih, cell, t);
-        particle_weights<N, AT>(a, t, w, wd);
-    };
-    // the first round's particles are requested before the block, so that one
-    // memory round trip serves both (4 % faster for order 6)
-    fetch_round(0);
-    {
-        if (fill)
-            block_dma<N, CT, C, G, B>(static_cast<const CT*>(a.grid), a.n0, a.n1, a.P1, long(a.pitch2), o0, o1, o2,
-                                      lds);
-        // the weights' arithmetic stays below every block load: the compiler
-        // waits for all loads in flight before the first use of a position,
-        // so arithmetic scheduled between the block loads would split them
-        // into two round trips
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0);  // every counter at zero: the block is in LDS
+// Lanes per particle for `count` particles on W wavefronts: as many as still
+// hold all of them in one round (order 6: 6, 3 or 2 lanes of 1, 2 or 3 axis-0
+// planes; order 4: 4 or 2; order 2: 2), else one.  A sparse tile's wavefronts
+// then finish sooner and read LDS banks that differ between the lanes of a
+// particle (planes are an odd number of 16-byte slots apart).
+template <int N, int W, bool SIX>
+__device__ __forceinline__ int particle_lanes(uint32_t count) {
+    if constexpr (N == 6) {
+        if (SIX && count <= uint32_t(W * 10)) return 6;
+        if (count <= uint32_t(W * 21)) return 3;
+    } else if constexpr (N == 4) {
+        if (count <= uint32_t(W * 16)) return 4;
     }
-    setup_round();
-    lds_barrier();
-    for (uint32_t j0 = 0;;) {
-        // a wavefront without any particle in this round skips it (uniform);
-        // inside a working wavefront, lanes past the end evaluate the box's
-        // first particle and store nothing
-        if (j0 + uint32_t(ppw * (tid / 64)) < count) {
-            const CT* base =
-                tile + ((cell[0] - o0) * G::R1 + (cell[1] - o1)) * G::LROW + (cell[2] - o2) * G::PS;
-            auto rows = [base](int ia, int ib) { return base + (ia * G::R1 + ib) * G::LROW; };
-            bool done = false;
-            if constexpr (SL > 0) {
-                if (split) {
-                    // lane `part` takes planes part*PPL .. part*PPL + PPL - 1; the
-                    // lanes holding planes 0 and N/2 gather the other planes of
-                    // their half and add them up in the order of contract_planes
-                    constexpr int PPL = N / SL;
-                    PlaneSum<AT, C> V[PPL];
-                    plane_sums<N, CT, AT, C, GRAD, PPL, G::PS>(
-                        w, wd, [&](int k, int ib) { return rows(part * PPL + k, ib); }, V);
-                    Partial<AT, C> lo, hi;
+    return count <= uint32_t(W * 32) ? 2 : 1;
+}
+
+// Particle of this lane among those of one round (j), and its part of the
+// particle's axis-0 planes.
+struct LaneRole {
+    uint32_t j;
+    int part;
+    bool ok;   // false: a spare lane (64 is no multiple of the lanes per particle)
+};
+__device__ __forceinline__ LaneRole lane_role(int lanes) {
+    const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    LaneRole r;
+    if (lanes == 1) {
+        r.j = threadIdx.x;
+        r.part = 0;
+        r.ok = true;
+    } else if (lanes == 2) {
+        r.j = threadIdx.x >> 1;
+        r.part = lane & 1;
+        r.ok = true;
+    } else if (lanes == 4) {
+        r.j = threadIdx.x >> 2;
+        r.part = lane & 3;
+        r.ok = true;
+    } else if (lanes == 3) {
+        r.j = wid * 21 + lane / 3;
+        r.part = int(lane % 3);
+        r.ok = lane < 63;
+    } else {
+        r.j = wid * 10 + lane / 6;
+        r.part = int(lane % 6);
+        r.ok = lane < 60;
+    }
+    return r;
+}
+
+// One particle on SL > 2 neighbouring lanes, N / SL axis-0 planes each: the
+// lanes holding planes 0 and N / 2 fetch the other planes of their half from
+// the lanes next to them and add them up in the order of contract_planes; the
+// sum of the upper half goes to part 0, which stores.
+template <int N, typename CT, typename AT, int C, bool GRAD, int SL, int PS, typename RowFn>
+__device__ __forceinline__ void split_eval(const GatherArgs& a, long p, bool store, int part, const AT (*w)[N],
+                                           const AT (*wd)[N], RowFn rows) {
+    constexpr int PPL = N / SL, H = N / 2;
+    const int lane = threadIdx.x & 63;
+    PlaneSum<AT, C> V[PPL];
+    plane_sums<N, CT, AT, C, GRAD, PPL, PS>(w, wd, [&](int k, int ib) { return rows(part * PPL + k, ib); }, V);
+    const bool upper = part * PPL >= H;
+    AT w0[H], wd0[H];
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        lo.u[c] = lo.g0[c] = lo.g1[c] = lo.g2[c] = AT(0);
-                        hi.u[c] = hi.g0[c] = hi.g1[c] = hi.g2[c] = AT(0);
-                    }
-                    if constexpr (N == 6) {
-                        // part 0: planes 0, 1 (+ 2 from part 1); part 2: (3 from part 1 +) 4, 5
-                        const PlaneSum<AT, C> X = shfl_planesum<AT, C, GRAD>(V[0], (lane + 1) & 63);
-                        const PlaneSum<AT, C> Y = shfl_planesum<AT, C, GRAD>(V[1], (lane + 63) & 63);
-                        chain_add<AT, C, GRAD>(lo, w[0][0], wd[0][0], V[0]);
-                        chain_add<AT, C, GRAD>(lo, w[0][1], wd[0][1], V[1]);
-                        chain_add<AT, C, GRAD>(lo, w[0][2], wd[0][2], X);
-                        chain_add<AT, C, GRAD>(hi, w[0][3], wd[0][3], Y);
-                        chain_add<AT, C, GRAD>(hi, w[0][4], wd[0][4], V[0]);
-                        chain_add<AT, C, GRAD>(hi, w[0][5], wd[0][5], V[1]);
-                    } else {
-                        // part 0: plane 0 (+ 1 from part 1); part 2: plane 2 (+ 3 from part 3)
-                        static_assert(N == 4, "split lanes for orders 4 and 6");
-                        const PlaneSum<AT, C> X = shfl_planesum<AT, C, GRAD>(V[0], (lane + 1) & 63);
-                        chain_add<AT, C, GRAD>(lo, w[0][0], wd[0][0], V[0]);
-                        chain_add<AT, C, GRAD>(lo, w[0][1], wd[0][1], X);
-                        chain_add<AT, C, GRAD>(hi, w[0][2], wd[0][2], V[0]);
-                        chain_add<AT, C, GRAD>(hi, w[0][3], wd[0][3], X);
-                    }
-                    const Partial<AT, C> H = shfl_partial<AT, C, GRAD>(hi, (lane + 2) & 63);
-                    if (active && part == 0) store_sum<AT, C, GRAD>(a, p, lo, H);
-                    done = true;
+    for (int k = 0; k < H; ++k) {
+        w0[k] = upper ? w[0][H + k] : w[0][k];
+        wd0[k] = upper ? wd[0][H + k] : wd[0][k];
+    }
+    Partial<AT, C> sum;
+#pragma unroll
+    for (int c = 0; c < C; ++c) sum.u[c] = sum.g0[c] = sum.g1[c] = sum.g2[c] = AT(0);
+    if constexpr (SL == 3) {
+        // planes 0 1 | 2 3 | 4 5: part 0 takes 2 from part 1, part 2 takes 3
+        const PlaneSum<AT, C> X = shfl_planesum<AT, C, GRAD>(V[0], (lane + 1) & 63);
+        const PlaneSum<AT, C> Y = shfl_planesum<AT, C, GRAD>(V[1], (lane + 63) & 63);
+        auto pick = [&](const PlaneSum<AT, C>& lo, const PlaneSum<AT, C>& hi) {
+            PlaneSum<AT, C> r;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                r.v[c] = upper ? hi.v[c] : lo.v[c];
+                if constexpr (GRAD) {
+                    r.v1[c] = upper ? hi.v1[c] : lo.v1[c];
+                    r.v2[c] = upper ? hi.v2[c] : lo.v2[c];
                 }
             }
-            if (done) {
-            } else if (pair) {
-                // both lanes of a pair run the same instructions: lane `half`
-                // takes planes half*N/2 .. half*N/2 + N/2 - 1
-                const int ia0 = half * (N / 2);
-                AT w0s[N / 2], wd0s[N / 2];
+            return r;
+        };
+        chain_add<AT, C, GRAD>(sum, w0[0], wd0[0], pick(V[0], Y));
+        chain_add<AT, C, GRAD>(sum, w0[1], wd0[1], pick(V[1], V[0]));
+        chain_add<AT, C, GRAD>(sum, w0[2], wd0[2], pick(X, V[1]));
+        const Partial<AT, C> up = shfl_partial<AT, C, GRAD>(sum, (lane + 2) & 63);
+        if (store) store_sum<AT, C, GRAD>(a, p, sum, up);
+    } else if constexpr (SL == 6) {
+        const PlaneSum<AT, C> X = shfl_planesum<AT, C, GRAD>(V[0], (lane + 1) & 63);
+        const PlaneSum<AT, C> Y = shfl_planesum<AT, C, GRAD>(V[0], (lane + 2) & 63);
+        chain_add<AT, C, GRAD>(sum, w0[0], wd0[0], V[0]);
+        chain_add<AT, C, GRAD>(sum, w0[1], wd0[1], X);
+        chain_add<AT, C, GRAD>(sum, w0[2], wd0[2], Y);
+        const Partial<AT, C> up = shfl_partial<AT, C, GRAD>(sum, (lane + 3) & 63);
+        if (store) store_sum<AT, C, GRAD>(a, p, sum, up);
+    } else {
+        static_assert(SL == 4 && N == 4, "lanes per particle: 3, 4 or 6");
+        PlaneSum<AT, C> X;
 #pragma unroll
-                for (int k = 0; k < N / 2; ++k) {
-                    w0s[k] = half ? w[0][N / 2 + k] : w[0][k];
-                    wd0s[k] = half ? wd[0][N / 2 + k] : wd[0][k];
-                }
-                Partial<AT, C> mine, other;
-                contract_planes<N, CT, AT, C, GRAD, N / 2, true, G::PS>(
-                    w0s, wd0s, w, wd, [&](int k, int ib) { return rows(ia0 + k, ib); }, mine);
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    other.u[c] = shfl_xor1(mine.u[c]);
-                    other.g0[c] = shfl_xor1(mine.g0[c]);
-                    other.g1[c] = shfl_xor1(mine.g1[c]);
-                    other.g2[c] = shfl_xor1(mine.g2[c]);
-                }
-                if (active && half == 0) store_sum<AT, C, GRAD>(a, p, mine, other);
-            } else {
-                Partial<AT, C> lo, hi;
-                contract_planes<N, CT, AT, C, GRAD, N / 2, true, G::PS>(w[0], wd[0], w, wd, rows, lo);
-                contract_planes<N, CT, AT, C, GRAD, N / 2, true, G::PS>(
-                    w[0] + N / 2, wd[0] + N / 2, w, wd, [&](int k, int ib) { return rows(N / 2 + k, ib); },
-                    hi);
-                if (active) store_sum<AT, C, GRAD>(a, p, lo, hi);
+        for (int c = 0; c < C; ++c) {
+            X.v[c] = quad_lane<QUAD_XOR1>(V[0].v[c]);
+            if constexpr (GRAD) {
+                X.v1[c] = quad_lane<QUAD_XOR1>(V[0].v1[c]);
+                X.v2[c] = quad_lane<QUAD_XOR1>(V[0].v2[c]);
             }
         }
-        j0 += uint32_t(stride);
-        if (j0 >= count) break;
-        fetch_round(j0);
-        setup_round();
+        chain_add<AT, C, GRAD>(sum, w0[0], wd0[0], V[0]);
+        chain_add<AT, C, GRAD>(sum, w0[1], wd0[1], X);
+        Partial<AT, C> up;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            up.u[c] = quad_lane<QUAD_XOR2>(sum.u[c]);
+            if constexpr (GRAD) {
+                up.g0[c] = quad_lane<QUAD_XOR2>(sum.g0[c]);
+                up.g1[c] = quad_lane<QUAD_XOR2>(sum.g1[c]);
+                up.g2[c] = quad_lane<QUAD_XOR2>(sum.g2[c]);
+            }
+        }
+        if (store) store_sum<AT, C, GRAD>(a, p, sum, up);
     }
-    lds_barrier();
+}
+
+// One particle on two lanes, a half of the axis-0 planes each.
+template <int N, typename CT, typename AT, int C, bool GRAD, int PS, typename RowFn>
+__device__ __forceinline__ void pair_eval(const GatherArgs& a, long p, bool store, int half, const AT (*w)[N],
+                                          const AT (*wd)[N], RowFn rows) {
+    const int ia0 = half * (N / 2);
+    AT w0s[N / 2], wd0s[N / 2];
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) {
+        w0s[k] = half ? w[0][N / 2 + k] : w[0][k];
+        wd0s[k] = half ? wd[0][N / 2 + k] : wd[0][k];
+    }
+    Partial<AT, C> mine, other;
+    contract_planes<N, CT, AT, C, GRAD, N / 2, true, PS>(
+        w0s, wd0s, w, wd, [&](int k, int ib) { return rows(ia0 + k, ib); }, mine);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        other.u[c] = quad_lane<QUAD_XOR1>(mine.u[c]);
+        if constexpr (GRAD) {
+            other.g0[c] = quad_lane<QUAD_XOR1>(mine.g0[c]);
+            other.g1[c] = quad_lane<QUAD_XOR1>(mine.g1[c]);
+            other.g2[c] = quad_lane<QUAD_XOR1>(mine.g2[c]);
+        }
+    }
+    if (store) store_sum<AT, C, GRAD>(a, p, mine, other);
 }
 
 // NaN outputs for the `count` particles without a cell (the last bucket),
@@ -1431,99 +1536,163 @@ __device__ __forceinline__ void nonfinite_eval(const GatherArgs& a, uint32_t cou
     if (threadIdx.x == 0) atomicAdd(a.nonfinite, (unsigned long long)count);
 }
 
-// The `count` binned particles from slot `start` of bucket `cur` (Morton tile
-// `cur` of T^3 cells, or the bucket of particles without a cell when `cur` ==
-// nbuckets_finite) evaluated by one workgroup of B threads
-// (block_eval_cells); `fill` false: the LDS holds tile `cur`'s block already.
-// Every thread of the workgroup must call this with the same arguments.
-template <int N, typename CT, int C, bool GRAD, int T, int B>
-__device__ __forceinline__ void bucket_eval(const GatherArgs& a, uint32_t cur, uint32_t count, uint32_t start,
-                                            u32x4* tile_v, bool fill = true) {
-    using AT = typename Acc<CT>::type;
-    if (cur == a.nbuckets_finite) {
-        nonfinite_eval<AT, C, GRAD, B>(a, count, start);
-    } else {
-        const int o0 = int(compact3(cur >> 2)) * T;
-        const int o1 = int(compact3(cur >> 1)) * T;
-        const int o2 = int(compact3(cur)) * T;
-        block_eval_cells<N, CT, C, GRAD, TileGeom<N, CT, C, T>, B>(a, o0, o1, o2, count, start, tile_v, fill);
-    }
-}
-
 // ------------------------------------------------------- taking items -------
 
-// A workgroup's place in the work items.  It takes units (equal parts of a
-// chunk's items) of its home range in order, through the range's counter, then
-// those of the other ranges, and is done when every range is exhausted.  Which
-// ranges still have units is read for all of them at once (eight ranges tried
-// one after another cost a workgroup without work eight round trips: 80 instead
-// of 46 us for the 64 tiles of a 32^3 field).  All members are the same in
-// every lane; every thread of the workgroup calls every function.
+// A workgroup's place in the work items.  It takes units of its home range in
+// order, through the range's counter, then those of the other ranges, and is done
+// when every range is exhausted.  Which ranges still have units is read for all
+// of them at once (eight ranges tried one after another cost a workgroup without
+// work eight round trips: 80 instead of 46 us for the 64 tiles of a 32^3 field).
+// Units dealt to the workgroups in turn instead of taken: 2232 instead of 1730
+// us for 5 * 10^6 particles at 512^3 (the workgroups do not keep step).
+//
+// The next unit is fetched while the items of the current one are evaluated, one
+// step (counter, descriptor, items) per item, each when the loads of the step
+// before have come in anyway; the items themselves stand in the lanes of a
+// register.  All other members are the same in every lane, and every thread of
+// the workgroup calls every function.
 template <int B>
-struct ItemQueue {
+struct ItemStream {
     ItemSource s;
-    uint32_t* sh;        // two LDS words (B > 64)
+    uint32_t* sh;        // three LDS words (B > 64)
     uint32_t gbeg, nch;  // chunks [gbeg, gbeg + nch)
-    uint32_t x, unit;    // current range and unit of it
-    uint32_t i, m;       // items [i, i + m) of the unit
+    uint32_t x;          // current range
+    uint32_t xbeg, xend; // its first chunk, and its units
+    u32x4 its;           // lane l: item base + l
+    uint32_t base, k, m; // items [base + k, base + m) are left of the unit
+    int stage;           // of the next unit: 1 counter, 2 descriptor, 3 items requested, 4 here, 5 none left
+    uint32_t v;          // stage 1: the counter's value (first lane)
+    u32x4 d, nits;       // stages 2 and 3
+    uint32_t nbase, nm;
 
-    // Next unit of the range, requested by the first lane (valid in that lane
-    // only).
-    __device__ __forceinline__ uint32_t issue() const {
-        return threadIdx.x == 0 ? atomicAdd(s.ctl + ITEM_CTL_STRIDE * x, 1u) : 0u;
-    }
-    // v of the first lane becomes the current unit; false when no range has one.
-    __device__ __forceinline__ bool settle(uint32_t v) {
-        if constexpr (B == 64) {
-            unit = __builtin_amdgcn_readfirstlane(v);
-        } else {
-            if (threadIdx.x == 0) sh[0] = v;
-            __syncthreads();
-            unit = __builtin_amdgcn_readfirstlane(sh[0]);
-            __syncthreads();
-        }
-        if (unit >= units(x)) {
-            if constexpr (B == 64) {
-                seek();
-            } else {
-                // the first wavefront looks for all (they must agree)
-                if (threadIdx.x < 64) {
-                    seek();
-                    sh[0] = x;
-                    sh[1] = unit;
-                }
-                __syncthreads();
-                x = __builtin_amdgcn_readfirstlane(sh[0]);
-                unit = __builtin_amdgcn_readfirstlane(sh[1]);
-                __syncthreads();
-            }
-            if (x == ITEM_RANGES) return false;
-        }
-        const u32x4 d = s.desc[gbeg + item_range_begin(x, nch) + unit / s.units];
-        const uint32_t n = __builtin_amdgcn_readfirstlane(d.z), first = __builtin_amdgcn_readfirstlane(d.w);
-        const uint32_t u = unit % s.units;
-        const uint32_t lo = n * u / s.units;
-        i = first + lo;
-        m = n * (u + 1) / s.units - lo;
-        return true;
-    }
-    __device__ __forceinline__ bool begin(const ItemSource& src, uint32_t* lds, uint32_t home) {
+    // The first item into it; false when there is none at all.
+    __device__ __forceinline__ bool begin(const ItemSource& src, uint32_t* lds, uint32_t home, u32x4& it) {
         s = src;
         sh = lds;
         x = home;
-        const uint32_t v = issue();
+        request();
         gbeg = s.g0 ? __builtin_amdgcn_readfirstlane(*s.g0) : 0u;
         nch = __builtin_amdgcn_readfirstlane(*s.g1) - gbeg;
-        return settle(v);
+        enter();
+        k = m = 0;
+        return next_wait(it);
+    }
+    // After a wait for all loads: the compiler needs no further one for these.
+    __device__ __forceinline__ void settle() { asm volatile("" : "+v"(v), "+v"(d), "+v"(nits)); }
+    // Before a barrier that follows a wait for all loads ...
+    __device__ __forceinline__ void publish() {
+        if constexpr (B > 64)
+            if (stage == 1 && threadIdx.x == 0) sh[0] = v;
+    }
+    // ... and after it.
+    __device__ __forceinline__ void step() {
+        if (stage == 1) {
+            uint32_t unit = __builtin_amdgcn_readfirstlane(B > 64 ? sh[0] : v);
+            if (unit >= xend && !seek(unit)) {
+                stage = 5;
+                return;
+            }
+            nm = unit & ((1u << s.ulog) - 1u);   // until the descriptor is here
+            d = load_global16(s.desc + xbeg + (unit >> s.ulog));
+            stage = 2;
+        } else if (stage == 2) {
+            const uint32_t n = __builtin_amdgcn_readfirstlane(d.z), first = __builtin_amdgcn_readfirstlane(d.w);
+            const uint32_t lo = (n * nm) >> s.ulog, hi = (n * (nm + 1)) >> s.ulog;
+            nbase = first + lo;
+            nm = hi - lo;
+            if (nm == 0) {
+                request();
+            } else {
+                nits = fetch(nbase, nm);
+                stage = 3;
+            }
+        } else if (stage == 3) {
+            stage = 4;
+        }
+    }
+    // The next item into it without waiting for any; false: not known yet (or
+    // there is none).
+    __device__ __forceinline__ bool next(u32x4& it) {
+        if (k + 1 < m && k + 1 < 64) {
+            ++k;
+        } else if (k + 1 >= m && stage == 4) {
+            start_unit();
+        } else {
+            return false;
+        }
+        it = item();
+        return true;
+    }
+    // The next item into it; false when all ranges are exhausted.
+    __device__ __forceinline__ bool next_wait(u32x4& it) {
+        if (k + 1 < m) {   // past the 64 items of the register
+            base += k + 1;
+            m -= k + 1;
+            k = 0;
+            its = fetch(base, m);
+        } else {
+            while (stage < 4) {
+                __builtin_amdgcn_s_waitcnt(0);
+                publish();
+                if constexpr (B > 64) __syncthreads();
+                step();
+                if constexpr (B > 64) __syncthreads();   // sh may be written again
+            }
+            if (stage == 5) return false;
+            start_unit();
+        }
+        it = item();
+        return true;
     }
 
    private:
-    __device__ __forceinline__ uint32_t units(uint32_t r) const {
-        return (item_range_begin(r + 1, nch) - item_range_begin(r, nch)) * s.units;
+    __device__ __forceinline__ u32x4 item() const {
+        return u32x4{uint32_t(__builtin_amdgcn_readlane(its.x, k)), uint32_t(__builtin_amdgcn_readlane(its.y, k)),
+                     uint32_t(__builtin_amdgcn_readlane(its.z, k)), uint32_t(__builtin_amdgcn_readlane(its.w, k))};
     }
-    // One wavefront: a unit of another range that still has some, or x =
-    // ITEM_RANGES.  Counters only grow, so the loop ends.
-    __device__ __forceinline__ void seek() {
+    __device__ __forceinline__ void request() {
+        v = threadIdx.x == 0 ? atomicAdd(s.ctl + ITEM_CTL_STRIDE * x, 1u) : 0u;
+        stage = 1;
+    }
+    __device__ __forceinline__ u32x4 fetch(uint32_t from, uint32_t n) const {
+        return load_global16(s.items + from + min(threadIdx.x & 63u, n - 1));
+    }
+    __device__ __forceinline__ void start_unit() {
+        its = nits;
+        base = nbase;
+        m = nm;
+        k = 0;
+        request();
+    }
+    __device__ __forceinline__ uint32_t units(uint32_t r) const {
+        return (item_range_begin(r + 1, nch) - item_range_begin(r, nch)) << s.ulog;
+    }
+    // A unit of another range that still has some; false when none has.
+    __device__ __forceinline__ bool seek(uint32_t& unit) {
+        if constexpr (B > 64) {
+            // the first wavefront looks for all (they must agree)
+            if (threadIdx.x < 64) {
+                seek_wave(unit);
+                sh[1] = x;
+                sh[2] = unit;
+            }
+            __syncthreads();
+            x = __builtin_amdgcn_readfirstlane(sh[1]);
+            unit = __builtin_amdgcn_readfirstlane(sh[2]);
+            __syncthreads();
+        } else {
+            seek_wave(unit);
+        }
+        if (x == ITEM_RANGES) return false;
+        enter();
+        return true;
+    }
+    __device__ __forceinline__ void enter() {
+        xbeg = gbeg + item_range_begin(x, nch);
+        xend = units(x);
+    }
+    // One wavefront; counters only grow, so the loop ends.
+    __device__ __forceinline__ void seek_wave(uint32_t& unit) {
         for (;;) {
             const uint32_t l = threadIdx.x % ITEM_RANGES;
             const uint32_t at =
@@ -1534,9 +1703,9 @@ struct ItemQueue {
                 return;
             }
             const uint32_t turn = (x + 1) % ITEM_RANGES;
-            const uint32_t rot = (some | (some << ITEM_RANGES)) >> turn;
-            x = (turn + uint32_t(__builtin_ctz(rot))) % ITEM_RANGES;
-            unit = __builtin_amdgcn_readfirstlane(issue());
+            x = (turn + uint32_t(__builtin_ctz((some | (some << ITEM_RANGES)) >> turn))) % ITEM_RANGES;
+            request();
+            unit = __builtin_amdgcn_readfirstlane(v);
             if (unit < units(x)) return;
         }
     }
@@ -1552,6 +1721,310 @@ __device__ __forceinline__ void item_take_end(uint32_t* ctl) {
         for (int x = 0; x < ITEM_RANGES; ++x) atomicExch(ctl + ITEM_CTL_STRIDE * x, 0u);
         atomicExch(done, 0u);
     }
+}
+
+// Weight pairs (w, w') of a particle on several lanes, through LDS: every lane
+// forms those of its own stencil indices along the three axes and reads the
+// others', where forming all of them in every lane took half of a sparse tile's
+// vector instructions.  The Horner steps and the coefficients are those of
+// bspline_weights, so the weights are the same to the last bit.
+template <int N, typename AT, int W>
+struct SharedWeights {
+    // row j: M[j][N-1 .. 0], then M1[j][N-2 .. 0] (w' without its chain factor)
+    static constexpr int ROW = (2 * N - 1 + 3) / 4 * 4;
+    AT coef[N][ROW];
+    // pairs of axes 1 and 2 of the particles of a round; SPW of them per wavefront
+    static constexpr int SPW = N == 6 ? 22 : 16;   // (order 6: the spare lane has its own)
+    AT pair[W][SPW][2][N][2];
+};
+
+// What a tiled kernel does with one particle: value and gradient.
+template <int N_, typename CT_, int C_, bool GRAD, int T_, int W_>
+struct ValueGather {
+    static constexpr int N = N_, C = C_, T = T_;
+    using CT = CT_;
+    using AT = typename Acc<CT>::type;
+    using G = TileGeom<N, CT, C, T>;
+    using Args = GatherArgs;
+    static constexpr bool SHARE = sizeof(AT) == 4 && N >= 4;
+    struct Empty {};
+    using Shared = typename std::conditional<SHARE, SharedWeights<N, AT, W_>, Empty>::type;
+    struct Weights {
+        AT w[3][N], wd[3][N];
+    };
+    template <int W>
+    __device__ __forceinline__ static int lanes(uint32_t count) {
+        return particle_lanes<N, W, SHARE>(count);
+    }
+    __device__ __forceinline__ static void init(const Args& a, Shared* sh) {
+        if constexpr (SHARE) {
+            constexpr BSpline<N> S{};
+            constexpr LagrangeM<N> L{};
+            if (threadIdx.x == 0) {
+                const bool lag = a.basis == BSI_BASIS_LAGRANGE;
+#pragma unroll
+                for (int j = 0; j < N; ++j) {
+#pragma unroll
+                    for (int i = 0; i < N; ++i) sh->coef[j][N - 1 - i] = lag ? AT(L.M[j][i]) : AT(S.M[j][i]);
+#pragma unroll
+                    for (int i = 0; i < N - 1; ++i) sh->coef[j][2 * N - 2 - i] = lag ? AT(L.M1[j][i]) : AT(S.M1[j][i]);
+                }
+            }
+            __syncthreads();
+        }
+    }
+    __device__ __forceinline__ static void setup(const Args& a, const RawParticle<AT>& raw, int lanes,
+                                                 const LaneRole& role, int* cell, Weights& k, Shared* sh) {
+        const int n[3] = {a.n0, a.n1, a.n2};
+        const double ih[3] = {a.ih0, a.ih1, a.ih2};
+        AT t[3];
+        locate(raw, n, ih, cell, t);   // finite by construction of the bucket
+        if constexpr (SHARE) {
+            if (lanes > 2) {
+                if (N == 4 || lanes == 6) share<1>(t, ih, role, k, sh);
+                else share<N == 6 ? 2 : 1>(t, ih, role, k, sh);
+                return;
+            }
+        }
+        particle_weights<N, AT>(a, t, k.w, k.wd);
+    }
+    template <typename RowFn>
+    __device__ __forceinline__ static void eval(const Args& a, long p, bool active, int lanes, int part,
+                                                const Weights& k, RowFn rows) {
+        if constexpr (N == 6) {
+            if (SHARE && lanes == 6)
+                return split_eval<N, CT, AT, C, GRAD, 6, G::PS>(a, p, active && part == 0, part, k.w, k.wd, rows);
+            if (lanes == 3)
+                return split_eval<N, CT, AT, C, GRAD, 3, G::PS>(a, p, active && part == 0, part, k.w, k.wd, rows);
+        } else if constexpr (N == 4) {
+            if (lanes == 4)
+                return split_eval<N, CT, AT, C, GRAD, 4, G::PS>(a, p, active && part == 0, part, k.w, k.wd, rows);
+        }
+        if (lanes == 2)
+            return pair_eval<N, CT, AT, C, GRAD, G::PS>(a, p, active && part == 0, part, k.w, k.wd, rows);
+        Partial<AT, C> lo, hi;
+        contract_planes<N, CT, AT, C, GRAD, N / 2, true, G::PS>(k.w[0], k.wd[0], k.w, k.wd, rows, lo);
+        contract_planes<N, CT, AT, C, GRAD, N / 2, true, G::PS>(
+            k.w[0] + N / 2, k.wd[0] + N / 2, k.w, k.wd, [&](int i, int ib) { return rows(N / 2 + i, ib); }, hi);
+        if (active) store_sum<AT, C, GRAD>(a, p, lo, hi);
+    }
+    template <int B>
+    __device__ __forceinline__ static void nonfinite(const Args& a, uint32_t count, uint32_t start) {
+        nonfinite_eval<AT, C, GRAD, B>(a, count, start);
+    }
+
+   private:
+    // Weights of a particle on N / PPL lanes.  Axes 1 and 2: all of them, through
+    // LDS.  Axis 0: each of k.w[0][i], i < N / 2, is plane i of the lane's half
+    // (the lanes that add a half up read the next lanes' values).
+    template <int PPL>
+    __device__ __forceinline__ static void share(const AT* t, const double* ih, const LaneRole& role, Weights& k,
+                                                 Shared* sh) {
+        constexpr int SL = N / PPL, H = N / 2;
+        const int lane = threadIdx.x & 63;
+        auto& slot = sh->pair[threadIdx.x >> 6][lane / SL];
+        AT w0[PPL], wd0[PPL];
+#pragma unroll
+        for (int i = 0; i < PPL; ++i) {
+            const int j = role.part * PPL + i;
+            AT c[Shared::ROW];
+#pragma unroll
+            for (int q = 0; q < Shared::ROW; q += 4)
+                *reinterpret_cast<f32x4*>(c + q) = *reinterpret_cast<const f32x4*>(&sh->coef[j][q]);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                AT w = c[0], wd = c[N];
+#pragma unroll
+                for (int q = 1; q < N; ++q) w = fused(w, t[d], c[q]);
+#pragma unroll
+                for (int q = 1; q < N - 1; ++q) wd = fused(wd, t[d], c[N + q]);
+                wd *= AT(ih[d]);
+                if (d == 0) {
+                    w0[i] = w;
+                    wd0[i] = wd;
+                } else {
+                    slot[d - 1][j][0] = w;
+                    slot[d - 1][j][1] = wd;
+                }
+            }
+        }
+#pragma unroll
+        for (int d = 1; d < 3; ++d)
+#pragma unroll
+            for (int j = 0; j < N; j += 2) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(&slot[d - 1][j][0]);
+                k.w[d][j] = v[0];
+                k.wd[d][j] = v[1];
+                k.w[d][j + 1] = v[2];
+                k.wd[d][j + 1] = v[3];
+            }
+        // axis 0: planes of the half, in order
+        if constexpr (SL == 4) {
+            k.w[0][0] = w0[0];
+            k.wd[0][0] = wd0[0];
+            k.w[0][1] = quad_lane<QUAD_XOR1>(w0[0]);
+            k.wd[0][1] = quad_lane<QUAD_XOR1>(wd0[0]);
+        } else if constexpr (SL == 6) {
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                k.w[0][i] = i == 0 ? w0[0] : __shfl(w0[0], (lane + i) & 63, 64);
+                k.wd[0][i] = i == 0 ? wd0[0] : __shfl(wd0[0], (lane + i) & 63, 64);
+            }
+        } else {
+            // parts 0 | 1 | 2 hold planes 0 1 | 2 3 | 4 5
+            const bool upper = role.part == 2;
+            const AT nw = __shfl(w0[0], (lane + 1) & 63, 64), nd = __shfl(wd0[0], (lane + 1) & 63, 64);
+            const AT pw = __shfl(w0[PPL - 1], (lane + 63) & 63, 64), pd = __shfl(wd0[PPL - 1], (lane + 63) & 63, 64);
+            k.w[0][0] = upper ? pw : w0[0];
+            k.wd[0][0] = upper ? pd : wd0[0];
+            k.w[0][1] = upper ? w0[0] : w0[PPL - 1];
+            k.wd[0][1] = upper ? wd0[0] : wd0[PPL - 1];
+            k.w[0][H - 1] = upper ? w0[PPL - 1] : nw;
+            k.wd[0][H - 1] = upper ? wd0[PPL - 1] : nd;
+        }
+#pragma unroll
+        for (int i = H; i < N; ++i) {
+            k.w[0][i] = k.w[0][i - H];
+            k.wd[0][i] = k.wd[0][i - H];
+        }
+    }
+};
+
+// LDS of a persistent workgroup.
+template <typename K>
+constexpr int tile_lds_bytes() {
+    return K::G::SLOTS * 16;
+}
+
+// A persistent workgroup of B threads (W wavefronts) of a tiled kernel K: for each
+// work item the block of its tile is filled into LDS, then its particles are
+// contracted from there.  args_of(tag, a) sets a to the arguments of the items'
+// field.  Every thread of the workgroup calls this.
+//
+// What bounds it is latency, not a rate: at 512^3, order 6, FP32, 5 * 10^6
+// particles (1.36 ms, five workgroups' worth of LDS a CU) the contraction alone
+// takes 0.87 ms, without the block copies it is 0.99 ms, without the stores 1.25 ms,
+// and the vector units are 38 % busy, LDS 35 %.  So a row of four tiles along
+// axis 0 is one workgroup's (tile_key), whose block slides and copies 8 of 13
+// planes only; a particle's planes are dealt to several lanes and its weights
+// formed once (SharedWeights); and items and particle records are requested one
+// item ahead.  Against blocks copied whole and lanes that each form all weights:
+// 512^3, FP32 order 6, 10^7 clustered particles 2125 -> 1981 us; 256^3, 10^6: order
+// 6 231 -> 217, order 4 unchanged at 164.  Half-height blocks with the next planes
+// copied during the contraction took 2106 instead of 1405 us, results stored one
+// item late 1412 instead of 1364.
+template <typename K, int B, typename ArgsOf>
+__device__ __forceinline__ void tiled_gather(ArgsOf args_of, const ItemSource& src, uint32_t home, u32x4* lds,
+                                             typename K::Shared* shared, uint32_t* sh) {
+    using CT = typename K::CT;
+    using AT = typename K::AT;
+    using G = typename K::G;
+    constexpr int N = K::N, C = K::C, T = K::T, W = B / 64;
+    static_assert(sizeof(CT) != 2 || bf16_rows_fit<N, C, T, G::LROW>(), "BF16 row reads would leave the LDS row");
+    const CT* tile = reinterpret_cast<const CT*>(lds);
+    ItemStream<B> stream;
+    u32x4 it;
+    if (!stream.begin(src, sh, home, it)) {
+        item_take_end(src.ctl);
+        return;
+    }
+    // particles of one round of an item
+    struct Round {
+        RawParticle<AT> raw;
+        uint32_t p;
+        bool active;
+    };
+    typename K::Args a;
+    uint32_t tag = it.w;
+    args_of(tag, a);
+    K::init(a, shared);
+    uint32_t off[plane_steps<G>()];
+    plane_offsets<CT, C, G>(a.pitch2, off);
+    auto fetch = [&](const u32x4& item, int lanes, uint32_t j0, Round& r) {
+        const LaneRole role = lane_role(lanes);
+        const uint32_t j = j0 + role.j;
+        r.active = j < item.z && role.ok;
+        const uint32_t jj = item.y + (r.active ? j : 0u);
+        r.p = a.perm[jj];
+        r.raw.load(a.binned, long(jj));
+    };
+    BlockRing<G, T> ring;
+    int lanes = K::template lanes<W>(it.z);
+    Round r;
+    fetch(it, lanes, 0, r);
+    for (;;) {
+        const int o0 = int(it.x >> 20), o1 = int((it.x >> 10) & 1023u), o2 = int(it.x & 1023u);
+        if (it.x != NO_CELL) {
+            const int i0 = ring.advance(it.x);
+            if (i0 < G::R0)
+                block_dma<N, CT, C, G, T, B>(a.grid, a.n0, a.n1, a.P1, a.pitch2, o0, o1, o2, ring, i0, off, lds);
+        }
+        // everything that has been requested (the last results have gone out
+        // meanwhile)
+        wait_loads();
+        r.raw.settle(r.p);
+        stream.settle();
+        stream.publish();
+        lds_barrier();
+        stream.step();
+        // the next item's first particles, on their way during the contraction
+        // (not across fields: their arguments are not here yet)
+        u32x4 nit;
+        bool known = stream.next(nit);
+        int nlanes = 1;
+        Round nr;
+        const bool ahead = known && nit.w == tag;
+        if (ahead) {
+            nlanes = K::template lanes<W>(nit.z);
+            fetch(nit, nlanes, 0, nr);
+        }
+        if (it.x == NO_CELL) {
+            K::template nonfinite<B>(a, it.z, it.y);
+        } else {
+            const LaneRole role = lane_role(lanes);
+            const uint32_t first = __builtin_amdgcn_readfirstlane(role.j);
+            for (uint32_t j0 = 0;;) {
+                Round r2;
+                const bool again = lanes == 1 && j0 + uint32_t(B) < it.z;
+                if (again) fetch(it, 1, j0 + uint32_t(B), r2);
+                // a wavefront without any particle skips the round (uniform);
+                // inside a working one, lanes past the end evaluate the
+                // item's first particle and store nothing
+                if (j0 + first < it.z) {
+                    int cell[3];
+                    typename K::Weights wts;
+                    K::setup(a, r.raw, lanes, role, cell, wts, shared);
+                    // row (ia, ib) of the particle's stencil
+                    const CT* base = tile + (cell[1] - o1) * G::LROW + (cell[2] - o2) * G::PS;
+                    const int c0 = ring.s + cell[0] - o0;
+                    auto rows = [base, c0](int ia, int ib) {
+                        return base + BlockRing<G, T>::wrap(c0 + ia) * (G::PLANE * G::VEC) + ib * G::LROW;
+                    };
+                    K::eval(a, long(r.p), r.active, lanes, role.part, wts, rows);
+                }
+                if (!again) break;
+                j0 += uint32_t(B);
+                r = r2;
+            }
+        }
+        lds_barrier();   // every LDS read done before planes are replaced
+        if (!known) known = stream.next_wait(nit);
+        if (!known) break;
+        if (!ahead) {
+            if (nit.w != tag) {
+                tag = nit.w;
+                args_of(tag, a);
+                plane_offsets<CT, C, G>(a.pitch2, off);
+                ring.held = NO_CELL;
+            }
+            nlanes = K::template lanes<W>(nit.z);
+            fetch(nit, nlanes, 0, nr);
+        }
+        it = nit;
+        lanes = nlanes;
+        r = nr;
+    }
+    item_take_end(src.ctl);
 }
 
 }  // namespace bsi

@@ -45,7 +45,7 @@ __device__ __forceinline__ void bspline_weights2(AT t, AT* wdd) {
     for (int j = 0; j < N; ++j) {
         AT acc = AT(B.M2[j][N - 3]);
 #pragma unroll
-        for (int i = N - 4; i >= 0; --i) acc = acc * t + AT(B.M2[j][i]);
+        for (int i = N - 4; i >= 0; --i) acc = fused(acc, t, AT(B.M2[j][i]));
         wdd[j] = acc;
     }
 }
@@ -54,10 +54,10 @@ struct HessArgs {
     const void* grid;
     const void* binned;        // the particles in binned order (RawParticle)
     const uint32_t* perm;      // particle of every binned slot
-    uint32_t nbf;              // finite tiles; tile nbf holds the particles without a cell
+    uint32_t nbuckets_finite;  // finite tiles; the next one holds the particles without a cell
     long P;
     int n0, n1, n2, P1;
-    long pitch2;
+    int pitch2;
     double ih0, ih1, ih2;
     void* u;
     void* grad;  // or nullptr
@@ -321,110 +321,74 @@ __device__ __forceinline__ void hess_nan(const HessArgs& a, long p) {
     }
 }
 
-constexpr int HESS_TB = 64;           // threads per workgroup of the tiled kernel
-constexpr uint32_t HESS_ROUNDS = 4;   // rounds of one wavefront per work item
-
-// The `count` binned particles from slot `start` of Morton tile `cur` (8^3
-// cells), or of the bucket without a cell when `cur` == nbf, by one
-// wavefront.  With `fill` the tile's (8+N-1)^3 block of the grid is first
-// copied into LDS by the load unit's DMA path (else the LDS holds it from the
-// previous call); then every particle reads its stencil from LDS, two lanes
-// per particle (one half of the axis-0 sum each, combined with a lane
-// shuffle) when the piece holds at most 32 particles.
-template <int N, typename CT, int C, typename G>
-__device__ __forceinline__ void hess_piece(const HessArgs& a, uint32_t cur, uint32_t start, uint32_t count,
-                                           u32x4* lds, bool fill) {
+// What the tiled kernel does with one particle: u, grad u and the second
+// derivatives, on two lanes (one half of the axis-0 sum each, combined by a lane
+// exchange) or one.
+template <int N_, typename CT_, int C_>
+struct HessGather {
+    static constexpr int N = N_, C = C_, T = 8;
+    using CT = CT_;
     using AT = typename Acc<CT>::type;
-    const CT* tile = reinterpret_cast<const CT*>(lds);
-    const int tid = threadIdx.x;
-    if (cur == a.nbf) {
-        for (uint32_t j = tid; j < count; j += HESS_TB) hess_nan<AT, C>(a, long(a.perm[start + j]));
-        if (tid == 0) atomicAdd(a.nonfinite, (unsigned long long)count);
-        return;
-    }
-    const bool pair = count <= uint32_t(HESS_TB / 2);
-    const int stride = pair ? HESS_TB / 2 : HESS_TB;
-    const int o0 = int(compact3(cur >> 2)) * 8;
-    const int o1 = int(compact3(cur >> 1)) * 8;
-    const int o2 = int(compact3(cur)) * 8;
-    if (fill) {
-        // the block's 16-byte slots, global -> LDS, all requested at once
-        block_dma<N, CT, C, G, HESS_TB>(static_cast<const CT*>(a.grid), a.n0, a.n1, a.P1, a.pitch2, o0, o1, o2, lds);
-        __builtin_amdgcn_s_waitcnt(0);
-        lds_barrier();
-    }
-    const uint32_t jlane = pair ? uint32_t(tid >> 1) : uint32_t(tid);
-    const int half = pair ? (tid & 1) : 0;
-    for (uint32_t j0 = 0; j0 < count; j0 += uint32_t(stride)) {
-        const uint32_t jj = j0 + jlane;
-        const bool active = jj < count;
-        const uint32_t slot = start + (active ? jj : 0u);
-        const long p = long(a.perm[slot]);
-        RawParticle<AT> raw;
-        raw.load(a.binned, long(slot));
-        int cell[3];
+    using G = TileGeom<N, CT, C, T, false>;   // rows packed densely (hess_planes reads them)
+    using Args = HessArgs;
+    struct Weights {
         AT w[3][N], wd[3][N], wdd[3][N];
-        hess_setup<N, AT>(a, raw, cell, w, wd, wdd);  // finite by construction of the tile
-        const CT* base = tile + ((cell[0] - o0) * G::R1 + (cell[1] - o1)) * G::LROW + (cell[2] - o2) * C;
-        auto rows = [base](int ia, int ib) { return base + (ia * G::R1 + ib) * G::LROW; };
-        if (pair) {
-            const int ia0 = half * (N / 2);
+    };
+    template <int W>
+    __device__ __forceinline__ static int lanes(uint32_t count) {
+        return count <= uint32_t(W * 32) ? 2 : 1;
+    }
+    struct Shared {};
+    __device__ __forceinline__ static void init(const Args&, Shared*) {}
+    __device__ __forceinline__ static void setup(const Args& a, const RawParticle<AT>& raw, int, const LaneRole&,
+                                                 int* cell, Weights& k, Shared*) {
+        hess_setup<N, AT>(a, raw, cell, k.w, k.wd, k.wdd);   // finite by construction of the tile
+    }
+    template <typename RowFn>
+    __device__ __forceinline__ static void eval(const Args& a, long p, bool active, int lanes, int part,
+                                                const Weights& k, RowFn rows) {
+        if (lanes == 2) {
+            const int ia0 = part * (N / 2);
             AT w0s[N / 2], wd0s[N / 2], wdd0s[N / 2];
 #pragma unroll
-            for (int k = 0; k < N / 2; ++k) {
-                w0s[k] = half ? w[0][N / 2 + k] : w[0][k];
-                wd0s[k] = half ? wd[0][N / 2 + k] : wd[0][k];
-                wdd0s[k] = half ? wdd[0][N / 2 + k] : wdd[0][k];
+            for (int i = 0; i < N / 2; ++i) {
+                w0s[i] = part ? k.w[0][N / 2 + i] : k.w[0][i];
+                wd0s[i] = part ? k.wd[0][N / 2 + i] : k.wd[0][i];
+                wdd0s[i] = part ? k.wdd[0][N / 2 + i] : k.wdd[0][i];
             }
             HessSums<AT, C> mine, other;
-            hess_planes<N, CT, AT, C, N / 2>(w0s, wd0s, wdd0s, w, wd, wdd,
-                                             [&](int k, int ib) { return rows(ia0 + k, ib); }, mine);
+            hess_planes<N, CT, AT, C, N / 2>(w0s, wd0s, wdd0s, k.w, k.wd, k.wdd,
+                                             [&](int i, int ib) { return rows(ia0 + i, ib); }, mine);
 #pragma unroll
             for (int m = 0; m < 10; ++m)
 #pragma unroll
-                for (int c = 0; c < C; ++c) other.s[m][c] = __shfl_xor(mine.s[m][c], 1, 64);
-            if (active && half == 0) hess_store<AT, C>(a, p, mine, other);
+                for (int c = 0; c < C; ++c) other.s[m][c] = quad_lane<QUAD_XOR1>(mine.s[m][c]);
+            if (active && part == 0) hess_store<AT, C>(a, p, mine, other);
         } else {
             HessSums<AT, C> lo, hi;
-            hess_planes<N, CT, AT, C, N / 2>(w[0], wd[0], wdd[0], w, wd, wdd, rows, lo);
-            hess_planes<N, CT, AT, C, N / 2>(w[0] + N / 2, wd[0] + N / 2, wdd[0] + N / 2, w, wd, wdd,
-                                             [&](int k, int ib) { return rows(N / 2 + k, ib); }, hi);
+            hess_planes<N, CT, AT, C, N / 2>(k.w[0], k.wd[0], k.wdd[0], k.w, k.wd, k.wdd, rows, lo);
+            hess_planes<N, CT, AT, C, N / 2>(k.w[0] + N / 2, k.wd[0] + N / 2, k.wdd[0] + N / 2, k.w, k.wd, k.wdd,
+                                             [&](int i, int ib) { return rows(N / 2 + i, ib); }, hi);
             if (active) hess_store<AT, C>(a, p, lo, hi);
         }
     }
-}
+    template <int B>
+    __device__ __forceinline__ static void nonfinite(const Args& a, uint32_t count, uint32_t start) {
+        for (uint32_t j = threadIdx.x; j < count; j += B) hess_nan<AT, C>(a, long(a.perm[start + j]));
+        if (threadIdx.x == 0) atomicAdd(a.nonfinite, (unsigned long long)count);
+    }
+};
 
-// LDS-tiled variant: persistent one-wave workgroups over the work items (the
-// non-empty Morton tiles of 8^3 cells cut into pieces of at most HESS_ROUNDS
-// rounds, so that a crowded tile, a dense cluster of particles, is shared by
-// several CUs).  As in the tiled gather, the items are split into one range per
-// XCD; a workgroup takes the items of its home range (blockIdx % ITEM_RANGES:
-// workgroups are dealt to the XCDs in turn) a unit at a time, then those of
-// the other ranges, and consecutive items of one tile reuse its block in LDS.
+constexpr int HESS_TB = 64;           // threads per workgroup of the tiled kernel
+constexpr uint32_t HESS_ROUNDS = 4;   // rounds of one wavefront per work item
+
+// LDS-tiled variant: the evaluation's tiled gather with these sums.
 template <int N, typename CT, int C>
 __global__ __launch_bounds__(HESS_TB) void k_gather_hess_tiled(HessArgs a) {
-    using G = TileGeom<N, CT, C, 8, false>;   // rows packed densely (hess_planes reads them)
-    static_assert(sizeof(CT) != 2 || bf16_rows_fit<N, C, 8, G::LROW>(), "BF16 row reads would leave the LDS row");
-    __shared__ u32x4 lds[G::SLOTS];
-    // wave-uniform values steer every loop that holds a barrier
-    ItemQueue<HESS_TB> q;
-    uint32_t prev = 0xffffffffu;  // tile whose block the LDS holds
-    bool more = q.begin(a.src, nullptr, uint32_t(blockIdx.x) % ITEM_RANGES);
-    while (more) {
-        uint32_t next = q.m == 0 ? q.issue() : 0u;
-        for (uint32_t k = 0; k < q.m; ++k) {
-            const u32x4 it = a.src.items[q.i + k];
-            const uint32_t cur = __builtin_amdgcn_readfirstlane(it.x);
-            const uint32_t start = __builtin_amdgcn_readfirstlane(it.y);
-            const uint32_t count = __builtin_amdgcn_readfirstlane(it.z);
-            if (k + 1 == q.m) next = q.issue();
-            hess_piece<N, CT, C, G>(a, cur, start, count, lds, cur != prev);
-            if (cur != a.nbf) prev = cur;
-            lds_barrier();  // every LDS read done before a later piece refills it
-        }
-        more = q.settle(next);
-    }
-    item_take_end(a.src.ctl);
+    using K = HessGather<N, CT, C>;
+    __shared__ u32x4 lds[tile_lds_bytes<K>() / 16];
+    tiled_gather<K, HESS_TB>([&](uint32_t, HessArgs& x) { x = a; }, a.src, uint32_t(blockIdx.x) % ITEM_RANGES, lds,
+                             nullptr, nullptr);
 }
 
 template <typename CT>
@@ -497,7 +461,7 @@ bsi_status hessian_run(bsi_field* f, const double* pos, int64_t P, void* u, void
     a.grid = f->grid;
     a.binned = b.binned;
     a.perm = b.perm;
-    a.nbf = uint32_t(bin_bucket_count(f, tile));
+    a.nbuckets_finite = uint32_t(bin_key_count(f, tile));
     a.P = long(P);
     a.n0 = f->n[0];
     a.n1 = f->n[1];
