@@ -102,7 +102,7 @@ typedef struct bsi_eval_config {
     int32_t variant;     /* 0 = LDS-tiled gather when sort_tile > 0 and the tile fits (sizes 4, 6,
                             8, 12, 16 whose block is at most 64 KB of LDS and whose origin is
                             16-byte aligned); otherwise, and for 1, one thread per particle
-                            reading the grid directly */
+                            (or one per axis-0 plane) reading the grid directly */
     int32_t tiles_per_group; /* read by no kernel now (the tiled gather takes work items, the
                                 batch's tile kernels one tile at a time); kept so that tuning
                                 records and callers' structs keep their layout; any value */
@@ -184,7 +184,8 @@ bsi_status bsi_field_get_coefficients(const bsi_field* field, double* grid_dev,
 bsi_status bsi_eval(bsi_field* field, const double* pos_dev, int64_t P,
                     void* u_dev, void* grad_dev, void* hip_stream);
 /* Same with explicit tuning knobs (NULL = the context's tuned configuration
- * for this field and particle count, see bsi_ctx_lookup_config). */
+ * for this field and particle count, see bsi_ctx_lookup_config; without one,
+ * the default, less binning or tiles where few particles do not repay them). */
 bsi_status bsi_eval_ex(bsi_field* field, const double* pos_dev, int64_t P,
                        void* u_dev, void* grad_dev, const bsi_eval_config* cfg,
                        void* hip_stream);
@@ -345,9 +346,9 @@ typedef struct bsi_server_report {
  * HIP streams (default priority) and one scheduler thread that owns all of
  * the server's GPU work.  Requests are admitted in arrival order as soon as a
  * slot is free and the arena holds the request's buffers; each admitted
- * request copies its positions in, runs the binned gather of its field (the
- * configuration bsi_ctx_lookup_config gives for its size) and copies u (and
- * grad) out on its slot's stream, so requests overlap on the device and a
+ * request copies its positions in, is evaluated (as by bsi_eval; its footprint is
+ * that of the configuration bsi_ctx_lookup_config gives for its size) and copies
+ * u (and grad) out on its slot's stream, so requests overlap on the device and a
  * request's result is bitwise the result of bsi_eval_ex on the same field
  * with that configuration, whatever else runs.  While a server runs, use its
  * context from other threads only after bsi_server_drain.  BSI_E_NOMEM if the

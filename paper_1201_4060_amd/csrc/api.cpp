@@ -412,7 +412,7 @@ bsi_status bsi_eval_ex(bsi_field* f, const double* pos, int64_t P, void* u, void
     f->last_stream = s;
     bsi_eval_config c{};
     if (cfg) c = *cfg;
-    else BSI_TRY(lookup_config(f->ctx, f, P, &c));
+    else BSI_TRY(one_shot_config(f->ctx, f, P, &c));
     BSI_CHECK(c.sort_tile >= 0 && c.sort_tile <= 1024, BSI_E_INVAL, "sort_tile out of range");
     return eval_run(f, pos, P, u, grad, c, s);
 }

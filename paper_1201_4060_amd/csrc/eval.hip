@@ -148,6 +148,13 @@ __global__ __launch_bounds__(256) void k_gather(GatherArgs a) {
     direct_eval<N, CT, C, GRAD>(a, j);
 }
 
+// The same with N lanes per particle (orders 4 and 6), one wavefront a workgroup.
+template <int N, typename CT, int C, bool GRAD>
+__global__ __launch_bounds__(64) void k_gather_split(GatherArgs a) {
+    __shared__ __align__(16) SplitSlots<N, typename Acc<CT>::type> slots;
+    direct_split_eval<N, CT, C, GRAD>(a, long(logical_block(a.xcd_remap)) * (64 / N), slots);
+}
+
 // Wavefronts per SIMD that a tiled instance is compiled for: as many as its
 // registers allow without spilling (its LDS blocks may allow fewer).
 template <int N, typename CT, int C>
@@ -188,8 +195,32 @@ CellArgs cell_args(const bsi_field* f, const double* pos, long P) {
     return a;
 }
 
+// Several lanes per particle (k_gather_split) or one (k_gather).  Unbinned: several
+// while the particles do not fill the chip's wavefronts one lane each (64^3 FP32
+// order 6: 10^4 particles 22 against 32 us, 2 * 10^4 27 / 33, 4 * 10^4 37 / 35).
+// Binned: several for a sparse cloud, whose particles share little in the cache
+// (whole evaluations; 1024^3 BF16 scalar, 4 * 10^6: 1502 / 2070 us, 256^3 FP32 order
+// 6, 1.6 * 10^5: 122 / 167; from one particle in eight cells on one lane does with
+// fewer instructions: 128^3 FP32 scalar, 10^6: 178 / 158), but one again for the
+// largest stencils below one particle in 256 cells, bound by memory pages (512^3
+// FP32 order 6, 3.2 * 10^5: 421 / 379, 256^3, 8 * 10^4: 88 / 113).
+bool split_lanes(const bsi_field* f, long P, bool binned) {
+    if (!binned) return P < 32768;
+    const double dens = double(P) / (double(f->n[0]) * f->n[1] * f->n[2]);
+    const bool large = f->N * f->N * f->N * f->C >= 512;
+    return dens < 1.0 / 8 && (!large || dens >= 1.0 / 256);
+}
+
 template <int N, typename CT, int C>
-void launch_gather_t(const GatherArgs& ga, bool grad, unsigned nb, unsigned block, hipStream_t s) {
+void launch_gather_t(const GatherArgs& ga, bool grad, bool split, unsigned nb, unsigned block, hipStream_t s) {
+    if constexpr (N > 2) {
+        if (split) {
+            const unsigned ns = unsigned((ga.P + 64 / N - 1) / (64 / N));
+            if (grad) hipLaunchKernelGGL((k_gather_split<N, CT, C, true>), dim3(ns), dim3(64), 0, s, ga);
+            else hipLaunchKernelGGL((k_gather_split<N, CT, C, false>), dim3(ns), dim3(64), 0, s, ga);
+            return;
+        }
+    }
     if (grad)
         hipLaunchKernelGGL((k_gather<N, CT, C, true>), dim3(nb), dim3(block), 0, s, ga);
     else
@@ -197,17 +228,17 @@ void launch_gather_t(const GatherArgs& ga, bool grad, unsigned nb, unsigned bloc
 }
 
 template <typename CT>
-void launch_gather_ct(int N, int C, const GatherArgs& ga, bool grad, unsigned nb, unsigned block,
+void launch_gather_ct(int N, int C, const GatherArgs& ga, bool grad, bool split, unsigned nb, unsigned block,
                       hipStream_t s) {
     if (N == 2) {
-        if (C == 1) launch_gather_t<2, CT, 1>(ga, grad, nb, block, s);
-        else launch_gather_t<2, CT, 3>(ga, grad, nb, block, s);
+        if (C == 1) launch_gather_t<2, CT, 1>(ga, grad, split, nb, block, s);
+        else launch_gather_t<2, CT, 3>(ga, grad, split, nb, block, s);
     } else if (N == 4) {
-        if (C == 1) launch_gather_t<4, CT, 1>(ga, grad, nb, block, s);
-        else launch_gather_t<4, CT, 3>(ga, grad, nb, block, s);
+        if (C == 1) launch_gather_t<4, CT, 1>(ga, grad, split, nb, block, s);
+        else launch_gather_t<4, CT, 3>(ga, grad, split, nb, block, s);
     } else {
-        if (C == 1) launch_gather_t<6, CT, 1>(ga, grad, nb, block, s);
-        else launch_gather_t<6, CT, 3>(ga, grad, nb, block, s);
+        if (C == 1) launch_gather_t<6, CT, 1>(ga, grad, split, nb, block, s);
+        else launch_gather_t<6, CT, 3>(ga, grad, split, nb, block, s);
     }
 }
 
@@ -545,9 +576,10 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
         BSI_CHECK(ok, BSI_E_UNSUPPORTED, "no tiled gather instance for this tile size");
     } else {
         const unsigned nb = unsigned((P + block - 1) / block);
-        if (f->desc.coef == BSI_F64) launch_gather_ct<double>(f->N, f->C, ga, g, nb, block, s);
-        else if (f->desc.coef == BSI_F32) launch_gather_ct<float>(f->N, f->C, ga, g, nb, block, s);
-        else launch_gather_ct<uint16_t>(f->N, f->C, ga, g, nb, block, s);
+        const bool split = split_lanes(f, long(P), tile > 0);
+        if (f->desc.coef == BSI_F64) launch_gather_ct<double>(f->N, f->C, ga, g, split, nb, block, s);
+        else if (f->desc.coef == BSI_F32) launch_gather_ct<float>(f->N, f->C, ga, g, split, nb, block, s);
+        else launch_gather_ct<uint16_t>(f->N, f->C, ga, g, split, nb, block, s);
     }
     BSI_HIP(hipGetLastError());
     return BSI_OK;

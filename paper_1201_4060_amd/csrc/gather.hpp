@@ -854,53 +854,6 @@ struct Partial {
     AT u[C], g0[C], g1[C], g2[C];
 };
 
-// One axis-0 plane: rows row(ib), ib < N, reduced along axis 2 then axis 1,
-// accumulated into out with the plane's axis-0 weights w0k, wd0k (rows read
-// straight from global memory).
-template <int N, typename CT, typename AT, int C, bool GRAD, typename PlaneRowFn>
-__device__ __forceinline__ void contract_plane(AT w0k, AT wd0k, const AT (*w)[N], const AT (*wd)[N],
-                                               PlaneRowFn row, Partial<AT, C>& out) {
-    AT v[C], v1[C], v2[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) v[c] = v1[c] = v2[c] = AT(0);
-#pragma unroll
-    for (int ib = 0; ib < N; ++ib) {
-        const CT* r = row(ib);
-        CT raw[N * C];
-#pragma unroll
-        for (int e = 0; e < N * C; ++e) raw[e] = r[e];
-        AT tr[C], trd[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) tr[c] = trd[c] = AT(0);
-#pragma unroll
-        for (int e = 0; e < N; ++e) {
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const AT val = widen<CT, AT>(raw[e * C + c]);
-                tr[c] += w[2][e] * val;
-                if constexpr (GRAD) trd[c] += wd[2][e] * val;
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            v[c] += w[1][ib] * tr[c];
-            if constexpr (GRAD) {
-                v1[c] += wd[1][ib] * tr[c];
-                v2[c] += w[1][ib] * trd[c];
-            }
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        out.u[c] += w0k * v[c];
-        if constexpr (GRAD) {
-            out.g0[c] += wd0k * v[c];
-            out.g1[c] += w0k * v1[c];
-            out.g2[c] += w0k * v2[c];
-        }
-    }
-}
-
 // Raw values of one stencil row (N points x C components along axis 2) held
 // in registers between their LDS read and their use.  BF16 rows in LDS start
 // on 2-byte boundaries, and unaligned wide LDS reads are slow: they are read
@@ -957,6 +910,51 @@ template <typename AT, int C>
 struct PlaneSum {
     AT v[C], v1[C], v2[C];
 };
+
+// A row in global memory read value by value (the compiler merges FP32 and FP64
+// values into wide loads; BF16 ones stay 2-byte loads).
+template <int N, typename CT, int C>
+struct PlainRow {
+    CT raw[N * C];
+    __device__ __forceinline__ void load(const CT* r) {
+#pragma unroll
+        for (int e = 0; e < N * C; ++e) raw[e] = r[e];
+    }
+    __device__ __forceinline__ CT get(int e) const { return raw[e]; }
+};
+
+// One plane from rows row(ib), ib < N, in global memory, each read as a Row: the
+// loads are left to the compiler, which issues them all before the first sum.
+template <int N, typename CT, typename AT, int C, bool GRAD, typename Row, typename PlaneRowFn>
+__device__ __forceinline__ void plane_sum(const AT (*w)[N], const AT (*wd)[N], PlaneRowFn row, PlaneSum<AT, C>& V) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) V.v[c] = V.v1[c] = V.v2[c] = AT(0);
+#pragma unroll
+    for (int ib = 0; ib < N; ++ib) {
+        Row cur;
+        cur.load(row(ib));
+        AT tr[C], trd[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) tr[c] = trd[c] = AT(0);
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const AT val = widen<CT, AT>(cur.get(e * C + c));
+                tr[c] += w[2][e] * val;
+                if constexpr (GRAD) trd[c] += wd[2][e] * val;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            V.v[c] += w[1][ib] * tr[c];
+            if constexpr (GRAD) {
+                V.v1[c] += wd[1][ib] * tr[c];
+                V.v2[c] += w[1][ib] * trd[c];
+            }
+        }
+    }
+}
 
 // PlaneSum of NP consecutive planes from LDS rows row(k, ib), the rows
 // software-pipelined as in contract_planes (the same arithmetic, row by row).
@@ -1123,8 +1121,11 @@ __device__ __forceinline__ void contract_planes(const AT* w0, const AT* wd0, con
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < NIA; ++k)
-            contract_plane<N, CT, AT, C, GRAD>(w0[k], wd0[k], w, wd, [&](int ib) { return row(k, ib); }, out);
+        for (int k = 0; k < NIA; ++k) {
+            PlaneSum<AT, C> V;
+            plane_sum<N, CT, AT, C, GRAD, PlainRow<N, CT, C>>(w, wd, [&](int ib) { return row(k, ib); }, V);
+            chain_add<AT, C, GRAD>(out, w0[k], wd0[k], V);
+        }
     }
 }
 
@@ -1323,48 +1324,7 @@ __device__ __forceinline__ void block_dma(const void* grid, int n0, int n1, int 
     }
 }
 
-// One particle evaluated straight from the grid in global memory (the caches
-// provide the reuse between neighbouring binned particles).  j is the
-// particle's slot in binned order, or its index when the particles are not
-// binned.
-template <int N, typename CT, int C, bool GRAD>
-__device__ __forceinline__ void direct_eval(const GatherArgs& a, long j) {
-    using AT = typename Acc<CT>::type;
-    const int n[3] = {a.n0, a.n1, a.n2};
-    const double ih[3] = {a.ih0, a.ih1, a.ih2};
-    long p = j;
-    int cell[3];
-    AT t[3];
-    bool ok;
-    if (a.perm) {
-        p = long(a.perm[j]);
-        RawParticle<AT> raw;
-        raw.load(a.binned, j);
-        ok = locate(raw, n, ih, cell, t);
-    } else {
-        const double x[3] = {a.pos[3 * j], a.pos[3 * j + 1], a.pos[3 * j + 2]};
-        ok = locate<AT>(x, n, ih, cell, t);
-    }
-    if (!ok) {
-        write_nan<AT, C, GRAD>(a, p);
-        atomicAdd(a.nonfinite, 1ull);
-    } else {
-        AT w[3][N], wd[3][N];
-        particle_weights<N, AT>(a, t, w, wd);
-        const CT* base = static_cast<const CT*>(a.grid) + (long(a.cs * cell[0]) * a.P1 + a.cs * cell[1]) * a.pitch2 +
-                         long(a.cs * cell[2]) * C;
-        const long rowA = long(a.P1) * a.pitch2;
-        const long rowB = a.pitch2;
-        Partial<AT, C> lo, hi;
-        auto row = [&](int ia, int ib) { return base + ia * rowA + ib * rowB; };
-        contract_planes<N, CT, AT, C, GRAD, N / 2>(w[0], wd[0], w, wd, row, lo);
-        contract_planes<N, CT, AT, C, GRAD, N / 2>(w[0] + N / 2, wd[0] + N / 2, w, wd,
-                                                   [&](int k, int ib) { return row(N / 2 + k, ib); }, hi);
-        store_sum<AT, C, GRAD>(a, p, lo, hi);
-    }
-}
-
-// The aligned dword reads of a BF16 row (contract_plane) stay inside the row's
+// The aligned dword reads of a BF16 row (LdsRow) stay inside the row's
 // LDS pitch for every stencil start dc = 0 .. T2-1 of a T2-cell box.
 template <int N, int C, int T2, int LROW>
 constexpr bool bf16_rows_fit() {
@@ -1429,13 +1389,11 @@ __device__ __forceinline__ LaneRole lane_role(int lanes) {
 // lanes holding planes 0 and N / 2 fetch the other planes of their half from
 // the lanes next to them and add them up in the order of contract_planes; the
 // sum of the upper half goes to part 0, which stores.
-template <int N, typename CT, typename AT, int C, bool GRAD, int SL, int PS, typename RowFn>
-__device__ __forceinline__ void split_eval(const GatherArgs& a, long p, bool store, int part, const AT (*w)[N],
-                                           const AT (*wd)[N], RowFn rows) {
+template <int N, typename AT, int C, bool GRAD, int SL>
+__device__ __forceinline__ void split_sum(const GatherArgs& a, long p, bool store, int part, const AT (*w)[N],
+                                          const AT (*wd)[N], const PlaneSum<AT, C>* V) {
     constexpr int PPL = N / SL, H = N / 2;
     const int lane = threadIdx.x & 63;
-    PlaneSum<AT, C> V[PPL];
-    plane_sums<N, CT, AT, C, GRAD, PPL, PS>(w, wd, [&](int k, int ib) { return rows(part * PPL + k, ib); }, V);
     const bool upper = part * PPL >= H;
     AT w0[H], wd0[H];
 #pragma unroll
@@ -1502,6 +1460,16 @@ __device__ __forceinline__ void split_eval(const GatherArgs& a, long p, bool sto
     }
 }
 
+// The same from the LDS rows of the planes.
+template <int N, typename CT, typename AT, int C, bool GRAD, int SL, int PS, typename RowFn>
+__device__ __forceinline__ void split_eval(const GatherArgs& a, long p, bool store, int part, const AT (*w)[N],
+                                           const AT (*wd)[N], RowFn rows) {
+    constexpr int PPL = N / SL;
+    PlaneSum<AT, C> V[PPL];
+    plane_sums<N, CT, AT, C, GRAD, PPL, PS>(w, wd, [&](int k, int ib) { return rows(part * PPL + k, ib); }, V);
+    split_sum<N, AT, C, GRAD, SL>(a, p, store, part, w, wd, V);
+}
+
 // One particle on two lanes, a half of the axis-0 planes each.
 template <int N, typename CT, typename AT, int C, bool GRAD, int PS, typename RowFn>
 __device__ __forceinline__ void pair_eval(const GatherArgs& a, long p, bool store, int half, const AT (*w)[N],
@@ -1526,6 +1494,173 @@ __device__ __forceinline__ void pair_eval(const GatherArgs& a, long p, bool stor
         }
     }
     if (store) store_sum<AT, C, GRAD>(a, p, mine, other);
+}
+
+// Particle of slot j in binned order, or of index j when the particles are not
+// binned: its index p, cell and fractional position; false when it has none.
+template <typename AT>
+__device__ __forceinline__ bool direct_particle(const GatherArgs& a, long j, long& p, int* cell, AT* t) {
+    const int n[3] = {a.n0, a.n1, a.n2};
+    const double ih[3] = {a.ih0, a.ih1, a.ih2};
+    p = j;
+    if (a.perm) {
+        p = long(a.perm[j]);
+        RawParticle<AT> raw;
+        raw.load(a.binned, j);
+        return locate(raw, n, ih, cell, t);
+    }
+    const double x[3] = {a.pos[3 * j], a.pos[3 * j + 1], a.pos[3 * j + 2]};
+    return locate<AT>(x, n, ih, cell, t);
+}
+
+// Row (0, 0) of the particle's stencil in the grid.
+template <typename CT, int C>
+__device__ __forceinline__ const CT* direct_base(const GatherArgs& a, const int* cell) {
+    return static_cast<const CT*>(a.grid) + (long(a.cs * cell[0]) * a.P1 + a.cs * cell[1]) * a.pitch2 +
+           long(a.cs * cell[2]) * C;
+}
+
+// One particle evaluated straight from the grid in global memory (the caches
+// provide the reuse between neighbouring binned particles).
+template <int N, typename CT, int C, bool GRAD>
+__device__ __forceinline__ void direct_eval(const GatherArgs& a, long j) {
+    using AT = typename Acc<CT>::type;
+    long p;
+    int cell[3];
+    AT t[3];
+    if (!direct_particle(a, j, p, cell, t)) {
+        write_nan<AT, C, GRAD>(a, p);
+        atomicAdd(a.nonfinite, 1ull);
+        return;
+    }
+    AT w[3][N], wd[3][N];
+    particle_weights<N, AT>(a, t, w, wd);
+    const CT* base = direct_base<CT, C>(a, cell);
+    const long rowA = long(a.P1) * a.pitch2;
+    const long rowB = a.pitch2;
+    Partial<AT, C> lo, hi;
+    auto row = [&](int ia, int ib) { return base + ia * rowA + ib * rowB; };
+    contract_planes<N, CT, AT, C, GRAD, N / 2>(w[0], wd[0], w, wd, row, lo);
+    contract_planes<N, CT, AT, C, GRAD, N / 2>(w[0] + N / 2, wd[0] + N / 2, w, wd,
+                                               [&](int k, int ib) { return row(N / 2 + k, ib); }, hi);
+    store_sum<AT, C, GRAD>(a, p, lo, hi);
+}
+
+// Weight polynomials by stencil index, highest power first: row j of a basis holds
+// those of w_j, then of w_j' (without its chain factor).
+template <int N, typename AT>
+struct WeightRows {
+    static constexpr int ROW = (2 * N - 1 + 3) / 4 * 4;
+    AT row[3][N][ROW];   // B-spline, Lagrange, Hermite (N = 4)
+    template <typename Basis>
+    constexpr void fill(int b) {
+        Basis m{};
+        for (int j = 0; j < N; ++j) {
+            for (int i = 0; i < N; ++i) row[b][j][N - 1 - i] = AT(m.M[j][i]);
+            for (int i = 0; i < N - 1; ++i) row[b][j][2 * N - 2 - i] = AT(m.M1[j][i]);
+        }
+    }
+    constexpr WeightRows() : row{} {
+        fill<BSpline<N>>(0);
+        fill<LagrangeM<N>>(1);
+        if constexpr (N == 4) fill<HermiteM>(2);
+    }
+};
+template <int N, typename AT>
+__device__ const WeightRows<N, AT> weight_rows{};
+
+// Weight pairs of axes 1 and 2 of a wavefront's particles (the spare lanes of
+// order 6 have a slot too).
+template <int N, typename AT>
+struct SplitSlots {
+    AT pair[(63 + N) / N][2][N][2];
+};
+
+// Weights of a particle on N lanes: each lane forms those of stencil index `part`
+// along the three axes (the Horner steps of bspline_weights) and reads the others'
+// through LDS; w[0][i], i < N / 2, is plane i of the lane's half from the lane on
+// (split_sum).
+template <int N, typename AT>
+__device__ __forceinline__ void split_weights(const GatherArgs& a, const AT* t, int part, AT (*slot)[N][2],
+                                              AT (*w)[N], AT (*wd)[N]) {
+    const int lane = threadIdx.x & 63;
+    const int b = a.basis == BSI_BASIS_LAGRANGE ? 1 : a.basis == BSI_BASIS_HERMITE ? 2 : 0;
+    const AT* c = weight_rows<N, AT>.row[b][part];
+    const double ih[3] = {a.ih0, a.ih1, a.ih2};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        AT x = c[0], xd = c[N];
+#pragma unroll
+        for (int q = 1; q < N; ++q) x = fused(x, t[d], c[q]);
+#pragma unroll
+        for (int q = 1; q < N - 1; ++q) xd = fused(xd, t[d], c[N + q]);
+        xd *= AT(ih[d]);
+        if (d == 0) {
+            w[0][0] = x;
+            wd[0][0] = xd;
+        } else {
+            slot[d - 1][part][0] = x;
+            slot[d - 1][part][1] = xd;
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < 3; ++d)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            w[d][j] = slot[d - 1][j][0];
+            wd[d][j] = slot[d - 1][j][1];
+        }
+    if constexpr (N == 4) {
+        w[0][1] = quad_lane<QUAD_XOR1>(w[0][0]);
+        wd[0][1] = quad_lane<QUAD_XOR1>(wd[0][0]);
+    } else {
+#pragma unroll
+        for (int i = 1; i < N / 2; ++i) {
+            w[0][i] = __shfl(w[0][0], (lane + i) & 63, 64);
+            wd[0][i] = __shfl(wd[0][0], (lane + i) & 63, 64);
+        }
+    }
+#pragma unroll
+    for (int i = N / 2; i < N; ++i) {
+        w[0][i] = w[0][i - N / 2];
+        wd[0][i] = wd[0][i - N / 2];
+    }
+}
+
+// The same on N neighbouring lanes (N = 4 or 6), one axis-0 plane each: all of a
+// particle's rows are requested at once, where one lane works through N times as
+// many, and each weight is formed once.  j0 is the wavefront's first particle;
+// every lane of it calls this.  A BF16 row is read as aligned dwords, one 16-byte
+// load or three instead of 6 or 18 of two bytes; they end at most four bytes past
+// the row, and the grid's allocation goes on further (4 KB).
+template <int N, typename CT, int C, bool GRAD>
+__device__ __forceinline__ void direct_split_eval(const GatherArgs& a, long j0,
+                                                  SplitSlots<N, typename Acc<CT>::type>& slots) {
+    using AT = typename Acc<CT>::type;
+    const int lane = threadIdx.x & 63;
+    const int part = lane % N;
+    // spare lanes (N = 6: four) and lanes past the end work on the last particle
+    // of the wavefront and store nothing
+    const bool mine = lane / N < 64 / N && j0 + lane / N < a.P;
+    const long j = min(j0 + min(lane / N, 64 / N - 1), a.P - 1);
+    long p;
+    int cell[3];
+    AT t[3];
+    const bool ok = direct_particle(a, j, p, cell, t);
+    if (!ok) {
+        cell[0] = cell[1] = cell[2] = 0;
+        t[0] = t[1] = t[2] = AT(0);
+        if (mine && part == 0) {
+            write_nan<AT, C, GRAD>(a, p);
+            atomicAdd(a.nonfinite, 1ull);
+        }
+    }
+    const CT* plane = direct_base<CT, C>(a, cell) + part * (long(a.P1) * a.pitch2);
+    AT w[3][N], wd[3][N];
+    split_weights<N, AT>(a, t, part, slots.pair[lane / N], w, wd);
+    PlaneSum<AT, C> V;
+    plane_sum<N, CT, AT, C, GRAD, LdsRow<N, CT, C>>(w, wd, [&](int ib) { return plane + ib * long(a.pitch2); }, V);
+    split_sum<N, AT, C, GRAD, N>(a, p, mine && ok && part == 0, part, w, wd, &V);
 }
 
 // NaN outputs for the `count` particles without a cell (the last bucket),

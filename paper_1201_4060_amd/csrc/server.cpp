@@ -93,7 +93,8 @@ struct Request {
     void* u = nullptr;
     void* grad = nullptr;
     int64_t t_submit = 0;
-    bsi_eval_config cfg{};
+    bsi_eval_config cfg{};   // looked up: what the footprint is reckoned with
+    bsi_eval_config run{};   // evaluated with (needs no more)
     size_t bytes = 0;    // arena footprint
     size_t off = 0;      // arena offset
     int slot = -1;
@@ -172,7 +173,7 @@ bsi_status launch(bsi_server* sv, Slot& sl) {
     const hipStream_t s = sl.stream;
     BSI_HIP(hipEventRecord(sl.start, s));
     BSI_HIP(hipMemcpyAsync(d_pos, r.pos, 3 * size_t(r.P) * sizeof(double), hipMemcpyHostToDevice, s));
-    BSI_TRY(eval_run_ws(f, d_pos, r.P, d_u, r.grad ? d_g : nullptr, r.cfg, s, d_ws));
+    BSI_TRY(eval_run_ws(f, d_pos, r.P, d_u, r.grad ? d_g : nullptr, r.run, s, d_ws));
     BSI_HIP(hipMemcpyAsync(r.u, d_u, size_t(r.P) * f->C * osz, hipMemcpyDeviceToHost, s));
     if (r.grad) BSI_HIP(hipMemcpyAsync(r.grad, d_g, size_t(r.P) * f->C * 3 * osz, hipMemcpyDeviceToHost, s));
     BSI_HIP(hipEventRecord(sl.stop, s));
@@ -383,6 +384,7 @@ bsi_status bsi_server_submit(bsi_server* sv, int32_t field_id, const double* pos
         r.field = it->second;
     }
     BSI_TRY(lookup_config(sv->ctx, r.field, P, &r.cfg));
+    BSI_TRY(one_shot_config(sv->ctx, r.field, P, &r.run));
     r.pos = pos_host;
     r.P = P;
     r.u = u_host;

@@ -70,6 +70,8 @@ extern "C" bsi_status bsi_eval_static(bsi_field* f, const double* pos, int64_t P
     BSI_HIP(hipSetDevice(f->ctx->device));
     hipStream_t s = pick_stream(f->ctx, stream);
     f->last_stream = s;
+    // (the limit above is that of the looked-up configuration; this one needs no more)
+    if (!cfg) BSI_TRY(one_shot_config(f->ctx, f, P, &c));
     UntimedScope untimed;  // stage timing would create events
     return eval_run_ws(f, pos, P, u, grad, c, s, need ? ws : nullptr);
 }

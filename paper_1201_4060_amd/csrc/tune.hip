@@ -91,14 +91,15 @@ namespace {
 bool tiled_supported_any(const bsi_field* f, int tile) { return tiled_supported(f, tile); }
 }  // namespace
 
-bsi_status lookup_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out) {
+// The tuned configuration for P particles, if there is one.
+static bool tuned_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out) {
     const int d = density_class(f, P);
     std::lock_guard<std::mutex> lk(ctx->mu);
     const auto key = std::make_tuple(f->N, int(f->desc.coef), f->C, d);
     auto it = ctx->tune_table.find(key);
     if (it != ctx->tune_table.end()) {
         *out = it->second;
-        return BSI_OK;
+        return true;
     }
     int best = 3;  // accept neighbours up to two density classes away
     for (const auto& kv : ctx->tune_table) {
@@ -111,8 +112,39 @@ bsi_status lookup_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_c
             *out = kv.second;
         }
     }
-    if (best < 3) return BSI_OK;
+    return best < 3;
+}
+
+bsi_status lookup_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out) {
+    if (!tuned_config(ctx, f, P, out)) *out = default_config(f, P);
+    return BSI_OK;
+}
+
+// A single evaluation that nothing else runs beside: below some 10^5 particles it is
+// bound by the latency of its launches and of one item or particle, not by what
+// the LDS tiles save (whole evaluations, us, unbinned / binned and direct / tiled):
+//   64^3 FP32 order 6:     2 * 10^4  27 / 41 / 67,  1.6 * 10^5  72 / 84 / 111,
+//                          3.2 * 10^5  104 / 119 / 121,  10^6  292 / 281 / 175
+//   32^3 FP64 scalar:      10^4  19 / 35 / 59,  10^6  90 / 110 / 123
+//   256^3 FP32 order 4:    4 * 10^4  33 / 49 / -,  3.2 * 10^5  139 / 112 / 137,
+//                          10^6  397 / 271 / 214
+//   256^3 FP32 order 6:    4 * 10^4  57 / 67 / -,  3.2 * 10^5  322 / 191 / 180
+//   256^3 BF16 scalar:     3.2 * 10^5  206 / 86 / 143,  10^6  610 / 168 / 167
+//   64^3 FP64 order 6:     2 * 10^4  48 / 56 / 64,  4 * 10^4  81 / 63 / 73
+// So: no binning up to 48 Ki particles (half for the largest FP64 stencils), nor for
+// a grid that fits an XCD's L2 up to 2^28 stencil values; no tiles below 3 * 2^25.
+bsi_status one_shot_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out) {
+    if (tuned_config(ctx, f, P, out)) return BSI_OK;
     *out = default_config(f, P);
+    const int64_t stencil = int64_t(f->N) * f->N * f->N * f->C;
+    const int64_t few = f->desc.coef == BSI_F64 && stencil >= 512 ? 24576 : 49152;
+    const bool resident = f->grid_bytes <= (size_t(4) << 20);
+    if (P <= few || (resident && P <= (int64_t(1) << 28) / stencil)) {
+        out->variant = 1;
+        out->sort_tile = 0;
+    } else if (P <= (int64_t(3) << 25) / stencil) {
+        out->variant = 1;
+    }
     return BSI_OK;
 }
 

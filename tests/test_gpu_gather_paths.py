@@ -57,3 +57,40 @@ def test_tile_populations(n, C, N, coef):
                 tol = TOL_F64 if coef == "f64" else TOL_F32
                 assert np.max(rel_err(u, want_u)) < tol and np.max(rel_err(g, want_g)) < tol
             assert np.array_equal(u, ref[0]) and np.array_equal(g, ref[1]), cfg
+
+
+@pytest.mark.parametrize("n,C,N,coef,basis", [
+    (48, 3, 6, "f32", "bspline"), (48, 1, 6, "bf16", "bspline"), (36, 3, 6, "bf16", "bspline"),
+    (24, 3, 4, "f64", "lagrange"), (64, 3, 6, "f64", "bspline"), (32, 3, 4, "f32", "hermite"),
+    (16, 1, 2, "f32", "lagrange")])
+def test_direct_lanes(n, C, N, coef, basis):
+    """Evaluations without a configuration (the choice by particle count) and direct ones on one
+    or several lanes per particle: counts around a wavefront's 10 or 16 particles, around the
+    choices' limits, particles at the last cells of the grid and without a cell, value alone."""
+    import paper_1201_4060_amd as bsi
+    log(f"direct n={n} C={C} N={N} coef={coef} {basis}")
+    dt = {"f64": bsi.BSI_F64, "f32": bsi.BSI_F32, "bf16": bsi.BSI_BF16}[coef]
+    kw = {"bspline": {}, "lagrange": dict(basis=bsi.BSI_BASIS_LAGRANGE, prefilter=bsi.BSI_PREFILTER_NONE),
+          "hermite": dict(basis=bsi.BSI_BASIS_HERMITE, prefilter=bsi.BSI_PREFILTER_NONE)}[basis]
+    rng = np.random.default_rng(n + N)
+    gn = 2 * n if basis == "hermite" else n
+    grid = rng.standard_normal((C, gn, gn, gn))
+    last = 2 * np.pi * (1 - np.array([1e-9, 0.3 / n, 0.9 / n]))
+    with bsi.Context(0) as ctx, bsi.Field(ctx, n, C, N, dt, **kw) as f:
+        f.set_coefficients(dev(grid))
+        for P in (1, 9, 10, 11, 15, 16, 17, 64, 1003, 24577, 32767, 32768, 49152, 49153, 70001):
+            pos = rng.uniform(0, 2 * np.pi, (P, 3))
+            pos[:: 7] = last
+            if P > 20:
+                pos[5] = np.nan
+                pos[P - 1, 1] = np.inf
+            d = dev(pos)
+            ref = None
+            for c in (bsi.EvalConfig(sort_tile=8, block=256, xcd_remap=1, variant=0), None,
+                      bsi.EvalConfig(sort_tile=0, block=256, xcd_remap=0, variant=1),
+                      bsi.EvalConfig(sort_tile=8, block=256, xcd_remap=1, variant=1)):
+                u, g = (host(t) for t in f.eval(d, cfg=c))
+                v = host(f.eval(d, grad=False, cfg=c)[0])
+                ref = (u, g) if ref is None else ref
+                assert np.array_equal(u, ref[0], equal_nan=True) and np.array_equal(g, ref[1], equal_nan=True), (P, c)
+                assert np.array_equal(v, ref[0], equal_nan=True), (P, c)
