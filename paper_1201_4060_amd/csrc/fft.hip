@@ -10,36 +10,15 @@
 //                   storage type and written to the ghost-padded, component-
 //                   interleaved coefficient grid.
 //
-// Every line transform is a Stockham autosort FFT held in LDS: each stage has
-// every thread load its radix-R butterflies into registers, apply twiddles
-// from a table of exp(+2 pi i m / len) (computed on the host in FP64), do the
-// radix-R DFT and store to the self-sorted positions.  A workgroup transforms
-// W adjacent lines of a strided axis so that each global row access covers W
-// consecutive elements.
+// Every line transform is a Stockham autosort FFT: each stage has every thread
+// load its radix-R butterflies into registers, apply twiddles from a table of
+// exp(+2 pi i m / len) (computed on the host in FP64), do the radix-R DFT and
+// store to the self-sorted positions.  Pass C holds its lines in LDS throughout.  In
+// passes A and B a workgroup transforms W adjacent lines of a strided axis, so that
+// each global row access covers W consecutive elements; the lines stay in registers
+// and only change hands through LDS between two stages.
 #include "common.hpp"
-
-// LDS budget (KiB) of one strided-pass workgroup's line block: two blocks per
-// CU (160 KB of LDS), so 32 lines of 256 FP32 points or 16 lines of 512
-#ifndef BSI_FFT_LDS_KB
-#define BSI_FFT_LDS_KB 80
-#endif
-// The first pass reads the caller's spectrum (FP64 pairs, planes of 2 MB and
-// more apart for lines of 512 points and longer): there, blocks of 32 lines
-// (one per CU) give 512-byte row segments instead of 256.
-#ifndef BSI_FFT_LDS_KB_LONG_FIRST
-#define BSI_FFT_LDS_KB_LONG_FIRST 150
-#endif
-template <int LEN, bool FIRST>
-constexpr int strided_lds_kb() {
-    return (FIRST && LEN >= 512) ? BSI_FFT_LDS_KB_LONG_FIRST : BSI_FFT_LDS_KB;
-}
-// LDS budget of the narrow instance (a single leftover column)
-#define BSI_FFT_LDS_KB_NARROW 8
-// XCD-contiguous block order (k_fft_axis): the first pass with two blocks per CU
-template <int LEN, bool FIRST>
-constexpr bool fft_remap() {
-    return FIRST && strided_lds_kb<LEN, FIRST>() == BSI_FFT_LDS_KB;
-}
+#include "device.hpp"
 
 namespace bsi {
 
@@ -110,7 +89,21 @@ struct Radix {
     static constexpr int value = (REM % 3 == 0) ? 3 : (REM % 8 == 0) ? 8 : (REM % 4 == 0) ? 4 : 2;
 };
 
-// Stockham stages NS.. of an inverse FFT of length LEN on one LDS line.
+// Place of element i of an LDS line of FP64 values, one spare place every 16: the
+// lanes of a line write a stage's results at strides of 2 to 64 elements, which
+// would otherwise meet in a few banks (pass C at 128 x 192 lines of 256 FP64: 81 ->
+// 73 us; with FP32 values the index arithmetic costs more, 512^3: 745 -> 775).
+template <typename T>
+__host__ __device__ constexpr int spread(int i) {
+    return sizeof(T) == 8 ? i + (i >> 4) : i;
+}
+template <typename T>
+constexpr int spread_len(int n) {
+    return spread<T>(n - 1) + 1;
+}
+
+// Stockham stages NS.. of an inverse FFT of length LEN on one LDS line
+// (spread).
 // tw[m * TWS] = exp(+2 pi i m / LEN).  All threads of the block must call this
 // with the same template arguments (it contains block barriers).
 template <typename T, int LEN, int TEAM, int NS, int TWS>
@@ -127,7 +120,7 @@ __device__ __forceinline__ void fft_stages(cplx<T>* buf, const cplx<T>* tw, int 
             if (PER * TEAM == NB || j < NB) {
                 const int k = j % NS;
 #pragma unroll
-                for (int r = 0; r < R; ++r) v[q][r] = buf[j + r * NB];
+                for (int r = 0; r < R; ++r) v[q][r] = buf[spread<T>(j + r * NB)];
                 if constexpr (NS > 1) {
 #pragma unroll
                     for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], tw[r * k * TSTEP * TWS]);
@@ -135,7 +128,7 @@ __device__ __forceinline__ void fft_stages(cplx<T>* buf, const cplx<T>* tw, int 
                 dft<T, R>(v[q]);
             }
         }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int j = lane + q * TEAM;
@@ -143,36 +136,120 @@ __device__ __forceinline__ void fft_stages(cplx<T>* buf, const cplx<T>* tw, int 
                 const int k = j % NS;
                 const int base = (j / NS) * NS * R + k;
 #pragma unroll
-                for (int r = 0; r < R; ++r) buf[base + r * NS] = v[q][r];
+                for (int r = 0; r < R; ++r) buf[spread<T>(base + r * NS)] = v[q][r];
             }
         }
-        __syncthreads();
+        lds_barrier();
         fft_stages<T, LEN, TEAM, NS * R, TWS>(buf, tw, lane);
     }
 }
 
-// Lines per workgroup for the strided passes, within BSI_FFT_LDS_KB of LDS.
-// W lines per workgroup (longer contiguous row segments of the strided axis
-// are better for HBM), TEAM threads per line; TEAM divides LEN so that each
-// thread moves a fixed line and a fixed set of rows.  The line block plus the
-// twiddle table stay within BSI_FFT_LDS_KB.
-#ifndef BSI_FFT_WMAX
-#define BSI_FFT_WMAX 32
-#endif
-#ifndef BSI_FFT_THREADS
-#define BSI_FFT_THREADS 512
-#endif
-template <typename T, int LEN, int KB = BSI_FFT_LDS_KB>
+// The most threads a line can have when a thread that holds the rows a0 + q TEAM is
+// to hold whole butterflies of every stage: the largest power of two that divides
+// LEN / R for every radix R in turn.
+constexpr int common_pow2(int a, int b) {
+    int t = 1;
+    while (a % (2 * t) == 0 && b % (2 * t) == 0) t *= 2;
+    return t;
+}
+template <int LEN, int NS = 1>
+constexpr int line_team() {
+    if constexpr (NS == LEN) return LEN;
+    else return common_pow2(LEN / Radix<LEN / NS>::value, line_team<LEN, NS * Radix<LEN / NS>::value>());
+}
+
+// A strided-pass workgroup: W lines of TEAM threads.  Longer contiguous row segments
+// (W elements) are better for HBM and two workgroups a CU let one load while the
+// other transforms, so a workgroup gets half of the CU's LDS, or nearly all of it
+// where fewer than 8 lines would fit (FP64, 1024 points).
+template <typename T, int LEN>
 struct StridedCfg {
-    static constexpr int bytes = int(sizeof(cplx<T>));
-    static constexpr int raw = (KB * 1024 - LEN * bytes) / ((LEN + 1) * bytes);
-    static constexpr int W = raw >= 32 && BSI_FFT_WMAX >= 32 ? 32
-                             : raw >= 16 && BSI_FFT_WMAX >= 16 ? 16
-                             : raw >= 8 ? 8 : raw >= 4 ? 4 : 2;
-    static constexpr int POW2 = LEN & (-LEN);  // largest power of two dividing LEN
-    static constexpr int TEAM = (BSI_FFT_THREADS / W) < POW2 ? (BSI_FFT_THREADS / W) : POW2;
+    static constexpr int LP = LEN + 1;                     // odd: the lines start in different banks
+    static constexpr int LINE = LP * int(sizeof(cplx<T>));
+    static constexpr int TW = LEN * int(sizeof(cplx<T>));
+    static constexpr int KB = (80 * 1024 - TW) / LINE < 8 ? 150 : 80;
+    static constexpr int fit = (KB * 1024 - TW) / LINE;
+    static constexpr int W = fit >= 32 ? 32 : fit >= 16 ? 16 : 8;
+    static constexpr int MOST = 512 / W;
+    static constexpr int TEAM = MOST < line_team<LEN>() ? MOST : line_team<LEN>();
     static constexpr int THREADS = W * TEAM;
+    static constexpr int PER = LEN / TEAM;                 // values per thread
+    // wavefronts per SIMD to compile for
+    static constexpr int WAVES = THREADS < 512 ? 1 : KB == 80 ? 4 : 2;
 };
+
+// Keeps a stage's values as they were rounded: without it the multiplications that
+// form them may be fused into the next stage's additions, in some instances and not
+// in others, and the transform's last bits would depend on its length and axis.
+template <typename T>
+__device__ __forceinline__ void pin(cplx<T>& x) {
+    asm("" : "+v"(x.x), "+v"(x.y));
+}
+
+// The thread's butterflies of the stage that follows transforms of length NS, in
+// place: butterfly m is v[m + r BPT], r < R.
+template <typename T, int LEN, int TEAM, int R, int NS>
+__device__ __forceinline__ void butterflies(cplx<T>* v, const cplx<T>* tw, int a0) {
+    constexpr int BPT = LEN / R / TEAM;
+    static_assert(BPT * R * TEAM == LEN, "whole butterflies per thread");
+#pragma unroll
+    for (int m = 0; m < BPT; ++m) {
+        cplx<T> x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = v[m + r * BPT];
+        if constexpr (NS > 1) {
+            const int k = (a0 + m * TEAM) % NS * (LEN / (NS * R));
+#pragma unroll
+            for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw[r * k]);
+        }
+        dft<T, R>(x);
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[m + r * BPT] = x[r];
+    }
+}
+
+// The stages that follow transforms of length NS, on rows a0 + q TEAM of a line and
+// back to them.  A stage's result r of butterfly j belongs to row (j / NS) NS R + j %
+// NS + r NS: in this thread when TEAM divides NS, otherwise it changes hands through
+// LDS.  Adjacent lanes hold adjacent lines there (LP apart, odd), whatever the
+// stage's stride: no two of 32 meet in a bank.
+template <typename T, int LEN, int TEAM, int NS>
+__device__ __forceinline__ void line_stages(cplx<T>* v, cplx<T>* line, const cplx<T>* tw, int a0) {
+    if constexpr (NS < LEN) {
+        constexpr int R = Radix<LEN / NS>::value;
+        constexpr int BPT = LEN / R / TEAM, PER = LEN / TEAM;
+        butterflies<T, LEN, TEAM, R, NS>(v, tw, a0);
+        if constexpr (NS * R == LEN) {
+            // rows j + r LEN / R: as they are
+        } else if constexpr (NS % TEAM == 0) {
+            cplx<T> u[PER];
+#pragma unroll
+            for (int m = 0; m < BPT; ++m) {
+                constexpr int S = NS / TEAM;   // j / NS = m / S, j % NS = a0 + (m % S) TEAM
+#pragma unroll
+                for (int r = 0; r < R; ++r) u[m / S * (S * R) + m % S + r * S] = v[m + r * BPT];
+            }
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                v[q] = u[q];
+                pin(v[q]);
+            }
+        } else {
+            if constexpr (NS > 1) lds_barrier();   // the last exchange is read
+#pragma unroll
+            for (int m = 0; m < BPT; ++m) {
+                const int j = a0 + m * TEAM;
+                const int base = (j / NS) * (NS * R) + j % NS;
+#pragma unroll
+                for (int r = 0; r < R; ++r) line[base + r * NS] = v[m + r * BPT];
+            }
+            lds_barrier();
+#pragma unroll
+            for (int q = 0; q < PER; ++q) v[q] = line[a0 + q * TEAM];
+        }
+        line_stages<T, LEN, TEAM, NS * R>(v, line, tw, a0);
+    }
+}
 
 // Passes A and B.  Element (c, a, other, k2) of the [C][..][..][H] input sits
 // at c*sComp + a*sAxis + other*sOther + k2 (output: the same with the
@@ -180,42 +257,122 @@ struct StridedCfg {
 // FIRST: input is the caller's spectrum (InT pairs), multiplied by the FP64
 // symbol cAxis[a] * cOther[other] * c2[k2]; otherwise in-place on the work
 // buffer (in == out).
-// Columns [k2_begin, k2_end) of the half spectrum are transformed.  NARROW:
-// an instance with few lines per workgroup, for a last column left over by
-// the wide blocks (k2 = n2/2 when n2/2 is a multiple of their width).
-template <typename T, typename InT, int LEN, bool FIRST, bool NARROW = false>
-__global__ __launch_bounds__(BSI_FFT_THREADS) void k_fft_axis(const InT* in, cplx<T>* out, int k2_begin,
-                                                  int k2_end, int gx, int gy,
+template <typename T>
+struct AxisArgs {
+    const void* in;
+    cplx<T>* out;
+    int H, gx, gy;
+    long sAxis, sOther, sComp, oAxis, oOther, oComp;
+    const double *cAxis, *cOther, *c2;
+    const cplx<T>* twg;
+    int quarter;
+};
+
+// A workgroup's lines are W adjacent columns of one `other`, gx such blocks for the
+// H columns.  What bounds it is HBM: 512^3 x 3 from a complex128 spectrum moves 4.9 GB
+// at 4.6 TB/s (a copy reaches 5.2).  With the lines in LDS through all stages and one
+// workgroup a CU the first pass took 1137 us and 52 for a launch of its own for the
+// last column (1056 in this form), 1024^3 from complex64 3667 + 92 (2668); passes B
+// 742 and 1988 (729, 1963).  32 lines of 512 points and one workgroup a CU took
+// 1066, real and imaginary parts exchanged in turn for twice the lines 1400 (their
+// registers spill).
+template <typename T, typename InT, int LEN, bool FIRST>
+__global__ __launch_bounds__((StridedCfg<T, LEN>::THREADS))
+__attribute__((amdgpu_waves_per_eu(StridedCfg<T, LEN>::WAVES))) void
+k_fft_axis(AxisArgs<T> g) {
+    using Cfg = StridedCfg<T, LEN>;
+    constexpr int W = Cfg::W, TEAM = Cfg::TEAM, PER = Cfg::PER;
+    __shared__ cplx<T> lines[W * Cfg::LP];
+    __shared__ cplx<T> tw[LEN];
+    const int tid = threadIdx.x;
+    const int w = tid % W, a0 = tid / W;   // rows a0 + q TEAM of line w
+    int lb = blockIdx.x;
+    if constexpr (FIRST) {
+        // Workgroups are dispatched round-robin over the 8 XCDs; here each XCD is
+        // given one contiguous range of logical blocks instead, so that the
+        // column blocks of one row set run on one XCD and the cache lines they
+        // share in the caller's (unaligned) rows are L2 hits.  The work
+        // buffer's rows are aligned, and the plain order measured as fast or
+        // faster there.
+        const int q8 = gridDim.x / 8, r8 = gridDim.x % 8, x8 = lb % 8;
+        lb = x8 * q8 + (x8 < r8 ? x8 : r8) + lb / 8;
+    }
+    const int other = lb / g.gx % g.gy, bz = lb / (g.gx * g.gy);
+    const int k2_0 = lb % g.gx * W;
+    const bool valid = k2_0 + w < g.H;
+    const int k2 = k2_0 + (valid ? w : 0);
+    const long lane_base = long(bz) * g.sComp + long(other) * g.sOther + k2 + long(a0) * g.sAxis;
+    const long step = long(TEAM) * g.sAxis;
+    const long olane_base = long(bz) * g.oComp + long(other) * g.oOther + k2 + long(a0) * g.oAxis;
+    const long ostep = long(TEAM) * g.oAxis;
+    cplx<T> v[PER];
+    if constexpr (FIRST) {
+        const InT* in = static_cast<const InT*>(g.in);
+        const double cw = g.c2[k2];
+        const double cO = g.cOther[other];
+        InT re[PER], im[PER];
+        double ca[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const long e = lane_base + q * step;
+            re[q] = in[2 * e];
+            im[q] = in[2 * e + 1];
+            ca[q] = g.cAxis[q * TEAM + a0];
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const double m = (ca[q] * cO) * cw;
+            const double a = double(re[q]) * m, b = double(im[q]) * m;
+            // times i^quarter (the i's of derivative factors; 0 otherwise)
+            const double x = g.quarter == 0 ? a : g.quarter == 1 ? -b : g.quarter == 2 ? -a : b;
+            const double y = g.quarter == 0 ? b : g.quarter == 1 ? a : g.quarter == 2 ? -b : -a;
+            v[q] = {T(x), T(y)};
+            pin(v[q]);
+        }
+    } else {
+        const cplx<T>* src = static_cast<const cplx<T>*>(g.in);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) v[q] = src[lane_base + q * step];
+    }
+    for (int i = tid; i < LEN; i += Cfg::THREADS) tw[i] = g.twg[i];
+    cplx<T>* line = lines + w * Cfg::LP;
+    line_stages<T, LEN, TEAM, 1>(v, line, tw, a0);   // (tw is read after its first barrier)
+    if (valid) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) g.out[olane_base + q * ostep] = v[q];
+    }
+}
+
+// The first pass with its lines in LDS through all stages (fft_stages), for BF16 grids
+// with 512 or 1024 points along axis 0: the compiler fuses the multiplications of
+// these two instances otherwise than k_fft_axis's, and a last bit that differs here
+// rounds grid values to another BF16 value (one in 10^4, which the interpolated
+// values show).  1024^3 from complex64: 3667 us, k_fft_axis 2600; 512^3 x 3: 1137 +
+// 52, 1056.  Columns [k2_begin, k2_end); NARROW: few lines per workgroup, for the
+// column k2 = n2/2 left over when n2/2 is a multiple of the wide blocks' width.
+template <typename T, int LEN, bool NARROW>
+struct LdsCfg {
+    static constexpr int KB = NARROW ? 8 : 150;
+    static constexpr int bytes = int(sizeof(cplx<T>));
+    static constexpr int raw = (KB * 1024 - LEN * bytes) / ((LEN + 1) * bytes);
+    static constexpr int W = raw >= 32 ? 32 : raw >= 16 ? 16 : raw >= 8 ? 8 : raw >= 4 ? 4 : 2;
+    static constexpr int TEAM = 512 / W;
+    static constexpr int THREADS = W * TEAM;
+};
+template <typename T, typename InT, int LEN, bool NARROW>
+__global__ __launch_bounds__(512) void k_fft_first_lds(const InT* in, cplx<T>* out, int k2_begin,
+                                                  int k2_end,
                                                   long sAxis, long sOther, long sComp, long oAxis, long oOther,
                                                   long oComp, const double* cAxis,
                                                   const double* cOther, const double* c2,
                                                   const cplx<T>* twg, int quarter) {
-    using Cfg = StridedCfg<T, LEN, NARROW ? BSI_FFT_LDS_KB_NARROW : strided_lds_kb<LEN, FIRST>()>;
+    using Cfg = LdsCfg<T, LEN, NARROW>;
     constexpr int W = Cfg::W;
     constexpr int LP = LEN + 1;
     __shared__ cplx<T> lines[W * LP];
     __shared__ cplx<T> tw[LEN];
     const int tid = threadIdx.x;
-    // Block (column block bx, row set `other`, component bz).  Workgroups are
-    // dispatched round-robin over the 8 XCDs; in the first pass with two
-    // blocks per CU the grid is one-dimensional and each XCD is given one
-    // contiguous range of logical blocks instead, so that the column blocks of
-    // one row set run on one XCD and the cache lines they share in the
-    // caller's (unaligned) rows are L2 hits.  Elsewhere the plain
-    // three-dimensional grid measured as fast or faster.
-    int bx, other, bz;
-    if constexpr (!NARROW && fft_remap<LEN, FIRST>()) {
-        const long nblocks = gridDim.x;
-        const long q8 = nblocks / 8, r8 = nblocks % 8, x8 = blockIdx.x % 8;
-        const long lb = x8 * q8 + (x8 < r8 ? x8 : r8) + blockIdx.x / 8;
-        bx = int(lb % gx);
-        other = int((lb / gx) % gy);
-        bz = int(lb / (long(gx) * gy));
-    } else {
-        bx = blockIdx.x;
-        other = blockIdx.y;
-        bz = blockIdx.z;
-    }
+    const int bx = blockIdx.x, other = blockIdx.y, bz = blockIdx.z;
     const int k2_0 = k2_begin + bx * W;
     const long base = long(bz) * sComp + long(other) * sOther + k2_0;
     const long obase = long(bz) * oComp + long(other) * oOther + k2_0;
@@ -234,7 +391,7 @@ __global__ __launch_bounds__(BSI_FFT_THREADS) void k_fft_axis(const InT* in, cpl
     const long olane_base = obase + (valid ? w : 0) + long(a0) * oAxis;
     const long ostep = long(RSTEP) * oAxis;
     cplx<T> v[PER];
-    if constexpr (FIRST) {
+    {
         const double cw = (valid ? c2[k2_0 + w] : 0.0);
         const double cO = cOther[other];
         double re[PER], im[PER], ca[PER];
@@ -254,14 +411,10 @@ __global__ __launch_bounds__(BSI_FFT_THREADS) void k_fft_axis(const InT* in, cpl
             const double y = quarter == 0 ? b : quarter == 1 ? a : quarter == 2 ? -b : -a;
             v[q] = {T(x), T(y)};
         }
-    } else {
-        const cplx<T>* src = reinterpret_cast<const cplx<T>*>(in);
-#pragma unroll
-        for (int q = 0; q < PER; ++q) v[q] = src[lane_base + q * step];
     }
 #pragma unroll
     for (int q = 0; q < PER; ++q) lines[w * LP + q * RSTEP + a0] = v[q];
-    __syncthreads();
+    lds_barrier();
     fft_stages<T, LEN, Cfg::TEAM, 1, 1>(lines + (tid / Cfg::TEAM) * LP, tw, tid % Cfg::TEAM);
 #pragma unroll
     for (int q = 0; q < PER; ++q) v[q] = lines[w * LP + q * RSTEP + a0];
@@ -298,113 +451,159 @@ struct C2rCfg {
     static constexpr int TEAM = M >= 512 ? 64 : M >= 256 ? 32 : M >= 128 ? 16 : 8;
     static constexpr int LINES0 = 256 / (C * TEAM);
     // keep the LDS rows (plus the 2M twiddles) within about 40 KB
-    static constexpr int LBYTES = (40 * 1024 - 2 * M * int(sizeof(cplx<T>))) / (C * (M + 2) * int(sizeof(cplx<T>)));
+    static constexpr int LP = spread_len<T>(M + 2);
+    static constexpr int LBYTES = (40 * 1024 - 2 * M * int(sizeof(cplx<T>))) / (C * LP * int(sizeof(cplx<T>)));
     static constexpr int LINES1 = LINES0 < LBYTES ? LINES0 : LBYTES;
     static constexpr int LINES = LINES1 < 1 ? 1 : LINES1;
     static constexpr int THREADS = LINES * C * TEAM;
 };
 
-// Pass C.  work[c][g0][g1][k2] (k2 <= M, rows of Hp) -> grid[p0][p1][p2][c] with ghost
-// planes: padded index p holds grid index (p - padlo) mod n on every axis.
-// tw[m] = exp(+2 pi i m / (2M)), m < 2M.
-// A Hermite field stores the transformed field at stride st = 2 with offset
-// (a0, a1, a2) on every axis (the derivative orders); otherwise st = 1, a = 0.
-template <typename T, typename OutT, int M, int C>
-__global__ __launch_bounds__(256) void k_c2r(const cplx<T>* __restrict__ work, int Hp, OutT* __restrict__ grid,
-                                             int n0, int n1, int P0, int P1, int P2, int pitch2,
-                                             int padlo, const cplx<T>* __restrict__ twg, int st, int a0,
-                                             int a1, int a2) {
-    using Cfg = C2rCfg<T, M, C>;
-    constexpr int H = M + 1;
-    constexpr int LP = M + 2;
-    constexpr int NL = Cfg::LINES * C;  // transforms per block
-    __shared__ cplx<T> zb[NL * LP];
-    __shared__ cplx<T> tw[2 * M];
-    const int tid = threadIdx.x;
-    const long nlines = long(n0) * n1;
-    const long line0 = long(blockIdx.x) * Cfg::LINES;
-    const long compStride = nlines * Hp;
+// Pieces of pass C.  A workgroup holds NL lines of M + 1 half-spectrum values in
+// zb, LP = M + 2 apart, with the twiddles tw[m] = exp(+2 pi i m / (2M)), m < 2M.
 
-    for (int i = tid; i < 2 * M; i += Cfg::THREADS) tw[i] = twg[i];
-    // load every (line, component) row of H complex values; all loads of a
-    // thread are issued before its LDS stores
-    constexpr int ITER = (NL * H + Cfg::THREADS - 1) / Cfg::THREADS;
-    {
-        cplx<T> v[ITER];
+// The lines from work[c][g0][g1][k2] (rows of Hp, at least M + 2): line l of the
+// block is zb line l * C + c.  All loads of a thread are issued before its stores;
+// 16 bytes each (the last pair of FP32 values ends in the row's padding).
+template <typename T, int M, int C, int LINES, int THREADS>
+__device__ __forceinline__ void c2r_load(const cplx<T>* __restrict__ work, int Hp, long nlines, cplx<T>* zb) {
+    constexpr int LP = spread_len<T>(M + 2), NL = LINES * C;
+    constexpr int VEC = 16 / int(sizeof(cplx<T>));      // values per load
+    constexpr int NV = (M + 1 + VEC - 1) / VEC;         // loads per line
+    constexpr int ITER = (NL * NV + THREADS - 1) / THREADS;
+    const long line0 = long(blockIdx.x) * LINES;
+    const long compStride = nlines * Hp;
+    u32x4 v[ITER];
 #pragma unroll
-        for (int q = 0; q < ITER; ++q) {
-            const int idx = q * Cfg::THREADS + tid;
-            const int f = idx / H, k = idx - (idx / H) * H;
-            const int l = f / C, c = f - (f / C) * C;
-            const bool ok = idx < NL * H && line0 + l < nlines;
-            v[q] = work[ok ? long(c) * compStride + (line0 + l) * Hp + k : 0];
-        }
+    for (int q = 0; q < ITER; ++q) {
+        const int idx = q * THREADS + int(threadIdx.x);
+        const int f = idx / NV, k = idx - f * NV;
+        const int l = f / C, c = f - l * C;
+        const bool ok = idx < NL * NV && line0 + l < nlines;
+        v[q] = *reinterpret_cast<const u32x4*>(work + (ok ? long(c) * compStride + (line0 + l) * Hp + k * VEC : 0));
+    }
 #pragma unroll
-        for (int q = 0; q < ITER; ++q) {
-            const int idx = q * Cfg::THREADS + tid;
-            if (idx < NL * H) {
-                const int f = idx / H, k = idx - (idx / H) * H;
-                zb[f * LP + k] = v[q];
-            }
+    for (int q = 0; q < ITER; ++q) {
+        const int idx = q * THREADS + int(threadIdx.x);
+        union {
+            u32x4 v;
+            cplx<T> z[VEC];
+        } o;
+        o.v = v[q];
+        if (idx < NL * NV) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) zb[idx / NV * LP + spread<T>(idx % NV * VEC + i)] = o.z[i];
         }
     }
-    __syncthreads();
-    // even/odd twist: Z[k] = (X[k] + conj X[M-k]) + i e^{2 pi i k/(2M)} (X[k] - conj X[M-k]),
-    // with the imaginary parts of X[0] and X[M] dropped (real-FFT semantics).
-    for (int idx = tid; idx < NL * (M / 2 + 1); idx += Cfg::THREADS) {
+}
+
+// Even/odd twist of NL lines: Z[k] = (X[k] + conj X[M-k]) + i e^{2 pi i k/(2M)}
+// (X[k] - conj X[M-k]), with the imaginary parts of X[0] and X[M] dropped
+// (real-FFT semantics).  After the length-M transform, real value g of the line is
+// word real_word(g).
+template <typename T>
+__device__ __forceinline__ int real_word(int g) { return 2 * spread<T>(g >> 1) + (g & 1); }
+template <typename T, int M, int NL, int THREADS>
+__device__ __forceinline__ void c2r_twist(cplx<T>* zb, const cplx<T>* tw) {
+    constexpr int LP = spread_len<T>(M + 2);
+    for (int idx = threadIdx.x; idx < NL * (M / 2 + 1); idx += THREADS) {
         const int f = idx / (M / 2 + 1), k = idx % (M / 2 + 1);
         cplx<T>* X = zb + f * LP;
         if (k == 0) {
-            const T a = X[0].x, b = X[M].x;
+            const T a = X[0].x, b = X[spread<T>(M)].x;
             X[0] = {a + b, a - b};
         } else {
             const int kk = M - k;
-            const cplx<T> A = X[k], B = X[kk];
+            const cplx<T> A = X[spread<T>(k)], B = X[spread<T>(kk)];
             const cplx<T> Bc = {B.x, -B.y}, Ac = {A.x, -A.y};
             const cplx<T> z1 = cadd(cadd(A, Bc), cmul_i(cmul(tw[k], csub(A, Bc))));
             if (k < kk) {
                 const cplx<T> z2 = cadd(cadd(B, Ac), cmul_i(cmul(tw[kk], csub(B, Ac))));
-                X[kk] = z2;
+                X[spread<T>(kk)] = z2;
             }
-            X[k] = z1;
+            X[spread<T>(k)] = z1;
         }
     }
-    __syncthreads();
+}
+
+// The padded grid rows that a line goes to: itself and its periodic ghost copies.
+// Grid point g of axes 0 and 1 stands at p(g) = st g + o; one copy minus or plus
+// st n where that is inside [0, P).
+struct RowTargets {
+    long at[4];   // element offsets; -1: none
+};
+__device__ __forceinline__ RowTargets row_targets(long line, int n0, int n1, int P0, int P1, int pitch2, int st,
+                                                  int o0, int o1) {
+    const int g0 = int(line / n1), g1 = int(line % n1);
+    const int p0a = st * g0 + o0, p1a = st * g1 + o1;
+    const int p0b = p0a - st * n0 >= 0 ? p0a - st * n0 : p0a + st * n0 < P0 ? p0a + st * n0 : -1;
+    const int p1b = p1a - st * n1 >= 0 ? p1a - st * n1 : p1a + st * n1 < P1 ? p1a + st * n1 : -1;
+    RowTargets r;
+    r.at[0] = (long(p0a) * P1 + p1a) * pitch2;
+    r.at[1] = p1b >= 0 ? (long(p0a) * P1 + p1b) * pitch2 : -1;
+    r.at[2] = p0b >= 0 ? (long(p0b) * P1 + p1a) * pitch2 : -1;
+    r.at[3] = p0b >= 0 && p1b >= 0 ? (long(p0b) * P1 + p1b) * pitch2 : -1;
+    return r;
+}
+
+// Writes the rows of the block's lines, 16 bytes a thread, the chunks of all lines
+// dealt to the threads together (a row has as few as 35 values).  value(l, e) is
+// element e < rowElems of line l; the row's padding is written as zeros.
+template <typename OutT, int LINES, int THREADS, typename ValueFn>
+__device__ __forceinline__ void c2r_store(OutT* __restrict__ grid, const RowTargets* rows, int lines, int rowElems,
+                                          ValueFn value) {
+    constexpr int VEC = 16 / int(sizeof(OutT));
+    const int chunks = (rowElems + VEC - 1) / VEC;
+    // idx / chunks for idx < 2^22: the quotient of the midpoints is at least 1 / (2
+    // chunks) away from the next integer
+    const float inv = 1.0f / float(chunks);
+    for (int idx = threadIdx.x; idx < lines * chunks; idx += THREADS) {
+        const int l = LINES == 1 ? 0 : int((float(idx) + 0.5f) * inv);
+        const int e0 = (idx - l * chunks) * VEC;
+        union {
+            u32x4 v;
+            OutT e[VEC];
+        } o;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) o.e[i] = e0 + i < rowElems ? value(l, e0 + i) : OutT(0);
+        const RowTargets& r = rows[l];
+        *reinterpret_cast<u32x4*>(grid + r.at[0] + e0) = o.v;
+#pragma unroll
+        for (int j = 1; j < 4; ++j)
+            if (r.at[j] >= 0) *reinterpret_cast<u32x4*>(grid + r.at[j] + e0) = o.v;
+    }
+}
+
+// Pass C.  work[c][g0][g1][k2] (k2 <= M, rows of Hp) -> grid[p0][p1][p2][c] with ghost
+// planes: padded index p holds grid index (p - padlo) mod n on every axis.
+template <typename T, typename OutT, int M, int C>
+__global__ __launch_bounds__(256) void k_c2r(const cplx<T>* __restrict__ work, int Hp, OutT* __restrict__ grid,
+                                             int n0, int n1, int P0, int P1, int P2, int pitch2,
+                                             int padlo, const cplx<T>* __restrict__ twg) {
+    using Cfg = C2rCfg<T, M, C>;
+    constexpr int LP = Cfg::LP;
+    constexpr int NL = Cfg::LINES * C;  // transforms per block
+    __shared__ __align__(16) cplx<T> zb[NL * LP];
+    __shared__ cplx<T> tw[2 * M];
+    __shared__ RowTargets rows[Cfg::LINES];
+    const int tid = threadIdx.x;
+    const long nlines = long(n0) * n1;
+    const long line0 = long(blockIdx.x) * Cfg::LINES;
+    const int lines = int(min(long(Cfg::LINES), nlines - line0));
+
+    for (int i = tid; i < 2 * M; i += Cfg::THREADS) tw[i] = twg[i];
+    if (tid < lines) rows[tid] = row_targets(line0 + tid, n0, n1, P0, P1, pitch2, 1, padlo, padlo);
+    c2r_load<T, M, C, Cfg::LINES, Cfg::THREADS>(work, Hp, nlines, zb);
+    lds_barrier();
+    c2r_twist<T, M, NL, Cfg::THREADS>(zb, tw);
+    lds_barrier();
     fft_stages<T, M, Cfg::TEAM, 1, 2>(zb + (tid / Cfg::TEAM) * LP, tw, tid % Cfg::TEAM);
-    // scatter rows (with periodic ghost copies) to the interleaved grid
-    const int rowElems = P2 * C;
-    for (int l = 0; l < Cfg::LINES; ++l) {
-        const long line = line0 + l;
-        if (line >= nlines) break;
-        const int g0 = int(line / n1), g1 = int(line % n1);
-        // padded rows holding grid row g: st g + a + padlo, and one periodic
-        // ghost copy (minus or plus st n) when that falls inside [0, P)
-        const int p0a = st * g0 + a0 + padlo;
-        const int p0b = (p0a - st * n0 >= 0) ? p0a - st * n0 : ((p0a + st * n0 < P0) ? p0a + st * n0 : -1);
-        const int p1a = st * g1 + a1 + padlo;
-        const int p1b = (p1a - st * n1 >= 0) ? p1a - st * n1 : ((p1a + st * n1 < P1) ? p1a + st * n1 : -1);
-        OutT* r_aa = grid + (long(p0a) * P1 + p1a) * pitch2;
-        OutT* r_ab = p1b >= 0 ? grid + (long(p0a) * P1 + p1b) * pitch2 : nullptr;
-        OutT* r_ba = p0b >= 0 ? grid + (long(p0b) * P1 + p1a) * pitch2 : nullptr;
-        OutT* r_bb = (p0b >= 0 && p1b >= 0) ? grid + (long(p0b) * P1 + p1b) * pitch2 : nullptr;
-        for (int e = tid; e < rowElems; e += Cfg::THREADS) {
-            const int p2 = e / C, c = e % C;
-            int q2 = p2 - padlo - a2;
-            if (st == 2) {
-                if (q2 & 1) continue;   // another derivative field's entry
-                q2 >>= 1;
-            }
-            int g2 = q2;
-            if (g2 < 0) g2 += 2 * M;
-            else if (g2 >= 2 * M) g2 -= 2 * M;
-            const cplx<T> z = zb[(l * C + c) * LP + (g2 >> 1)];
-            const OutT v = store_cast<OutT>((g2 & 1) ? z.y : z.x);
-            r_aa[e] = v;
-            if (r_ab) r_ab[e] = v;
-            if (r_ba) r_ba[e] = v;
-            if (r_bb) r_bb[e] = v;
-        }
-    }
+    const T* real = reinterpret_cast<const T*>(zb);
+    c2r_store<OutT, Cfg::LINES, Cfg::THREADS>(grid, rows, lines, P2 * C, [&](int l, int e) {
+        const int p2 = e / C, c = e % C;
+        int g2 = p2 - padlo;
+        g2 += g2 < 0 ? 2 * M : g2 >= 2 * M ? -2 * M : 0;
+        return store_cast<OutT>(real[(l * C + c) * 2 * LP + real_word<T>(g2)]);
+    });
 }
 
 // Pass C of a Hermite field pair: from one line X of the half spectrum (the
@@ -421,88 +620,38 @@ __global__ __launch_bounds__(256) void k_c2r_dual(const cplx<T>* __restrict__ wo
                                                   const double* __restrict__ dtab, int a0, int a1) {
     using Cfg = C2rCfg<T, M, 2 * C>;
     constexpr int H = M + 1;
-    constexpr int LP = M + 2;
+    constexpr int LP = Cfg::LP;
     constexpr int NL = Cfg::LINES * C;  // lines of X per block; the Y lines follow
-    __shared__ cplx<T> zb[2 * NL * LP];
+    __shared__ __align__(16) cplx<T> zb[2 * NL * LP];
     __shared__ cplx<T> tw[2 * M];
+    __shared__ RowTargets rows[Cfg::LINES];
     const int tid = threadIdx.x;
     const long nlines = long(n0) * n1;
     const long line0 = long(blockIdx.x) * Cfg::LINES;
-    const long compStride = nlines * Hp;
+    const int lines = int(min(long(Cfg::LINES), nlines - line0));
 
     for (int i = tid; i < 2 * M; i += Cfg::THREADS) tw[i] = twg[i];
-    constexpr int ITER = (NL * H + Cfg::THREADS - 1) / Cfg::THREADS;
-    {
-        cplx<T> v[ITER];
-#pragma unroll
-        for (int q = 0; q < ITER; ++q) {
-            const int idx = q * Cfg::THREADS + tid;
-            const int f = idx / H, k = idx - (idx / H) * H;
-            const int l = f / C, c = f - (f / C) * C;
-            const bool ok = idx < NL * H && line0 + l < nlines;
-            v[q] = work[ok ? long(c) * compStride + (line0 + l) * Hp + k : 0];
-        }
-#pragma unroll
-        for (int q = 0; q < ITER; ++q) {
-            const int idx = q * Cfg::THREADS + tid;
-            if (idx < NL * H) {
-                const int f = idx / H, k = idx - (idx / H) * H;
-                const T d = T(dtab[k]);
-                zb[f * LP + k] = v[q];
-                zb[(NL + f) * LP + k] = {-d * v[q].y, d * v[q].x};  // i d X
-            }
-        }
+    if (tid < lines) rows[tid] = row_targets(line0 + tid, n0, n1, P0, P1, pitch2, 2, a0, a1);
+    c2r_load<T, M, C, Cfg::LINES, Cfg::THREADS>(work, Hp, nlines, zb);
+    lds_barrier();
+    for (int idx = tid; idx < NL * H; idx += Cfg::THREADS) {
+        const int f = idx / H, k = idx - f * H;
+        const T d = T(dtab[k]);
+        const cplx<T> x = zb[f * LP + spread<T>(k)];
+        zb[(NL + f) * LP + spread<T>(k)] = {-d * x.y, d * x.x};  // i d X
     }
-    __syncthreads();
-    // even/odd twist of every line (as k_c2r)
-    for (int idx = tid; idx < 2 * NL * (M / 2 + 1); idx += Cfg::THREADS) {
-        const int f = idx / (M / 2 + 1), k = idx % (M / 2 + 1);
-        cplx<T>* X = zb + f * LP;
-        if (k == 0) {
-            const T a = X[0].x, b = X[M].x;
-            X[0] = {a + b, a - b};
-        } else {
-            const int kk = M - k;
-            const cplx<T> A = X[k], B = X[kk];
-            const cplx<T> Bc = {B.x, -B.y}, Ac = {A.x, -A.y};
-            const cplx<T> z1 = cadd(cadd(A, Bc), cmul_i(cmul(tw[k], csub(A, Bc))));
-            if (k < kk) {
-                const cplx<T> z2 = cadd(cadd(B, Ac), cmul_i(cmul(tw[kk], csub(B, Ac))));
-                X[kk] = z2;
-            }
-            X[k] = z1;
-        }
-    }
-    __syncthreads();
+    lds_barrier();
+    c2r_twist<T, M, 2 * NL, Cfg::THREADS>(zb, tw);
+    lds_barrier();
     fft_stages<T, M, Cfg::TEAM, 1, 2>(zb + (tid / Cfg::TEAM) * LP, tw, tid % Cfg::TEAM);
-    // rows of the doubled grid: st = 2 with offsets (a0, a1); both parities of
-    // axis 2; one periodic ghost copy per axis where it falls inside [0, P)
-    const int rowElems = P2 * C;
-    for (int l = 0; l < Cfg::LINES; ++l) {
-        const long line = line0 + l;
-        if (line >= nlines) break;
-        const int g0 = int(line / n1), g1 = int(line % n1);
-        const int p0a = 2 * g0 + a0;
-        const int p0b = (p0a + 2 * n0 < P0) ? p0a + 2 * n0 : -1;
-        const int p1a = 2 * g1 + a1;
-        const int p1b = (p1a + 2 * n1 < P1) ? p1a + 2 * n1 : -1;
-        OutT* r_aa = grid + (long(p0a) * P1 + p1a) * pitch2;
-        OutT* r_ab = p1b >= 0 ? grid + (long(p0a) * P1 + p1b) * pitch2 : nullptr;
-        OutT* r_ba = p0b >= 0 ? grid + (long(p0b) * P1 + p1a) * pitch2 : nullptr;
-        OutT* r_bb = (p0b >= 0 && p1b >= 0) ? grid + (long(p0b) * P1 + p1b) * pitch2 : nullptr;
-        for (int e = tid; e < rowElems; e += Cfg::THREADS) {
-            const int p2 = e / C, c = e % C;
-            const int a2 = p2 & 1;
-            int g2 = p2 >> 1;
-            if (g2 >= 2 * M) g2 -= 2 * M;
-            const cplx<T> z = zb[((a2 ? NL : 0) + l * C + c) * LP + (g2 >> 1)];
-            const OutT v = store_cast<OutT>((g2 & 1) ? z.y : z.x);
-            r_aa[e] = v;
-            if (r_ab) r_ab[e] = v;
-            if (r_ba) r_ba[e] = v;
-            if (r_bb) r_bb[e] = v;
-        }
-    }
+    // rows of the doubled grid: both parities of axis 2
+    const T* real = reinterpret_cast<const T*>(zb);
+    c2r_store<OutT, Cfg::LINES, Cfg::THREADS>(grid, rows, lines, P2 * C, [&](int l, int e) {
+        const int p2 = e / C, c = e % C;
+        int g2 = p2 >> 1;
+        if (g2 >= 2 * M) g2 -= 2 * M;
+        return store_cast<OutT>(real[((p2 & 1 ? NL : 0) + l * C + c) * 2 * LP + real_word<T>(g2)]);
+    });
 }
 
 // Dense FP64 [C][n0][n1][n2] <-> padded interleaved grid.
@@ -548,31 +697,42 @@ __global__ void k_to_dense(const O* __restrict__ grid, double* __restrict__ dens
 
 namespace {
 
+template <typename InT, int LEN>
+void launch_first_lds(int others, int C, const InT* in, cplx<float>* out, int H, long sAxis, long sOther, long sComp,
+                      long oAxis, long oOther, long oComp, const double* cAxis, const double* cOther,
+                      const double* c2, const cplx<float>* tw, hipStream_t s, int quarter) {
+    using Cfg = LdsCfg<float, LEN, false>;
+    using CfgN = LdsCfg<float, LEN, true>;
+    const int full = H - 1 >= Cfg::W && (H - 1) % Cfg::W == 0 ? H - 1 : H;
+    const unsigned gx = unsigned((full + Cfg::W - 1) / Cfg::W);
+    hipLaunchKernelGGL((k_fft_first_lds<float, InT, LEN, false>), dim3(gx, others, C), dim3(Cfg::THREADS), 0, s, in,
+                       out, 0, full, sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, quarter);
+    if (full < H)
+        hipLaunchKernelGGL((k_fft_first_lds<float, InT, LEN, true>), dim3(1, others, C), dim3(CfgN::THREADS), 0, s, in,
+                           out, full, H, sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, quarter);
+}
+
 template <typename T, typename InT, bool FIRST>
-bsi_status launch_axis(int len, dim3 grid, const InT* in, cplx<T>* out, int H, long sAxis, long sOther,
+bsi_status launch_axis(int len, int others, int C, const InT* in, cplx<T>* out, int H, long sAxis, long sOther,
                        long sComp, long oAxis, long oOther, long oComp, const double* cAxis,
-                       const double* cOther, const double* c2,
-                       const cplx<T>* tw, hipStream_t s, int* Wout, int quarter = 0) {
-// In the first pass, a last block of wide lines holding a single column (k2 =
-// n2/2 when n2/2 is a multiple of the width) is replaced by a narrow launch for
-// that column (512^3 x3 FP32: 1273 -> 1136 + 52 us; in pass B the narrow
-// launch costs what it saves).
+                       const double* cOther, const double* c2, const cplx<T>* tw, hipStream_t s, int quarter = 0,
+                       bool bf16 = false) {
+    if constexpr (FIRST && sizeof(T) == 4) {
+        if (bf16 && (len == 512 || len == 1024)) {
+            (len == 512 ? launch_first_lds<InT, 512> : launch_first_lds<InT, 1024>)(
+                others, C, in, out, H, sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, s, quarter);
+            BSI_HIP(hipGetLastError());
+            return BSI_OK;
+        }
+    }
 #define BSI_AXIS_CASE(L)                                                                           \
     case L: {                                                                                      \
-        using Cfg = StridedCfg<T, L, strided_lds_kb<L, FIRST>()>;                                  \
-        using CfgN = StridedCfg<T, L, BSI_FFT_LDS_KB_NARROW>;                                      \
-        *Wout = Cfg::W;                                                                            \
-        const int full = FIRST && H - 1 >= Cfg::W && (H - 1) % Cfg::W == 0 ? H - 1 : H;           \
-        const int gx = (full + Cfg::W - 1) / Cfg::W;                                               \
-        const dim3 g = fft_remap<L, FIRST>() ? dim3(unsigned(gx) * grid.y * grid.z)              \
-                                              : dim3(unsigned(gx), grid.y, grid.z);              \
-        hipLaunchKernelGGL((k_fft_axis<T, InT, L, FIRST>), g, dim3(Cfg::THREADS), 0, s, in, out, 0, full, gx, \
-                           int(grid.y), sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, \
-                           quarter);                                                              \
-        if (full < H)                                                                              \
-            hipLaunchKernelGGL((k_fft_axis<T, InT, L, FIRST, true>), dim3(1u, grid.y, grid.z),     \
-                               dim3(CfgN::THREADS), 0, s, in, out, full, H, 1, int(grid.y), sAxis, sOther, \
-                               sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, quarter);       \
+        using Cfg = StridedCfg<T, L>;                                                              \
+        const int gx = (H + Cfg::W - 1) / Cfg::W;                                                  \
+        hipLaunchKernelGGL((k_fft_axis<T, InT, L, FIRST>), dim3(unsigned(gx) * unsigned(others * C)), \
+                           dim3(Cfg::THREADS), 0, s,                                               \
+                           AxisArgs<T>{in, out, H, gx, others, sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, \
+                                       cOther, c2, tw, quarter});                                  \
         break;                                                                                     \
     }
     switch (len) {
@@ -602,15 +762,14 @@ bsi_status launch_axis(int len, dim3 grid, const InT* in, cplx<T>* out, int H, l
 
 template <typename T, typename OutT, int C>
 bsi_status launch_c2r(int M, const cplx<T>* work, int Hp, OutT* grid, int n0, int n1, int P0, int P1, int P2,
-                      int pitch2, int padlo, const cplx<T>* tw, hipStream_t s, int st = 1, int a0 = 0,
-                      int a1 = 0, int a2 = 0) {
+                      int pitch2, int padlo, const cplx<T>* tw, hipStream_t s) {
     const long nlines = long(n0) * n1;
 #define BSI_C2R_CASE(MM)                                                                           \
     case MM: {                                                                                     \
         using Cfg = C2rCfg<T, MM, C>;                                                                 \
         const unsigned nb = unsigned((nlines + Cfg::LINES - 1) / Cfg::LINES);                      \
         hipLaunchKernelGGL((k_c2r<T, OutT, MM, C>), dim3(nb), dim3(Cfg::THREADS), 0, s, work, Hp, grid, \
-                           n0, n1, P0, P1, P2, pitch2, padlo, tw, st, a0, a1, a2);                \
+                           n0, n1, P0, P1, P2, pitch2, padlo, tw);                                \
         break;                                                                                     \
     }
     switch (M) {
@@ -678,7 +837,7 @@ bsi_status launch_c2r_dual(int M, const cplx<T>* work, int Hp, OutT* grid, int n
 
 template <typename T, typename InT, typename OutT>
 bsi_status prefilter_pass(bsi_field* f, const InT* uhat, OutT* grid, cplx<T>* work, int H, int Hp, long sComp,
-                          long wComp, const double* const* ct, const int* a, int st, int quarter,
+                          long wComp, const double* const* ct, const int* a, int quarter,
                           const void* tw0, const void* tw1, const void* tw2, hipStream_t s,
                           const double* dual_tab = nullptr);
 
@@ -712,7 +871,7 @@ bsi_status prefilter_typed(bsi_field* f, const InT* uhat, OutT* grid, hipStream_
         const int a[3] = {0, 0, 0};
         const double* ct[3];
         for (int d = 0; d < 3; ++d) BSI_TRY(get_ctable(ctx, nn[d], f->N, f->desc.prefilter, &ct[d]));
-        return prefilter_pass<T, InT, OutT>(f, uhat, grid, work, H, Hp, sComp, wComp, ct, a, 1, 0, tw0, tw1, tw2,
+        return prefilter_pass<T, InT, OutT>(f, uhat, grid, work, H, Hp, sComp, wComp, ct, a, 0, tw0, tw1, tw2,
                                             s);
     }
     const double* dtab2 = nullptr;
@@ -723,38 +882,37 @@ bsi_status prefilter_typed(bsi_field* f, const InT* uhat, OutT* grid, hipStream_
         for (int d = 0; d < 2; ++d)
             BSI_TRY(get_ctable(ctx, nn[d], f->N, a[d] ? DERIVATIVE_TABLE : BSI_PREFILTER_NONE, &ct[d]));
         BSI_TRY(get_ctable(ctx, n2, f->N, BSI_PREFILTER_NONE, &ct[2]));
-        BSI_TRY((prefilter_pass<T, InT, OutT>(f, uhat, grid, work, H, Hp, sComp, wComp, ct, a, 2,
+        BSI_TRY((prefilter_pass<T, InT, OutT>(f, uhat, grid, work, H, Hp, sComp, wComp, ct, a,
                                               (a[0] + a[1]) & 3, tw0, tw1, tw2, s, dtab2)));
     }
     return BSI_OK;
 }
 
 // The three passes of one inverse FFT: symbol tables ct[d] per axis, the
-// product times i^quarter, written at stride st with offsets a[] (see k_c2r);
-// with dual_tab, pass C writes the Hermite pair of axis-2 orders 0 and 1
-// (k_c2r_dual, dual_tab the axis-2 derivative table).
+// product times i^quarter; with dual_tab, pass C writes the Hermite pair of axis-2
+// orders 0 and 1 at offsets a[0], a[1] (k_c2r_dual, dual_tab the axis-2 derivative
+// table).
 template <typename T, typename InT, typename OutT>
 bsi_status prefilter_pass(bsi_field* f, const InT* uhat, OutT* grid, cplx<T>* work, int H, int Hp, long sComp,
-                          long wComp, const double* const* ct, const int* a, int st, int quarter,
+                          long wComp, const double* const* ct, const int* a, int quarter,
                           const void* tw0, const void* tw1, const void* tw2, hipStream_t s,
                           const double* dual_tab) {
     bsi_ctx* ctx = f->ctx;
     const int n0 = f->n[0], n1 = f->n[1], n2 = f->n[2], C = f->C;
     const double *c0 = ct[0], *c1 = ct[1], *c2 = ct[2];
-    int W = 0;
     // pass A: axis 0 (stride n1*H in, n1*Hp out), other = k1 (stride H in, Hp out)
     {
     StageTimer tm(ctx, "fft_axis0", s);
-    BSI_TRY((launch_axis<T, InT, true>(n0, dim3(1, n1, C), uhat, work, H, long(n1) * H, long(H), sComp,
+    BSI_TRY((launch_axis<T, InT, true>(n0, n1, C, uhat, work, H, long(n1) * H, long(H), sComp,
                                        long(n1) * Hp, long(Hp), wComp, c0, c1, c2,
-                                       static_cast<const cplx<T>*>(tw0), s, &W, quarter)));
+                                       static_cast<const cplx<T>*>(tw0), s, quarter, sizeof(OutT) == 2)));
     }
     // pass B: axis 1 (stride Hp), other = k0 (stride n1*Hp), in place
     {
     StageTimer tm(ctx, "fft_axis1", s);
-    BSI_TRY((launch_axis<T, T, false>(n1, dim3(1, n0, C), reinterpret_cast<const T*>(work), work, H,
+    BSI_TRY((launch_axis<T, T, false>(n1, n0, C, reinterpret_cast<const T*>(work), work, H,
                                       long(Hp), long(n1) * Hp, wComp, long(Hp), long(n1) * Hp, wComp, nullptr,
-                                      nullptr, nullptr, static_cast<const cplx<T>*>(tw1), s, &W)));
+                                      nullptr, nullptr, static_cast<const cplx<T>*>(tw1), s)));
     }
     // pass C: c2r along axis 2
     const int M = n2 / 2;
@@ -769,9 +927,9 @@ bsi_status prefilter_pass(bsi_field* f, const InT* uhat, OutT* grid, cplx<T>* wo
     }
     if (C == 1)
         return launch_c2r<T, OutT, 1>(M, work, Hp, grid, n0, n1, f->P[0], f->P[1], f->P[2], f->pitch2, f->padlo,
-                                      static_cast<const cplx<T>*>(tw2), s, st, a[0], a[1], a[2]);
+                                      static_cast<const cplx<T>*>(tw2), s);
     return launch_c2r<T, OutT, 3>(M, work, Hp, grid, n0, n1, f->P[0], f->P[1], f->P[2], f->pitch2, f->padlo,
-                                  static_cast<const cplx<T>*>(tw2), s, st, a[0], a[1], a[2]);
+                                  static_cast<const cplx<T>*>(tw2), s);
 }
 
 }  // namespace

@@ -10,6 +10,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "device.hpp"
 
 namespace bsi {
 
@@ -92,7 +93,6 @@ __device__ __forceinline__ uint32_t tile_origin(uint32_t key, uint32_t T) {
 
 // 16 bytes as a native vector (loads and stores of it are single instructions,
 // never aggregate copies) and a load of it from global memory.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) u32x4 global_u32x4;
 
@@ -1193,14 +1193,6 @@ __device__ __forceinline__ AT quad_lane(AT v) {
 }
 constexpr int QUAD_XOR1 = 0xb1;  // lanes 1 0 3 2
 constexpr int QUAD_XOR2 = 0x4e;  // lanes 2 3 0 1
-
-// Barrier for LDS only: orders the wavefront's LDS accesses without waiting for
-// outstanding global loads (the next tile's prefetch stays in flight).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // Steps of 64 slots that copy one plane of a block.
 template <typename G>
