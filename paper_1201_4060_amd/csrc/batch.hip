@@ -553,7 +553,7 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     a.binned = base + o_pos;
     a.work = reinterpret_cast<u32x4*>(base + o_work);
     a.desc = b->gbuf.desc;
-    a.ulog = item_units_log2(b->grp.mmax, ITEM_UNITS_BATCH);
+    a.ulog = item_units_log2(b->grp.mmax, ITEM_UNITS_BATCH, Btot);
     a.ctl = reinterpret_cast<uint32_t*>(base + o_ctl);
     a.start = reinterpret_cast<uint32_t*>(base + o_start);
     for (auto& x : hi) {

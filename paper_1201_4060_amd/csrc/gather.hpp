@@ -278,11 +278,13 @@ static __global__ __launch_bounds__(1024) void k_grp_scan(uint32_t* __restrict__
 // 299 us, with 16384 230 / 287, with 32768 254 / 286 -- the next unit's loads
 // are hidden behind four items).  A batch, whose fields differ in what an item
 // costs: 32768 (31 fields of up to 128^3, orders 4 and 6: 119 + 230 us with 8192,
-// 129 + 188 with 32768, 150 + 212 with 65536).
+// 129 + 188 with 32768, 150 + 212 with 65536), but no more units than tiles, or some
+// are empty and taken in vain (9 fields of up to 96^3 with up to 4 * 10^5 particles:
+// 16 units a chunk 102 + 219 us, 8 units 65 + 203).
 constexpr uint32_t ITEM_UNITS = 8192, ITEM_UNITS_BATCH = 32768;
-inline uint32_t item_units_log2(uint32_t chunks, uint32_t target) {
+inline uint32_t item_units_log2(uint32_t chunks, uint32_t target, uint64_t most = ~uint64_t(0)) {
     uint32_t l = 3;
-    while (l < 6 && (uint64_t(chunks) << l) < target) ++l;
+    while (l < 6 && (uint64_t(chunks) << l) < target && (uint64_t(chunks) << (l + 1)) <= most) ++l;
     return l;
 }
 // The chunks are split into ITEM_RANGES contiguous ranges, one per XCD
