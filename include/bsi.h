@@ -95,7 +95,7 @@ typedef struct bsi_field_desc {
 
 /* Evaluation tuning knobs (results never depend on them). */
 typedef struct bsi_eval_config {
-    int32_t sort_tile;   /* cells per Morton tile edge for particle binning; 0 = no binning */
+    int32_t sort_tile;   /* cells per tile edge for particle binning; 0 = no binning */
     int32_t block;       /* threads per workgroup of the gather kernel (64..1024, multiple of 64) */
     int32_t xcd_remap;   /* 1 = map consecutive binned particle blocks onto one XCD (tiled
                             gather: each XCD's workgroups start on their own range of tiles)   */
@@ -199,7 +199,7 @@ bsi_status bsi_eval_ex(bsi_field* field, const double* pos_dev, int64_t P,
  * The call allocates nothing and creates no events (the context's stage
  * timing does not record it).  BSI_E_INVAL, with the bytes needed in
  * bsi_last_error(), when the call's workspace (about 70 bytes per particle
- * plus 8 per Morton tile of the field, for binned configurations) exceeds the
+ * plus 8 per tile of the field, for binned configurations) exceeds the
  * array; use fewer particles per call or bsi_eval_ex then.  Every call on a
  * GPU shares that GPU's array: calls that overlap on one GPU (other streams or
  * host threads) race and must not be issued; consecutive calls on one stream
@@ -289,7 +289,7 @@ typedef struct bsi_batch bsi_batch;
 
 /* (Items must be B-spline fields of orders 4 and 6; BSI_E_UNSUPPORTED otherwise.)
  * Plan the evaluation of `count` items (1..65535) as one unit of work: every
- * item's particles are binned by the Morton tile of its own sort granularity
+ * item's particles are binned by the tile of its own sort granularity
  * (one set of binning launches for all items), and per (order, components)
  * class present one persistent kernel walks the class's non-empty tiles of the
  * items gathered from LDS tiles (8^3 cells) and one kernel takes the class's

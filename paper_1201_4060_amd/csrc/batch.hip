@@ -5,7 +5,7 @@
 // with the same configuration.
 //
 // Plan (host, at creation): items are laid end to end in one particle index
-// space and one bucket index space.  Each item is binned by the Morton tile of
+// space and one bucket index space.  Each item is binned by the tile of
 // its own sort granularity; the tuned (or given) configuration decides per
 // item whether its particles are gathered tile by tile from LDS (tiles of 8^3
 // cells) or one lane per particle from global memory.

@@ -164,7 +164,7 @@ constexpr int tiled_waves() {
 }
 
 // LDS-tiled variant: persistent workgroups of B threads evaluate work items
-// (pieces of Morton tiles of T^3 cells, k_grp_fine), with xcd_remap those of the
+// (pieces of tiles of T^3 cells, k_grp_fine), with xcd_remap those of the
 // range blockIdx % ITEM_RANGES first (workgroups are dispatched to the XCDs in
 // turn).
 template <int N, typename CT, int C, bool GRAD, int T, int B>

@@ -5,7 +5,7 @@
 // (Section 3) the mixed derivative d2/dx_i dx_j takes the first-derivative
 // weights on axes i and j, and d2/dx_i^2 the second-derivative weights on
 // axis i; every factor carries the chain factor n/L of its axis.  The
-// particles are binned as for the evaluation (Morton tiles of 8^3 cells) and
+// particles are binned as for the evaluation (tiles of 8^3 cells) and
 // gathered from an LDS copy of each tile's block of the grid (or, for classes
 // without a tiled body, one lane per particle straight from the grid), the
 // contraction reducing axis 2 first, then axis 1, then axis 0 (the Table 1
@@ -444,7 +444,7 @@ bsi_status hessian_run(bsi_field* f, const double* pos, int64_t P, void* u, void
     BSI_CHECK(f->basis == BSI_BASIS_BSPLINE && (f->N == 4 || f->N == 6), BSI_E_UNSUPPORTED,
               "second derivatives are implemented for B-spline fields of orders 4 and 6");
     if (P == 0) return BSI_OK;
-    // binned by Morton tiles of 8 cells (at least n/256, so that the bucket
+    // binned by tiles of 8 cells (at least n/256, so that the bucket
     // table has at most 2^24 entries), for locality of the stencil reads
     const int nmax = std::max(f->n[0], std::max(f->n[1], f->n[2]));
     const int tile = std::max(8, (nmax + 255) / 256);
