@@ -20,15 +20,24 @@
 #include "common.hpp"
 #include "device.hpp"
 
+// No product is fused into a sum but where fused() says so: left to the compiler,
+// instances of different lengths and types fuse differently, and a transform's last
+// bits (and with them the BF16 rounding of its FP32 result) would depend on which
+// instance ran.
+#pragma clang fp contract(off)
+
 namespace bsi {
 
 template <typename T>
 __device__ __forceinline__ cplx<T> cadd(cplx<T> a, cplx<T> b) { return {a.x + b.x, a.y + b.y}; }
 template <typename T>
 __device__ __forceinline__ cplx<T> csub(cplx<T> a, cplx<T> b) { return {a.x - b.x, a.y - b.y}; }
+// a times the twiddle b.  Of the two products of the imaginary part the first is
+// rounded before the sum and the second is not; turned: the other way round (turned()
+// below; in pass C for axes of 32 points).
 template <typename T>
-__device__ __forceinline__ cplx<T> cmul(cplx<T> a, cplx<T> b) {
-    return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+__device__ __forceinline__ cplx<T> cmul(cplx<T> a, cplx<T> b, bool turned = false) {
+    return {fused(a.x, b.x, -(a.y * b.y)), turned ? fused(a.x, b.y, a.y * b.x) : fused(a.y, b.x, a.x * b.y)};
 }
 template <typename T>
 __device__ __forceinline__ cplx<T> cmul_i(cplx<T> a) { return {-a.y, a.x}; }  // i * a
@@ -45,11 +54,10 @@ __device__ __forceinline__ void dft3(cplx<T>* v) {
     const T h = T(0.86602540378443864676372317075294);  // sin(2 pi / 3)
     cplx<T> s = cadd(v[1], v[2]);
     cplx<T> d = csub(v[1], v[2]);
-    cplx<T> m = {v[0].x - T(0.5) * s.x, v[0].y - T(0.5) * s.y};
-    cplx<T> r = {-h * d.y, h * d.x};  // i * h * (v1 - v2)
+    cplx<T> m = {fused(T(-0.5), s.x, v[0].x), fused(T(-0.5), s.y, v[0].y)};
     v[0] = cadd(v[0], s);
-    v[1] = cadd(m, r);
-    v[2] = csub(m, r);
+    v[1] = {fused(-h, d.y, m.x), fused(h, d.x, m.y)};  // m + i h d
+    v[2] = {fused(h, d.y, m.x), fused(-h, d.x, m.y)};
 }
 template <typename T>
 __device__ __forceinline__ void dft4(cplx<T>* v) {
@@ -67,13 +75,18 @@ __device__ __forceinline__ void dft8(cplx<T>* v) {
     cplx<T> o[4] = {v[1], v[3], v[5], v[7]};
     dft4(e);
     dft4(o);
-    o[1] = {r2 * (o[1].x - o[1].y), r2 * (o[1].x + o[1].y)};    // * e^{+i pi/4}
-    o[2] = cmul_i(o[2]);                                         // * e^{+i pi/2}
-    o[3] = {-r2 * (o[3].x + o[3].y), r2 * (o[3].x - o[3].y)};   // * e^{+3i pi/4}
+    o[1] = {o[1].x - o[1].y, o[1].x + o[1].y};   // r2 o1 = o1 e^{+i pi/4}
+    o[2] = cmul_i(o[2]);                         // o2 e^{+i pi/2}
+    o[3] = {-(o[3].x + o[3].y), o[3].x - o[3].y};  // r2 o3 = o3 e^{+3i pi/4}
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        v[q] = cadd(e[q], o[q]);
-        v[q + 4] = csub(e[q], o[q]);
+        if (q & 1) {
+            v[q] = {fused(r2, o[q].x, e[q].x), fused(r2, o[q].y, e[q].y)};
+            v[q + 4] = {fused(-r2, o[q].x, e[q].x), fused(-r2, o[q].y, e[q].y)};
+        } else {
+            v[q] = cadd(e[q], o[q]);
+            v[q + 4] = csub(e[q], o[q]);
+        }
     }
 }
 template <typename T, int R>
@@ -123,7 +136,7 @@ __device__ __forceinline__ void fft_stages(cplx<T>* buf, const cplx<T>* tw, int 
                 for (int r = 0; r < R; ++r) v[q][r] = buf[spread<T>(j + r * NB)];
                 if constexpr (NS > 1) {
 #pragma unroll
-                    for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], tw[r * k * TSTEP * TWS]);
+                    for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], tw[r * k * TSTEP * TWS], LEN == 16);
                 }
                 dft<T, R>(v[q]);
             }
@@ -178,19 +191,33 @@ struct StridedCfg {
     static constexpr int WAVES = THREADS < 512 ? 1 : KB == 80 ? 4 : 2;
 };
 
-// Keeps a stage's values as they were rounded: without it the multiplications that
-// form them may be fused into the next stage's additions, in some instances and not
-// in others, and the transform's last bits would depend on its length and axis.
-template <typename T>
-__device__ __forceinline__ void pin(cplx<T>& x) {
-    asm("" : "+v"(x.x), "+v"(x.y));
+// The butterflies [lo, hi) of the stage after transforms of length ns whose twiddle
+// products are turned (cmul).  Either way is as exact.  But a last bit that differs
+// here rounds one value in 10^4 of a BF16 grid to its other neighbour, which the
+// interpolated values show (5e-5 of their norm at 1024^3), so the ways are part of
+// the result and are kept as stored grids have them: turned where a thread's
+// butterfly, of those `team` apart, meets an earlier one's twiddles again, `team`
+// being another number of threads than the present one in three passes; none in the
+// last column of the half spectrum where n2/2 is a multiple of 32 (k_fft_axis:
+// ALONE; that column is then a block of its own).
+struct Turned {
+    int lo, hi;
+};
+template <typename T, int LEN, int TEAM, bool FIRST>
+constexpr Turned turned(int ns) {
+    constexpr bool dbl = sizeof(T) == 8;
+    if (LEN % 3 == 0) return {0, 0};
+    if (FIRST && !dbl && LEN == 1024) return ns == 8 ? Turned{32, 128} : ns == 64 ? Turned{64, 96} : Turned{0, 0};
+    const int team = FIRST && !dbl && LEN == 512 ? 16 : !FIRST && dbl && LEN == 1024 ? 256 : TEAM;
+    return {ns > team ? ns : team, LEN};
 }
 
 // The thread's butterflies of the stage that follows transforms of length NS, in
 // place: butterfly m is v[m + r BPT], r < R.
-template <typename T, int LEN, int TEAM, int R, int NS>
-__device__ __forceinline__ void butterflies(cplx<T>* v, const cplx<T>* tw, int a0) {
+template <typename T, int LEN, int TEAM, bool FIRST, int R, int NS>
+__device__ __forceinline__ void butterflies(cplx<T>* v, const cplx<T>* tw, int a0, bool last) {
     constexpr int BPT = LEN / R / TEAM;
+    constexpr Turned U = turned<T, LEN, TEAM, FIRST>(NS);
     static_assert(BPT * R * TEAM == LEN, "whole butterflies per thread");
 #pragma unroll
     for (int m = 0; m < BPT; ++m) {
@@ -199,8 +226,14 @@ __device__ __forceinline__ void butterflies(cplx<T>* v, const cplx<T>* tw, int a
         for (int r = 0; r < R; ++r) x[r] = v[m + r * BPT];
         if constexpr (NS > 1) {
             const int k = (a0 + m * TEAM) % NS * (LEN / (NS * R));
+            bool turn = m * TEAM + TEAM > U.lo && m * TEAM < U.hi;
+            if (turn && (m * TEAM < U.lo || m * TEAM + TEAM > U.hi)) {
+                // a wavefront's rows (8 at most, lo and hi being multiples of 16) are on one side
+                const int j = __builtin_amdgcn_readfirstlane(a0) + m * TEAM;
+                turn = j >= U.lo && j < U.hi;
+            }
 #pragma unroll
-            for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw[r * k]);
+            for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw[r * k], turn && !last);
         }
         dft<T, R>(x);
 #pragma unroll
@@ -213,12 +246,12 @@ __device__ __forceinline__ void butterflies(cplx<T>* v, const cplx<T>* tw, int a
 // NS + r NS: in this thread when TEAM divides NS, otherwise it changes hands through
 // LDS.  Adjacent lanes hold adjacent lines there (LP apart, odd), whatever the
 // stage's stride: no two of 32 meet in a bank.
-template <typename T, int LEN, int TEAM, int NS>
-__device__ __forceinline__ void line_stages(cplx<T>* v, cplx<T>* line, const cplx<T>* tw, int a0) {
+template <typename T, int LEN, int TEAM, bool FIRST, int NS>
+__device__ __forceinline__ void line_stages(cplx<T>* v, cplx<T>* line, const cplx<T>* tw, int a0, bool last) {
     if constexpr (NS < LEN) {
         constexpr int R = Radix<LEN / NS>::value;
         constexpr int BPT = LEN / R / TEAM, PER = LEN / TEAM;
-        butterflies<T, LEN, TEAM, R, NS>(v, tw, a0);
+        butterflies<T, LEN, TEAM, FIRST, R, NS>(v, tw, a0, last);
         if constexpr (NS * R == LEN) {
             // rows j + r LEN / R: as they are
         } else if constexpr (NS % TEAM == 0) {
@@ -230,10 +263,7 @@ __device__ __forceinline__ void line_stages(cplx<T>* v, cplx<T>* line, const cpl
                 for (int r = 0; r < R; ++r) u[m / S * (S * R) + m % S + r * S] = v[m + r * BPT];
             }
 #pragma unroll
-            for (int q = 0; q < PER; ++q) {
-                v[q] = u[q];
-                pin(v[q]);
-            }
+            for (int q = 0; q < PER; ++q) v[q] = u[q];
         } else {
             if constexpr (NS > 1) lds_barrier();   // the last exchange is read
 #pragma unroll
@@ -247,7 +277,7 @@ __device__ __forceinline__ void line_stages(cplx<T>* v, cplx<T>* line, const cpl
 #pragma unroll
             for (int q = 0; q < PER; ++q) v[q] = line[a0 + q * TEAM];
         }
-        line_stages<T, LEN, TEAM, NS * R>(v, line, tw, a0);
+        line_stages<T, LEN, TEAM, FIRST, NS * R>(v, line, tw, a0, last);
     }
 }
 
@@ -327,7 +357,6 @@ k_fft_axis(AxisArgs<T> g) {
             const double x = g.quarter == 0 ? a : g.quarter == 1 ? -b : g.quarter == 2 ? -a : b;
             const double y = g.quarter == 0 ? b : g.quarter == 1 ? a : g.quarter == 2 ? -b : -a;
             v[q] = {T(x), T(y)};
-            pin(v[q]);
         }
     } else {
         const cplx<T>* src = static_cast<const cplx<T>*>(g.in);
@@ -336,91 +365,12 @@ k_fft_axis(AxisArgs<T> g) {
     }
     for (int i = tid; i < LEN; i += Cfg::THREADS) tw[i] = g.twg[i];
     cplx<T>* line = lines + w * Cfg::LP;
-    line_stages<T, LEN, TEAM, 1>(v, line, tw, a0);   // (tw is read after its first barrier)
+    constexpr int ALONE = LEN < 1024 ? 32 : sizeof(T) == 4 ? 16 : 8;
+    const bool last = FIRST && LEN >= 256 && k2_0 > 0 && k2_0 == g.H - 1 && k2_0 % ALONE == 0;
+    line_stages<T, LEN, TEAM, FIRST, 1>(v, line, tw, a0, last);   // (tw is read after its first barrier)
     if (valid) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) g.out[olane_base + q * ostep] = v[q];
-    }
-}
-
-// The first pass with its lines in LDS through all stages (fft_stages), for BF16 grids
-// with 512 or 1024 points along axis 0: the compiler fuses the multiplications of
-// these two instances otherwise than k_fft_axis's, and a last bit that differs here
-// rounds grid values to another BF16 value (one in 10^4, which the interpolated
-// values show).  1024^3 from complex64: 3667 us, k_fft_axis 2600; 512^3 x 3: 1137 +
-// 52, 1056.  Columns [k2_begin, k2_end); NARROW: few lines per workgroup, for the
-// column k2 = n2/2 left over when n2/2 is a multiple of the wide blocks' width.
-template <typename T, int LEN, bool NARROW>
-struct LdsCfg {
-    static constexpr int KB = NARROW ? 8 : 150;
-    static constexpr int bytes = int(sizeof(cplx<T>));
-    static constexpr int raw = (KB * 1024 - LEN * bytes) / ((LEN + 1) * bytes);
-    static constexpr int W = raw >= 32 ? 32 : raw >= 16 ? 16 : raw >= 8 ? 8 : raw >= 4 ? 4 : 2;
-    static constexpr int TEAM = 512 / W;
-    static constexpr int THREADS = W * TEAM;
-};
-template <typename T, typename InT, int LEN, bool NARROW>
-__global__ __launch_bounds__(512) void k_fft_first_lds(const InT* in, cplx<T>* out, int k2_begin,
-                                                  int k2_end,
-                                                  long sAxis, long sOther, long sComp, long oAxis, long oOther,
-                                                  long oComp, const double* cAxis,
-                                                  const double* cOther, const double* c2,
-                                                  const cplx<T>* twg, int quarter) {
-    using Cfg = LdsCfg<T, LEN, NARROW>;
-    constexpr int W = Cfg::W;
-    constexpr int LP = LEN + 1;
-    __shared__ cplx<T> lines[W * LP];
-    __shared__ cplx<T> tw[LEN];
-    const int tid = threadIdx.x;
-    const int bx = blockIdx.x, other = blockIdx.y, bz = blockIdx.z;
-    const int k2_0 = k2_begin + bx * W;
-    const long base = long(bz) * sComp + long(other) * sOther + k2_0;
-    const long obase = long(bz) * oComp + long(other) * oOther + k2_0;
-
-    for (int i = tid; i < LEN; i += Cfg::THREADS) tw[i] = twg[i];
-    // Thread tid always handles line w = tid % W; it moves PER elements of that
-    // line (rows a = q * RSTEP + tid / W), all loads issued before any store.
-    constexpr int RSTEP = Cfg::TEAM;
-    constexpr int PER = LEN / RSTEP;
-    static_assert(LEN % RSTEP == 0, "line length must be a multiple of the row step");
-    const int w = tid % W;
-    const int a0 = tid / W;
-    const bool valid = k2_0 + w < k2_end;
-    const long lane_base = base + (valid ? w : 0) + long(a0) * sAxis;
-    const long step = long(RSTEP) * sAxis;
-    const long olane_base = obase + (valid ? w : 0) + long(a0) * oAxis;
-    const long ostep = long(RSTEP) * oAxis;
-    cplx<T> v[PER];
-    {
-        const double cw = (valid ? c2[k2_0 + w] : 0.0);
-        const double cO = cOther[other];
-        double re[PER], im[PER], ca[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const long e = lane_base + q * step;
-            re[q] = double(in[2 * e]);
-            im[q] = double(in[2 * e + 1]);
-            ca[q] = cAxis[q * RSTEP + a0];
-        }
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const double m = (ca[q] * cO) * cw;
-            const double a = re[q] * m, b = im[q] * m;
-            // times i^quarter (the i's of derivative factors; 0 otherwise)
-            const double x = quarter == 0 ? a : quarter == 1 ? -b : quarter == 2 ? -a : b;
-            const double y = quarter == 0 ? b : quarter == 1 ? a : quarter == 2 ? -b : -a;
-            v[q] = {T(x), T(y)};
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < PER; ++q) lines[w * LP + q * RSTEP + a0] = v[q];
-    lds_barrier();
-    fft_stages<T, LEN, Cfg::TEAM, 1, 1>(lines + (tid / Cfg::TEAM) * LP, tw, tid % Cfg::TEAM);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) v[q] = lines[w * LP + q * RSTEP + a0];
-    if (valid) {
-#pragma unroll
-        for (int q = 0; q < PER; ++q) out[olane_base + q * ostep] = v[q];
     }
 }
 
@@ -515,9 +465,9 @@ __device__ __forceinline__ void c2r_twist(cplx<T>* zb, const cplx<T>* tw) {
             const int kk = M - k;
             const cplx<T> A = X[spread<T>(k)], B = X[spread<T>(kk)];
             const cplx<T> Bc = {B.x, -B.y}, Ac = {A.x, -A.y};
-            const cplx<T> z1 = cadd(cadd(A, Bc), cmul_i(cmul(tw[k], csub(A, Bc))));
+            const cplx<T> z1 = cadd(cadd(A, Bc), cmul_i(cmul(csub(A, Bc), tw[k])));
             if (k < kk) {
-                const cplx<T> z2 = cadd(cadd(B, Ac), cmul_i(cmul(tw[kk], csub(B, Ac))));
+                const cplx<T> z2 = cadd(cadd(B, Ac), cmul_i(cmul(csub(B, Ac), tw[kk])));
                 X[spread<T>(kk)] = z2;
             }
             X[spread<T>(k)] = z1;
@@ -697,34 +647,10 @@ __global__ void k_to_dense(const O* __restrict__ grid, double* __restrict__ dens
 
 namespace {
 
-template <typename InT, int LEN>
-void launch_first_lds(int others, int C, const InT* in, cplx<float>* out, int H, long sAxis, long sOther, long sComp,
-                      long oAxis, long oOther, long oComp, const double* cAxis, const double* cOther,
-                      const double* c2, const cplx<float>* tw, hipStream_t s, int quarter) {
-    using Cfg = LdsCfg<float, LEN, false>;
-    using CfgN = LdsCfg<float, LEN, true>;
-    const int full = H - 1 >= Cfg::W && (H - 1) % Cfg::W == 0 ? H - 1 : H;
-    const unsigned gx = unsigned((full + Cfg::W - 1) / Cfg::W);
-    hipLaunchKernelGGL((k_fft_first_lds<float, InT, LEN, false>), dim3(gx, others, C), dim3(Cfg::THREADS), 0, s, in,
-                       out, 0, full, sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, quarter);
-    if (full < H)
-        hipLaunchKernelGGL((k_fft_first_lds<float, InT, LEN, true>), dim3(1, others, C), dim3(CfgN::THREADS), 0, s, in,
-                           out, full, H, sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, quarter);
-}
-
 template <typename T, typename InT, bool FIRST>
 bsi_status launch_axis(int len, int others, int C, const InT* in, cplx<T>* out, int H, long sAxis, long sOther,
                        long sComp, long oAxis, long oOther, long oComp, const double* cAxis,
-                       const double* cOther, const double* c2, const cplx<T>* tw, hipStream_t s, int quarter = 0,
-                       bool bf16 = false) {
-    if constexpr (FIRST && sizeof(T) == 4) {
-        if (bf16 && (len == 512 || len == 1024)) {
-            (len == 512 ? launch_first_lds<InT, 512> : launch_first_lds<InT, 1024>)(
-                others, C, in, out, H, sAxis, sOther, sComp, oAxis, oOther, oComp, cAxis, cOther, c2, tw, s, quarter);
-            BSI_HIP(hipGetLastError());
-            return BSI_OK;
-        }
-    }
+                       const double* cOther, const double* c2, const cplx<T>* tw, hipStream_t s, int quarter = 0) {
 #define BSI_AXIS_CASE(L)                                                                           \
     case L: {                                                                                      \
         using Cfg = StridedCfg<T, L>;                                                              \
@@ -905,7 +831,7 @@ bsi_status prefilter_pass(bsi_field* f, const InT* uhat, OutT* grid, cplx<T>* wo
     StageTimer tm(ctx, "fft_axis0", s);
     BSI_TRY((launch_axis<T, InT, true>(n0, n1, C, uhat, work, H, long(n1) * H, long(H), sComp,
                                        long(n1) * Hp, long(Hp), wComp, c0, c1, c2,
-                                       static_cast<const cplx<T>*>(tw0), s, quarter, sizeof(OutT) == 2)));
+                                       static_cast<const cplx<T>*>(tw0), s, quarter)));
     }
     // pass B: axis 1 (stride Hp), other = k0 (stride n1*Hp), in place
     {

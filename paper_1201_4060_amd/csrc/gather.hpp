@@ -675,12 +675,6 @@ __device__ __forceinline__ AT widen(CT v) {
     else return AT(v);
 }
 
-// a * b + c with one rounding, written out where the compiler would otherwise
-// fuse in one kernel and not in another (products that two methods' weights have
-// in common are moved out of the branch between them).
-__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
 // w_j(t) = sum_i M[j][i] t^i and w'_j(t) = sum_i M1[j][i] t^i (Horner), with
 // the matrices of a compile-time table (M from the Section 7 general formula
 // for the B-spline).

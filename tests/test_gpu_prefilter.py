@@ -132,3 +132,21 @@ def test_prefilter_bf16_is_rne_of_f32(ctx):
         g32 = host(f32.get_coefficients())
         gb = host(fb.get_coefficients())
     assert np.array_equal(gb, bf16_round(g32))
+
+
+@pytest.mark.parametrize("inprec", ["c128", "c64"])
+@pytest.mark.parametrize("shape", [(384, 16, 16), (512, 16, 16), (768, 16, 16), (1024, 16, 16), (16, 512, 16),
+                                   (16, 1024, 16), (16, 16, 512), (16, 16, 1024)])
+def test_prefilter_bf16_is_rne_of_f32_long_axes(ctx, shape, inprec):
+    # the longest transforms along each axis: the same FP32 arithmetic whatever the storage type
+    import paper_1201_4060_amd as bsi
+    from gpu_common import bf16_round
+    C, N = 1, 6
+    uhat = _random_spectrum(shape, C, np.random.default_rng(sum(shape)))
+    uhat = dev(uhat.astype(np.complex64) if inprec == "c64" else uhat)
+    with bsi.Field(ctx, shape, C, N, bsi.BSI_F32) as f32, bsi.Field(ctx, shape, C, N, bsi.BSI_BF16) as fb:
+        f32.set_spectrum(uhat)
+        fb.set_spectrum(uhat)
+        g32 = host(f32.get_coefficients())
+        gb = host(fb.get_coefficients())
+    assert np.array_equal(gb, bf16_round(g32))
