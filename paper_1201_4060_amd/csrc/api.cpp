@@ -447,7 +447,7 @@ bsi_status bsi_eval_plan_create(bsi_field* f, int64_t max_particles, const bsi_e
     pl->f = f;
     pl->cfg = c;
     pl->cap = max_particles;
-    pl->ws_bytes = max_particles > 0 ? eval_ws_bytes(f, max_particles, c) : 0;
+    pl->ws_bytes = eval_ws_capacity(f, max_particles, c);
     if (pl->ws_bytes && hipMalloc(&pl->ws, pl->ws_bytes) != hipSuccess) {
         (void)hipGetLastError();
         delete pl;

@@ -265,6 +265,8 @@ bsi_status eval_run(bsi_field* f, const double* pos, int64_t P, void* u, void* g
 // eval_bin_ws (positions only: binning and work items) then eval_gather_ws
 // (the gather from that binning and the field's current grid)
 size_t eval_ws_bytes(const bsi_field* f, int64_t P, const bsi_eval_config& cfg);
+// a workspace that serves every count up to P
+size_t eval_ws_capacity(const bsi_field* f, int64_t P, const bsi_eval_config& cfg);
 bsi_status eval_check_config(const bsi_eval_config& cfg);
 bsi_status eval_run_ws(bsi_field* f, const double* pos, int64_t P, void* u, void* grad,
                        const bsi_eval_config& cfg, hipStream_t s, void* ws);

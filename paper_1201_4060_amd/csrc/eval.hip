@@ -501,6 +501,20 @@ size_t eval_ws_bytes(const bsi_field* f, int64_t P, const bsi_eval_config& cfg) 
     return bin_layout(f, P, tile, item_chunk(f, tile, cfg)).bytes;
 }
 
+// The most that any P' <= P takes.  A coarse range holds twice the keys for particle
+// counts below a step of grp_shift, and more items are reserved for its chunks, so
+// fewer particles can take a little more; between two steps every part of the
+// workspace grows with P', so the counts just below the steps and P itself tell.
+size_t eval_ws_capacity(const bsi_field* f, int64_t P, const bsi_eval_config& cfg) {
+    const int tile = effective_tile(f, cfg);
+    if (tile == 0 || P == 0) return 0;
+    size_t most = eval_ws_bytes(f, P, cfg);
+    const uint64_t nb = bin_key_count(f, tile) + 1;
+    for (int s = grp_shift(nb, P) + 1; s <= grp_shift(nb, 1); ++s)
+        most = std::max(most, eval_ws_bytes(f, std::min(P, grp_shift_end(nb, s)), cfg));
+    return most;
+}
+
 bsi_status eval_check_config(const bsi_eval_config& cfg) {
     const int block = cfg.block > 0 ? cfg.block : 256;
     BSI_CHECK(block % 64 == 0 && block >= 64 && block <= 256, BSI_E_INVAL,

@@ -559,6 +559,12 @@ inline int grp_shift(uint64_t nb, long P, uint64_t target = GRP_TARGET) {
     return s;
 }
 
+// The most particles (of evenly spread ones) that grp_shift gives a shift of at least
+// s > 0: one fewer than make s - 1 few enough ranges.
+inline int64_t grp_shift_end(uint64_t nb, int s, uint64_t target = GRP_TARGET) {
+    return int64_t(((nb + (uint64_t(1) << (s - 1)) - 1) >> (s - 1)) * target) - 1;
+}
+
 // Host-side plan of a grouping of `nidx` slots (nvalid of them particles)
 // over the keys [0, nbuckets) in `ncoarse` coarse ranges.
 struct GrpPlan {

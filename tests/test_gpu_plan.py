@@ -128,3 +128,23 @@ def test_plan_errors(ctx):
             assert np.isfinite(host(u)).all()
         with pytest.raises(bsi.BsiError):
             _bsi.bsi_eval_plan_create(f.handle, -1)
+
+
+@pytest.mark.parametrize("n,cap,least,given", [
+    (64, 2560, 2500, True), (128, 8704, 8300, True), (128, 33280, 33000, False), (256, 66048, 64000, True),
+    (256, 131584, 130400, True)])
+def test_plan_bins_every_count_up_to_its_capacity(ctx, n, cap, least, given):
+    # the binning's key ranges widen at certain counts: fewer particles can need more workspace
+    import paper_1201_4060_amd as bsi
+    c = bsi.EvalConfig(sort_tile=8, block=256, xcd_remap=1, variant=0) if given else None
+    pos = dev(synth.uniform_positions(cap, seed=720 + n))
+    uhat = synth.kolmogorov_spectrum(n, 1, seed=721)
+    with bsi.Field(ctx, n, 1, 6, bsi.BSI_F32) as f:
+        f.set_spectrum(dev(uhat))
+        with bsi.EvalPlan(f, cap, c) as pl:
+            for P in sorted({least, *range(least, cap, 97), cap - 2, cap - 1, cap}):
+                pl.bin(pos[:P])
+            pl.bin(pos[:cap - 1])
+            u, g = pl.run()
+            u0, g0 = f.eval(pos[:cap - 1], cfg=c)
+            assert _same(u, u0) and _same(g, g0)
