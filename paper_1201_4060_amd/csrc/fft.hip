@@ -367,7 +367,10 @@ k_fft_axis(AxisArgs<T> g) {
     cplx<T>* line = lines + w * Cfg::LP;
     constexpr int ALONE = LEN < 1024 ? 32 : sizeof(T) == 4 ? 16 : 8;
     const bool last = FIRST && LEN >= 256 && k2_0 > 0 && k2_0 == g.H - 1 && k2_0 % ALONE == 0;
-    line_stages<T, LEN, TEAM, FIRST, 1>(v, line, tw, a0, last);   // (tw is read after its first barrier)
+    // tw is read after the barrier of the stages' first exchange; a line on one thread
+    // (12 and 24 points) exchanges nothing
+    if constexpr (TEAM == 1) lds_barrier();
+    line_stages<T, LEN, TEAM, FIRST, 1>(v, line, tw, a0, last);
     if (valid) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) g.out[olane_base + q * ostep] = v[q];

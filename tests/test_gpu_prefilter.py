@@ -150,3 +150,16 @@ def test_prefilter_bf16_is_rne_of_f32_long_axes(ctx, shape, inprec):
         g32 = host(f32.get_coefficients())
         gb = host(fb.get_coefficients())
     assert np.array_equal(gb, bf16_round(g32))
+
+
+@pytest.mark.parametrize("coef", ["f32", "f64"])
+@pytest.mark.parametrize("shape", [(12, 24, 64), (24, 12, 64), (24, 24, 16), (12, 12, 12)])
+def test_prefilter_lines_on_one_thread(ctx, shape, coef):
+    # 12 and 24 points along axes 0 and 1: nothing changes hands, only the twiddles go through LDS
+    import paper_1201_4060_amd as bsi
+    from oracle import prefilter
+    uhat = _random_spectrum(shape, 3, np.random.default_rng(shape[0]))
+    with bsi.Field(ctx, shape, 3, 4, bsi.BSI_F32 if coef == "f32" else bsi.BSI_F64) as f:
+        f.set_spectrum(dev(uhat))
+        got = host(f.get_coefficients())
+    assert _rel(got, prefilter(uhat, 4)) < (2e-6 if coef == "f32" else TOL_F64)
