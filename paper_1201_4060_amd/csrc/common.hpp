@@ -275,8 +275,10 @@ bsi_status eval_bin_ws(bsi_field* f, const double* pos, int64_t P, const bsi_eva
 bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, void* grad,
                           const bsi_eval_config& cfg, hipStream_t s, void* ws);
 bsi_status lookup_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out);
-// the configuration of one evaluation by itself (same results, tune.hip)
-bsi_status one_shot_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out);
+// the configuration of one evaluation by itself (same results, tune.hip); looked_up =
+// lookup_config's, from the same look at the table: *out never needs more workspace
+bsi_status one_shot_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out,
+                           bsi_eval_config* looked_up = nullptr);
 bsi_status check_device_ptr_ex(const void* p, const char* what);
 bsi_status debug_cells_run(bsi_field* f, const double* pos, int64_t P, int32_t* cell, double* t,
                            hipStream_t s);

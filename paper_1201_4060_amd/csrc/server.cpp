@@ -383,8 +383,7 @@ bsi_status bsi_server_submit(bsi_server* sv, int32_t field_id, const double* pos
         BSI_CHECK(it != sv->fields.end(), BSI_E_INVAL, "unknown field id " + std::to_string(field_id));
         r.field = it->second;
     }
-    BSI_TRY(lookup_config(sv->ctx, r.field, P, &r.cfg));
-    BSI_TRY(one_shot_config(sv->ctx, r.field, P, &r.run));
+    BSI_TRY(one_shot_config(sv->ctx, r.field, P, &r.run, &r.cfg));
     r.pos = pos_host;
     r.P = P;
     r.u = u_host;

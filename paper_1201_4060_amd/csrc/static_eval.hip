@@ -56,9 +56,10 @@ extern "C" bsi_status bsi_eval_static(bsi_field* f, const double* pos, int64_t P
     BSI_TRY(check_device_ptr_ex(pos, "pos"));
     BSI_TRY(check_device_ptr_ex(u, "u"));
     if (grad) BSI_TRY(check_device_ptr_ex(grad, "grad"));
-    bsi_eval_config c{};
-    if (cfg) c = *cfg;
-    else BSI_TRY(lookup_config(f->ctx, f, P, &c));
+    // the limit is that of the looked-up configuration; the one that runs needs no more
+    bsi_eval_config c{}, run{};
+    if (cfg) c = run = *cfg;
+    else BSI_TRY(one_shot_config(f->ctx, f, P, &run, &c));
     BSI_CHECK(c.sort_tile >= 0 && c.sort_tile <= 1024, BSI_E_INVAL, "sort_tile out of range");
     const size_t need = eval_ws_bytes(f, P, c);
     BSI_CHECK(need <= STATIC_SCRATCH_BYTES, BSI_E_INVAL,
@@ -70,8 +71,6 @@ extern "C" bsi_status bsi_eval_static(bsi_field* f, const double* pos, int64_t P
     BSI_HIP(hipSetDevice(f->ctx->device));
     hipStream_t s = pick_stream(f->ctx, stream);
     f->last_stream = s;
-    // (the limit above is that of the looked-up configuration; this one needs no more)
-    if (!cfg) BSI_TRY(one_shot_config(f->ctx, f, P, &c));
     UntimedScope untimed;  // stage timing would create events
-    return eval_run_ws(f, pos, P, u, grad, c, s, need ? ws : nullptr);
+    return eval_run_ws(f, pos, P, u, grad, run, s, need ? ws : nullptr);
 }

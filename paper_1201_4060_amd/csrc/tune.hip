@@ -133,9 +133,12 @@ bsi_status lookup_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_c
 //   64^3 FP64 order 6:     2 * 10^4  48 / 56 / 64,  4 * 10^4  81 / 63 / 73
 // So: no binning up to 48 Ki particles (half for the largest FP64 stencils), nor for
 // a grid that fits an XCD's L2 up to 2^28 stencil values; no tiles below 3 * 2^25.
-bsi_status one_shot_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out) {
-    if (tuned_config(ctx, f, P, out)) return BSI_OK;
-    *out = default_config(f, P);
+bsi_status one_shot_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out,
+                           bsi_eval_config* looked_up) {
+    const bool tuned = tuned_config(ctx, f, P, out);
+    if (!tuned) *out = default_config(f, P);
+    if (looked_up) *looked_up = *out;
+    if (tuned) return BSI_OK;
     const int64_t stencil = int64_t(f->N) * f->N * f->N * f->C;
     const int64_t few = f->desc.coef == BSI_F64 && stencil >= 512 ? 24576 : 49152;
     const bool resident = f->grid_bytes <= (size_t(4) << 20);

@@ -79,3 +79,40 @@ def test_static_rejects_oversized_workspace():
         # an unbinned configuration needs no workspace at any size
         _bsi.bsi_eval_static(f.handle, pos[:1000], 1000, u, None, bsi.EvalConfig(sort_tile=0, block=256))
         torch.cuda.synchronize()
+
+
+def test_static_while_tuning_is_loaded(tmp_path):
+    # the workspace is that of the configuration that runs, whatever another thread loads meanwhile
+    import threading
+    import torch
+    import paper_1201_4060_amd as bsi
+    from paper_1201_4060_amd import _bsi
+    n, C, N, P = 32, 1, 4, 3000
+    dbs = []
+    for tile, variant in ((0, 1), (8, 0)):
+        db = tmp_path / f"tile{tile}.jsonl"
+        db.write_text("".join(
+            f'{{"order":{N},"coef":{bsi.BSI_F32},"ncomp":{C},"density_class":{d},"sort_tile":{tile},'
+            f'"variant":{variant},"tiles_per_group":1,"block":256,"xcd_remap":1}}\n' for d in range(-6, -1)))
+        dbs.append(str(db))
+    pos = dev(synth.uniform_positions(P, seed=94))
+    with bsi.Context(0) as ctx, bsi.Field(ctx, n, C, N, bsi.BSI_F32) as f:
+        f.set_spectrum(dev(synth.kolmogorov_spectrum(n, C, seed=95)))
+        want, _ = f.eval(pos, grad=False)
+        u = torch.empty_like(want)
+        stop = threading.Event()
+
+        def load():
+            while not stop.is_set():
+                for db in dbs:
+                    _bsi.bsi_ctx_load_tuning(ctx.handle, db)
+        t = threading.Thread(target=load)
+        t.start()
+        try:
+            for _ in range(2000):
+                _bsi.bsi_eval_static(f.handle, pos, P, u, None, None)
+        finally:
+            stop.set()
+            t.join()
+        torch.cuda.synchronize()
+        assert torch.equal(u, want)
