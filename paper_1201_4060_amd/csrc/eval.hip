@@ -69,6 +69,7 @@ __device__ __forceinline__ bool table_chunk(const ShiftCoarse& cm, const u32x4* 
                                             uint32_t& j0, uint32_t& n) {
     if (blockIdx.x >= __builtin_amdgcn_readfirstlane(*nchunks)) return false;
     const u32x4 d = desc[blockIdx.x];
+    if (__builtin_amdgcn_readfirstlane(d.x) & GRP_FOLLOWS) return false;
     uint32_t khi;
     cm.range(d.x, klo, khi);
     nf = khi - klo;

@@ -114,17 +114,18 @@ __device__ __forceinline__ u32x4 load_global16(const u32x4* p) {
 //   k_grp_coarse  each block scans the totals in LDS (its own copy: a launch
 //                 of a single-block scan costs more than repeating it) and
 //                 scatters its particles into the coarse ranges as 32-byte
-//                 records; one more block cuts the ranges into chunks of at
-//                 most GRP_CHUNK particles
-//   k_grp_fine    one workgroup per chunk, independent of all others: the
-//                 chunk's records are ranked by key in LDS and written in key
-//                 order into the chunk's own slots, and its runs of equal
-//                 keys become work items (cut into pieces of at most `ichunk`)
-// A range of more than GRP_CHUNK particles has several chunks, each sorted by
-// itself: a bucket's particles then lie in several runs, each with items of its
-// own.  Nothing reads buckets as wholes, so no table over all buckets is
-// written, and a crowded range needs no exchange between its workgroups.  The
-// order inside a run is whatever the LDS atomics give; no result depends on it.
+//                 records; one more block cuts the ranges into spans
+//                 (grp_span), and a span into chunks of GRP_CHUNK particles
+//   k_grp_fine    one workgroup per span, independent of all others: the
+//                 span's records are ranked by key in LDS and written in key
+//                 order into the span's own slots, and its runs of equal keys
+//                 become work items (cut into pieces of at most `ichunk`), dealt
+//                 evenly to the span's chunks
+// A range of more than a span has several, each sorted by itself: a bucket's
+// particles then lie in several runs, each with items of its own.  Nothing reads
+// buckets as wholes, so no table over all buckets is written, and a crowded
+// range needs no exchange between its workgroups.  The order inside a run is
+// whatever the LDS atomics give; no result depends on it.
 // The blocks of the two coarse passes are mapped so that each XCD takes one
 // contiguous range of slots, which keeps the partial-line writes of one coarse
 // range in one L2.  What bounds it: memory (24 B of position read twice, a
@@ -141,7 +142,7 @@ __device__ __forceinline__ u32x4 load_global16(const u32x4* p) {
 constexpr int GRP_BLOCK = 1024;
 constexpr uint32_t GRP_FINE_MAX = 8192;      // keys per coarse range: 32 KB of LDS
 constexpr uint32_t GRP_COARSE_MAX = 8193;    // coarse ranges (2^13, and one for the particles without a cell)
-constexpr uint32_t GRP_CHUNK = 2048;         // particles per chunk of the fine pass
+constexpr uint32_t GRP_CHUNK = 2048;         // particles per chunk
 constexpr int GRP_FINE_BLOCK = 256;
 constexpr int GRP_UNROLL = 4;                // slots per thread whose loads overlap in the coarse passes
 constexpr long GRP_NBLK_MAX = 512;           // blocks of the coarse passes: two of 1024 threads per CU
@@ -315,15 +316,37 @@ struct OneField {
     __device__ __forceinline__ void end(uint32_t) const {}
 };
 
-// Most items of a chunk of n particles over nf keys.
+// Particles per span of a range of cnt particles over nf keys: a chunk where that is
+// 128 particles a key on average, otherwise what a workgroup sorts in its registers
+// or, where 128 a key (256 from two such spans on) take more, a longer span whose
+// records are read twice.  Shorter runs cost the gather more than the sort saves.  With
+// chunks sorted alone a crowded range's tiles lay in up to 16 runs (10^7 clustered
+// particles at 512^3, order 6: gather FP32 1920 -> 1770 us, BF16 1525 -> 1435, binning
+// 462 -> 492), and ranges of many keys in runs of a few particles (1024^3, 4 * 10^7:
+// 8250 -> 4620, binning 2000 -> 2460).  Twice as many a key in ranges of less than 8192:
+// 4 * 10^7 uniform at 512^3 binning 1962 -> 2113 and gather 5031 -> 5278.
+constexpr uint32_t GRP_SPAN_REG = 4096;
+constexpr uint32_t GRP_SPAN_MAX = 32768;
+constexpr uint32_t GRP_SPAN_RUN = 128;
+__host__ __device__ inline uint32_t grp_span(uint32_t nf, uint32_t cnt) {
+    if (nf <= GRP_CHUNK / GRP_SPAN_RUN) return GRP_CHUNK;
+    const uint32_t run = cnt > 2 * GRP_SPAN_REG ? 2 * GRP_SPAN_RUN : GRP_SPAN_RUN;
+    const uint32_t n = (nf < GRP_SPAN_MAX / run ? nf : GRP_SPAN_MAX / run) * run;
+    return n > GRP_SPAN_REG ? (n + GRP_CHUNK - 1) / GRP_CHUNK * GRP_CHUNK : GRP_SPAN_REG;
+}
+
+// Most items of a span of n particles over nf keys.
 __host__ __device__ inline uint32_t grp_item_bound(uint32_t n, uint32_t nf, uint32_t ichunk) {
     return (n < nf ? n : nf) + n / ichunk;
 }
 
 // Chunk plan, by one workgroup of GRP_BLOCK threads: base[c] = first slot of
 // range c (base[ncoarse] = all particles), desc[g] = (range, first slot,
-// particles, first item slot) of chunk g, the chunks listed range by range.
+// particles, first item slot) of chunk g, the chunks listed range by range.  The
+// first chunk of a span stands for all of it, the others have GRP_FOLLOWS set; the
+// fine pass gives each of them its part of the items (words 2 and 3).
 // Thread t owns the ranges t * per ..
+constexpr uint32_t GRP_FOLLOWS = 0x80000000u;
 template <typename Coarse, typename Lists>
 __device__ __forceinline__ void grp_plan_block(const Coarse& cm, const Lists& ls, const uint32_t* __restrict__ total,
                                                uint32_t ncoarse, uint32_t ichunk, uint32_t* __restrict__ base,
@@ -335,8 +358,8 @@ __device__ __forceinline__ void grp_plan_block(const Coarse& cm, const Lists& ls
     auto bound = [&](uint32_t c, uint32_t cnt) {
         uint32_t lo, hi;
         cm.range(c, lo, hi);
-        const uint32_t full = cnt / GRP_CHUNK, rem = cnt % GRP_CHUNK;
-        return full * grp_item_bound(GRP_CHUNK, hi - lo, ichunk) + grp_item_bound(rem, hi - lo, ichunk);
+        const uint32_t span = grp_span(hi - lo, cnt), full = cnt / span, rem = cnt % span;
+        return full * grp_item_bound(span, hi - lo, ichunk) + grp_item_bound(rem, hi - lo, ichunk);
     };
     for (uint32_t q = 0; q < per; ++q) {
         if (c0 + q >= ncoarse) break;
@@ -357,9 +380,11 @@ __device__ __forceinline__ void grp_plan_block(const Coarse& cm, const Lists& ls
         ls.begin(c, g);
         uint32_t lo, hi;
         cm.range(c, lo, hi);
-        for (uint32_t j = 0; j < cnt; j += GRP_CHUNK, ++g) {
-            const uint32_t k = min(GRP_CHUNK, cnt - j);
-            desc[g] = u32x4{c, run + j, k, slot};
+        const uint32_t span = grp_span(hi - lo, cnt);
+        for (uint32_t j = 0; j < cnt; j += span) {
+            const uint32_t k = min(span, cnt - j);
+            desc[g++] = u32x4{c, run + j, k, slot};
+            for (uint32_t i = GRP_CHUNK; i < k; i += GRP_CHUNK) desc[g++] = u32x4{c | GRP_FOLLOWS, 0u, 0u, 0u};
             slot += grp_item_bound(k, hi - lo, ichunk);
         }
         run += cnt;
@@ -452,27 +477,12 @@ __device__ __forceinline__ void grp_put(void* out, uint32_t* perm, uint32_t d, c
     }
 }
 
-// The chunk of n <= PER * GRP_FINE_BLOCK records from slot j0, keys [klo, klo +
-// nf).  All its loads are issued at once.
-template <int PER, bool PACK, typename Lists>
-__device__ __forceinline__ void grp_sort_chunk(const Lists& ls, const GrpRec* __restrict__ rec, u32x4* desc, uint32_t c,
-                                               uint32_t j0, uint32_t n, uint32_t slot, uint32_t klo, uint32_t nf,
-                                               uint32_t ichunk, uint32_t* __restrict__ perm, void* __restrict__ out,
-                                               u32x4* __restrict__ items, uint32_t* lh, uint32_t* sh) {
-    u32x4 a[PER], b[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const u32x4* r = reinterpret_cast<const u32x4*>(rec + j0 + min(q * GRP_FINE_BLOCK + threadIdx.x, n - 1));
-        a[q] = load_global16(r);
-        b[q] = load_global16(r + 1);
-    }
-    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK) lh[f] = 0;
-    __syncthreads();
-    uint32_t rank[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q)
-        if (q * GRP_FINE_BLOCK + threadIdx.x < n) rank[q] = atomicAdd(&lh[a[q].x - klo], 1u);
-    __syncthreads();
+// lh[f], the span's particles of key klo + f, becomes the key's first slot from j0 on;
+// the runs' items are written from `slot` on and dealt to the span's `chunks`.
+template <typename Lists>
+__device__ __forceinline__ void grp_runs(const Lists& ls, u32x4* desc, uint32_t chunks, uint32_t c, uint32_t j0,
+                                         uint32_t slot, uint32_t klo, uint32_t nf, uint32_t ichunk,
+                                         u32x4* __restrict__ items, uint32_t* lh, uint32_t* sh) {
     // thread t owns the keys [t * per, (t + 1) * per)
     const uint32_t per = (nf + GRP_FINE_BLOCK - 1) / GRP_FINE_BLOCK;
     const uint32_t f0 = threadIdx.x * per;
@@ -489,7 +499,11 @@ __device__ __forceinline__ void grp_sort_chunk(const Lists& ls, const GrpRec* __
     uint32_t at = 0;
     if (emit) {
         at = block_scan<GRP_FINE_BLOCK>(pieces, sh, &total) + slot;
-        if (threadIdx.x == 0) reinterpret_cast<uint32_t*>(desc)[2] = total;
+        for (uint32_t i = threadIdx.x; i < chunks; i += GRP_FINE_BLOCK) {
+            const uint32_t lo = uint32_t(uint64_t(total) * i / chunks);
+            reinterpret_cast<uint32_t*>(desc + i)[2] = uint32_t(uint64_t(total) * (i + 1) / chunks) - lo;
+            reinterpret_cast<uint32_t*>(desc + i)[3] = slot + lo;
+        }
     }
     for (uint32_t q = 0; q < per; ++q) {
         const uint32_t f = f0 + q;
@@ -502,13 +516,76 @@ __device__ __forceinline__ void grp_sort_chunk(const Lists& ls, const GrpRec* __
         run += cnt;
     }
     __syncthreads();
+}
+
+// The span of n <= PER * GRP_FINE_BLOCK records (one chunk) from slot j0, keys [klo,
+// klo + nf).  All its loads are issued at once.
+template <int PER, bool PACK, typename Lists>
+__device__ __forceinline__ void grp_sort_chunk(const Lists& ls, const GrpRec* __restrict__ rec, u32x4* desc, uint32_t c,
+                                               uint32_t j0, uint32_t n, uint32_t slot, uint32_t klo, uint32_t nf,
+                                               uint32_t ichunk, uint32_t* __restrict__ perm, void* __restrict__ out,
+                                               u32x4* __restrict__ items, uint32_t* lh, uint32_t* sh) {
+    u32x4 a[PER], b[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const u32x4* r = reinterpret_cast<const u32x4*>(rec + j0 + min(q * GRP_FINE_BLOCK + threadIdx.x, n - 1));
+        a[q] = load_global16(r);
+        b[q] = load_global16(r + 1);
+    }
+    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK) lh[f] = 0;
+    __syncthreads();
+    // from here on a[q].x is the key from klo on and the record's rank among its equals
+    static_assert(GRP_FINE_MAX <= 1u << 13 && PER * GRP_FINE_BLOCK <= 1 << 19, "key and rank in one word");
 #pragma unroll
     for (int q = 0; q < PER; ++q)
-        if (q * GRP_FINE_BLOCK + threadIdx.x < n) grp_put<PACK>(out, perm, lh[a[q].x - klo] + rank[q], a[q], b[q]);
+        if (q * GRP_FINE_BLOCK + threadIdx.x < n) {
+            const uint32_t f = a[q].x - klo;
+            a[q].x = f | atomicAdd(&lh[f], 1u) << 13;
+        }
+    __syncthreads();
+    grp_runs(ls, desc, PER <= 8 ? 1u : (n + GRP_CHUNK - 1) / GRP_CHUNK, c, j0, slot, klo, nf, ichunk, items, lh, sh);
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * GRP_FINE_BLOCK + threadIdx.x < n)
+            grp_put<PACK>(out, perm, lh[a[q].x & 0x1fffu] + (a[q].x >> 13), a[q], b[q]);
+}
+
+// A longer span: its records are read twice, to count them and to place them.
+template <int PER, bool PACK, typename Lists>
+__device__ __forceinline__ void grp_sort_span(const Lists& ls, const GrpRec* __restrict__ rec, u32x4* desc, uint32_t c,
+                                              uint32_t j0, uint32_t n, uint32_t slot, uint32_t klo, uint32_t nf,
+                                              uint32_t ichunk, uint32_t* __restrict__ perm, void* __restrict__ out,
+                                              u32x4* __restrict__ items, uint32_t* lh, uint32_t* sh) {
+    constexpr uint32_t STEP = PER * GRP_FINE_BLOCK;
+    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK) lh[f] = 0;
+    __syncthreads();
+    for (uint32_t s0 = threadIdx.x; s0 < n; s0 += 2 * STEP) {
+        uint32_t key[2 * PER];
+#pragma unroll
+        for (int q = 0; q < 2 * PER; ++q) key[q] = rec[j0 + min(s0 + q * GRP_FINE_BLOCK, n - 1)].key;
+#pragma unroll
+        for (int q = 0; q < 2 * PER; ++q)
+            if (s0 + q * GRP_FINE_BLOCK < n) atomicAdd(&lh[key[q] - klo], 1u);
+    }
+    __syncthreads();
+    grp_runs(ls, desc, (n + GRP_CHUNK - 1) / GRP_CHUNK, c, j0, slot, klo, nf, ichunk, items, lh, sh);
+    for (uint32_t s0 = threadIdx.x; s0 < n; s0 += STEP) {
+        u32x4 a[PER], b[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const u32x4* r = reinterpret_cast<const u32x4*>(rec + j0 + min(s0 + q * GRP_FINE_BLOCK, n - 1));
+            a[q] = load_global16(r);
+            b[q] = load_global16(r + 1);
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (s0 + q * GRP_FINE_BLOCK < n)
+                grp_put<PACK>(out, perm, atomicAdd(&lh[a[q].x - klo], 1u), a[q], b[q]);
+    }
 }
 
 template <typename Coarse, typename Lists, bool PACK>
-static __global__ __launch_bounds__(GRP_FINE_BLOCK) void k_grp_fine(
+static __global__ __launch_bounds__(GRP_FINE_BLOCK) __attribute__((amdgpu_waves_per_eu(PACK ? 4 : 3))) void k_grp_fine(
     Coarse cm, Lists ls, const GrpRec* __restrict__ rec, u32x4* __restrict__ desc,
     const uint32_t* __restrict__ nchunks, uint32_t ichunk, uint32_t* __restrict__ perm, void* __restrict__ out,
     u32x4* __restrict__ items) {
@@ -516,8 +593,9 @@ static __global__ __launch_bounds__(GRP_FINE_BLOCK) void k_grp_fine(
     __shared__ uint32_t sh[GRP_FINE_BLOCK / 64];
     const uint32_t g = blockIdx.x;
     if (g >= __builtin_amdgcn_readfirstlane(*nchunks)) return;
+    const uint32_t c = __builtin_amdgcn_readfirstlane(reinterpret_cast<const uint32_t*>(desc + g)[0]);
+    if (c & GRP_FOLLOWS) return;   // (its words 2 and 3 are being written)
     const u32x4 de = desc[g];
-    const uint32_t c = __builtin_amdgcn_readfirstlane(de.x);
     const uint32_t j0 = __builtin_amdgcn_readfirstlane(de.y);
     const uint32_t n = __builtin_amdgcn_readfirstlane(de.z);
     uint32_t klo, khi;
@@ -528,9 +606,10 @@ static __global__ __launch_bounds__(GRP_FINE_BLOCK) void k_grp_fine(
         grp_sort_chunk<decltype(per)::value, PACK>(ls, rec, desc + g, c, j0, n, de.w, klo, nf, ichunk, perm, out, items,
                                                    lh, sh);
     };
-    // half as many records a thread where the range is an evenly filled one
     if (n <= 4 * GRP_FINE_BLOCK) sort(std::integral_constant<int, 4>{});
-    else sort(std::integral_constant<int, int(GRP_CHUNK) / GRP_FINE_BLOCK>{});
+    else if (n <= 8 * GRP_FINE_BLOCK) sort(std::integral_constant<int, 8>{});
+    else if (n <= GRP_SPAN_REG) sort(std::integral_constant<int, int(GRP_SPAN_REG) / GRP_FINE_BLOCK>{});
+    else grp_sort_span<8, PACK>(ls, rec, desc + g, c, j0, n, de.w, klo, nf, ichunk, perm, out, items, lh, sh);
 }
 
 // Coarse ranges of a single key space: range c = [c << s, min((c + 1) << s, nb)).
@@ -599,10 +678,12 @@ inline GrpPlan grp_plan(long nidx, uint32_t nvalid, uint32_t nbuckets, uint32_t 
     return g;
 }
 
-// Most work items of a grouping: a run per chunk and key present, and one more
-// per `ichunk` particles.
+// Most work items of a grouping: a run per span and key present, and one more per
+// `ichunk` particles.  A range has one span that is not full; the full ones hold
+// GRP_SPAN_RUN particles or more per key, or GRP_SPAN_MAX.
 inline size_t grp_item_cap(const GrpPlan& g, uint32_t ichunk) {
-    const size_t runs = size_t(g.nbuckets) + size_t(g.nvalid / GRP_CHUNK) * std::min(g.fine_max, GRP_CHUNK);
+    const size_t full = size_t(g.nvalid / GRP_SPAN_MAX) * g.fine_max + g.nvalid / GRP_SPAN_RUN;
+    const size_t runs = size_t(g.nbuckets) + full;
     return std::min(runs, size_t(g.nvalid)) + size_t(g.nvalid) / ichunk + 1;
 }
 

@@ -94,3 +94,30 @@ def test_direct_lanes(n, C, N, coef, basis):
                 ref = (u, g) if ref is None else ref
                 assert np.array_equal(u, ref[0], equal_nan=True) and np.array_equal(g, ref[1], equal_nan=True), (P, c)
                 assert np.array_equal(v, ref[0], equal_nan=True), (P, c)
+
+
+@pytest.mark.parametrize("coef", ["f32", "f64"])
+def test_crowded_key_ranges(coef):
+    # 10^6 particles over 32^3 tiles: key ranges of 32 tiles, some with about 1024, 2048, 4096, 8192
+    # and 40000 particles (the sizes where the binning sorts a range another way)
+    import torch
+    import paper_1201_4060_amd as bsi
+    n, N = 256, 4
+    rng = np.random.default_rng(17)
+    # a brick of 4^3 tiles is two ranges: corners of bricks far apart
+    out = [rng.random((700000, 3)) * 2 * np.pi]
+    for q, c in enumerate((300, 1300, 1400, 3300, 3400, 7400, 7500, 15900, 40000, 90000)):
+        lo = np.array([q % 4, q // 4, q % 3]) * 2 * np.pi / 4
+        out.append(lo + rng.random((c, 3)) * np.array([32, 32, 16]) * 2 * np.pi / n)
+    pos = np.concatenate(out + [np.full((5000, 3), np.nan)])
+    pos = np.concatenate([pos, rng.random((1000000 - len(pos), 3)) * 2 * np.pi])
+    pos = dev(pos[rng.permutation(len(pos))])
+    grid = dev(rng.standard_normal((1, n, n, n)))
+    with bsi.Context(0) as ctx, bsi.Field(ctx, n, 1, N, bsi.BSI_F32 if coef == "f32" else bsi.BSI_F64) as f:
+        f.set_coefficients(grid)
+        want = f.eval(pos, cfg=bsi.EvalConfig(sort_tile=0, block=256, xcd_remap=1, variant=1))
+        for rounds in (0, 1):
+            got = f.eval(pos, cfg=bsi.EvalConfig(sort_tile=8, block=256, xcd_remap=1, variant=0, item_rounds=rounds))
+            for a, b in zip(got, want):
+                assert torch.equal(torch.nan_to_num(a, nan=7e7), torch.nan_to_num(b, nan=7e7))
+        assert f.nonfinite_count() == 3 * 5000
