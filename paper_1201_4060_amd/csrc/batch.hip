@@ -157,7 +157,7 @@ __global__ __launch_bounds__(BATCH_B) void k_batch_tiles(BatchArgs b) {
         using K = ValueGather<N, CT, C, GRAD, 8, BATCH_B / 64>;
         __shared__ __align__(16) typename K::Shared shared;
         tiled_gather<K, BATCH_B>([&](uint32_t tag, GatherArgs& a) { a = b.items[tag].ga; }, src,
-                                 uint32_t(blockIdx.x) % ITEM_RANGES, lds, &shared, nullptr);
+                                 true, lds, &shared, nullptr);
     }
 }
 
@@ -553,7 +553,7 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     a.binned = base + o_pos;
     a.work = reinterpret_cast<u32x4*>(base + o_work);
     a.desc = b->gbuf.desc;
-    a.ulog = item_units_log2(b->grp.mmax, ITEM_UNITS_BATCH, Btot);
+    a.ulog = item_units_log2(b->grp, BATCH_CHUNK, ITEM_UNITS_BATCH, false);
     a.ctl = reinterpret_cast<uint32_t*>(base + o_ctl);
     a.start = reinterpret_cast<uint32_t*>(base + o_start);
     for (auto& x : hi) {

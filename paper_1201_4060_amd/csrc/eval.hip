@@ -176,7 +176,7 @@ k_gather_tiled(GatherArgs a) {
     __shared__ __align__(16) typename K::Shared shared;
     __shared__ uint32_t taken[3];
     tiled_gather<K, B>([&](uint32_t, GatherArgs& x) { x = a; }, a.src,
-                       a.xcd_remap ? uint32_t(blockIdx.x) % ITEM_RANGES : 0u, tile_v, &shared, taken);
+                       a.xcd_remap != 0, tile_v, &shared, taken);
 }
 
 // ------------------------------------------------------------- launchers ---
@@ -427,7 +427,7 @@ BinArrays bin_arrays(const bsi_field* f, long P, int tile, const BinLayout& l, v
     const GrpPlan g = bin_plan(bin_key_count(f, tile), P, &shift);
     const GrpBuffers gb = grp_buffers(g, reinterpret_cast<uint32_t*>(w + l.grp));
     BinArrays b;
-    b.units_log2 = item_units_log2(g.mmax, ITEM_UNITS);
+    b.units_log2 = l.ichunk ? item_units_log2(g, l.ichunk, ITEM_UNITS, f->N <= 4) : 0;
     b.desc = gb.desc;
     b.nchunks = gb.nchunks;
     b.binned = w + l.binned;

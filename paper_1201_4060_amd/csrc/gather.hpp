@@ -272,30 +272,18 @@ static __global__ __launch_bounds__(1024) void k_grp_scan(uint32_t* __restrict__
 // chunk plan (descriptor word 3; the fine pass puts their count in word 2).
 // The tiled gathers take them in units, equal parts of a chunk's items, so that
 // no list of all items is needed: one kept in order costs another launch, one
-// appended to by the chunks as they finish loses the order.  Eight units a
-// chunk where there are many chunks (a unit is then mostly a row of four tiles),
-// more where there are few, so that every CU gets some: `target` units at least.
-// One field: 8192 (10^6 particles at 256^3, order 6 / FP64 at 192 x 128 x 256: 217 /
-// 299 us, with 16384 230 / 287, with 32768 254 / 286 -- the next unit's loads
-// are hidden behind four items).  A batch, whose fields differ in what an item
-// costs: 32768 (31 fields of up to 128^3, orders 4 and 6: 119 + 230 us with 8192,
-// 129 + 188 with 32768, 150 + 212 with 65536), but no more units than tiles, or some
-// are empty and taken in vain (9 fields of up to 96^3 with up to 4 * 10^5 particles:
-// 16 units a chunk 102 + 219 us, 8 units 65 + 203).
+// appended to by the chunks as they finish loses the order.
 constexpr uint32_t ITEM_UNITS = 8192, ITEM_UNITS_BATCH = 32768;
-inline uint32_t item_units_log2(uint32_t chunks, uint32_t target, uint64_t most = ~uint64_t(0)) {
-    uint32_t l = 3;
-    while (l < 6 && (uint64_t(chunks) << l) < target && (uint64_t(chunks) << (l + 1)) <= most) ++l;
-    return l;
-}
+
 // The chunks are split into ITEM_RANGES contiguous ranges, one per XCD
 // (neighbouring tiles, whose blocks overlap, meet in the same L2); the next
 // unit of range x is counted at ITEM_CTL_STRIDE * x, each counter on a 128-byte
-// line of its own (atomics on one line serialise), then the count of finished
-// workgroups.
+// line of its own (atomics on one line serialise), then the counts of finished
+// workgroups: of ITEM_GROUPS groups of workgroups, and of those groups.
 constexpr int ITEM_RANGES = 8;
+constexpr int ITEM_GROUPS = 32;
 constexpr int ITEM_CTL_STRIDE = 32;
-constexpr int ITEM_CTL_WORDS = ITEM_CTL_STRIDE * (ITEM_RANGES + 1);
+constexpr int ITEM_CTL_WORDS = ITEM_CTL_STRIDE * (ITEM_RANGES + ITEM_GROUPS + 1);
 
 // First chunk of the x-th range of nch chunks.
 __host__ __device__ inline uint32_t item_range_begin(uint32_t x, uint32_t nch) {
@@ -676,6 +664,23 @@ inline GrpPlan grp_plan(long nidx, uint32_t nvalid, uint32_t nbuckets, uint32_t 
     // sum over ranges of ceil(n_c / GRP_CHUNK) <= nvalid / GRP_CHUNK + ncoarse
     g.mmax = nvalid / GRP_CHUNK + std::min(g.ncoarse, nvalid);
     return g;
+}
+
+// log2 of the units per chunk for about `items` items in all (evenly spread particles).
+// Eight: where there are many chunks a unit is then mostly a row of four tiles; four
+// for order 4 where a chunk has few items, since a unit costs as much as a cheap item
+// (10^6 particles, four / eight units: 128^3 uniform, order 4 FP32 78 / 84, BF16 79 /
+// 112 us, clustered 97 / 97, 98 / 126; order 6 clustered FP32 140 / 130, FP64 353 / 335,
+// its items being worth balancing).  More while fewer than `target` units come out,
+// so that every CU gets some, of three items at least: one of fewer is not yet there
+// when the one before ends (64^3 order 4, four / sixteen: FP32 61 / 85, BF16 50 / 105).
+inline uint32_t item_units_log2(const GrpPlan& g, uint32_t ichunk, uint32_t target, bool cheap) {
+    const uint64_t chunks = std::max<uint64_t>(1, std::max(g.nvalid / GRP_CHUNK, std::min(g.ncoarse, g.nvalid)));
+    const uint64_t tiles = std::min(g.nbuckets, g.nvalid);
+    const uint64_t items = std::max(tiles, g.nvalid / ichunk + tiles / 2);
+    uint32_t l = cheap && items < 16 * chunks ? 2 : 3;
+    while (l < 6 && (chunks << l) < target && 3 * (chunks << (l + 1)) <= items) ++l;
+    return l;
 }
 
 // Most work items of a grouping: a run per span and key present, and one more per
@@ -1772,15 +1777,21 @@ struct ItemStream {
     uint32_t base, k, m; // items [base + k, base + m) are left of the unit
     int stage;           // of the next unit: 1 counter, 2 descriptor, 3 items requested, 4 here, 5 none left
     uint32_t v;          // stage 1: the counter's value (first lane)
+    bool spread;         // workgroup b's home is range b mod ITEM_RANGES (else 0 for all)
+    uint32_t vadd;       // stage 1: the unit is v + vadd
     u32x4 d, nits;       // stages 2 and 3
     uint32_t nbase, nm;
 
     // The first item into it; false when there is none at all.
-    __device__ __forceinline__ bool begin(const ItemSource& src, uint32_t* lds, uint32_t home, u32x4& it) {
+    __device__ __forceinline__ bool begin(const ItemSource& src, uint32_t* lds, bool homes_spread, u32x4& it) {
         s = src;
         sh = lds;
-        x = home;
-        request();
+        // the first unit needs no counter: the workgroups of a range start on its first ones
+        spread = homes_spread;
+        x = spread ? blockIdx.x % ITEM_RANGES : 0u;
+        v = spread ? blockIdx.x / ITEM_RANGES : blockIdx.x;
+        vadd = 0;
+        stage = 1;
         gbeg = s.g0 ? __builtin_amdgcn_readfirstlane(*s.g0) : 0u;
         nch = __builtin_amdgcn_readfirstlane(*s.g1) - gbeg;
         enter();
@@ -1797,7 +1808,7 @@ struct ItemStream {
     // ... and after it.
     __device__ __forceinline__ void step() {
         if (stage == 1) {
-            uint32_t unit = __builtin_amdgcn_readfirstlane(B > 64 ? sh[0] : v);
+            uint32_t unit = __builtin_amdgcn_readfirstlane(B > 64 ? sh[0] : v) + vadd;
             if (unit >= xend && !seek(unit)) {
                 stage = 5;
                 return;
@@ -1862,7 +1873,12 @@ struct ItemStream {
     }
     __device__ __forceinline__ void request() {
         v = threadIdx.x == 0 ? atomicAdd(s.ctl + ITEM_CTL_STRIDE * x, 1u) : 0u;
+        vadd = firsts(x);
         stage = 1;
+    }
+    // Units of range r that workgroups start on.
+    __device__ __forceinline__ uint32_t firsts(uint32_t r) const {
+        return spread ? (gridDim.x + ITEM_RANGES - 1 - r) / ITEM_RANGES : r == 0 ? gridDim.x : 0u;
     }
     __device__ __forceinline__ u32x4 fetch(uint32_t from, uint32_t n) const {
         return load_global16(s.items + from + min(threadIdx.x & 63u, n - 1));
@@ -1907,7 +1923,7 @@ struct ItemStream {
             const uint32_t l = threadIdx.x % ITEM_RANGES;
             const uint32_t at =
                 __hip_atomic_load(s.ctl + ITEM_CTL_STRIDE * l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t some = uint32_t(__ballot(at < units(l))) & ((1u << ITEM_RANGES) - 1u);
+            const uint32_t some = uint32_t(__ballot(at + firsts(l) < units(l))) & ((1u << ITEM_RANGES) - 1u);
             if (some == 0) {
                 x = ITEM_RANGES;
                 return;
@@ -1915,7 +1931,7 @@ struct ItemStream {
             const uint32_t turn = (x + 1) % ITEM_RANGES;
             x = (turn + uint32_t(__builtin_ctz((some | (some << ITEM_RANGES)) >> turn))) % ITEM_RANGES;
             request();
-            unit = __builtin_amdgcn_readfirstlane(v);
+            unit = __builtin_amdgcn_readfirstlane(v) + vadd;
             if (unit < units(x)) return;
         }
     }
@@ -1923,14 +1939,22 @@ struct ItemStream {
 
 // Called once by every workgroup when all ranges are exhausted: the last one
 // sets the take counters back, so that another run over the same items needs no
-// launch to do it.
+// launch to do it.  The workgroups are counted in groups, and the groups: one counter
+// takes about 15 ns a workgroup, which held up the end of every run (32768 items at
+// 256^3 on 3072 workgroups, BF16 order 4: 117 us, 109 in groups, 104 when the first
+// units need no counter either).
 __device__ __forceinline__ void item_take_end(uint32_t* ctl) {
     if (threadIdx.x != 0) return;
+    const uint32_t g = blockIdx.x % ITEM_GROUPS;
+    const uint32_t groups = min(gridDim.x, uint32_t(ITEM_GROUPS));
+    const uint32_t members = (gridDim.x - g + ITEM_GROUPS - 1) / ITEM_GROUPS;
     uint32_t* done = ctl + ITEM_CTL_STRIDE * ITEM_RANGES;
-    if (atomicAdd(done, 1u) + 1 == gridDim.x) {
-        for (int x = 0; x < ITEM_RANGES; ++x) atomicExch(ctl + ITEM_CTL_STRIDE * x, 0u);
-        atomicExch(done, 0u);
-    }
+    uint32_t* all = done + ITEM_CTL_STRIDE * ITEM_GROUPS;
+    if (atomicAdd(done + ITEM_CTL_STRIDE * g, 1u) + 1 != members) return;
+    atomicExch(done + ITEM_CTL_STRIDE * g, 0u);
+    if (atomicAdd(all, 1u) + 1 != groups) return;
+    for (int x = 0; x < ITEM_RANGES; ++x) atomicExch(ctl + ITEM_CTL_STRIDE * x, 0u);
+    atomicExch(all, 0u);
 }
 
 // Weight pairs (w, w') of a particle on several lanes, through LDS: every lane
@@ -2124,7 +2148,7 @@ constexpr int tile_lds_bytes() {
 // copied during the contraction took 2106 instead of 1405 us, results stored one
 // item late 1412 instead of 1364.
 template <typename K, int B, typename ArgsOf>
-__device__ __forceinline__ void tiled_gather(ArgsOf args_of, const ItemSource& src, uint32_t home, u32x4* lds,
+__device__ __forceinline__ void tiled_gather(ArgsOf args_of, const ItemSource& src, bool spread, u32x4* lds,
                                              typename K::Shared* shared, uint32_t* sh) {
     using CT = typename K::CT;
     using AT = typename K::AT;
@@ -2134,7 +2158,7 @@ __device__ __forceinline__ void tiled_gather(ArgsOf args_of, const ItemSource& s
     const CT* tile = reinterpret_cast<const CT*>(lds);
     ItemStream<B> stream;
     u32x4 it;
-    if (!stream.begin(src, sh, home, it)) {
+    if (!stream.begin(src, sh, spread && gridDim.x >= ITEM_RANGES, it)) {
         item_take_end(src.ctl);
         return;
     }

@@ -387,7 +387,7 @@ template <int N, typename CT, int C>
 __global__ __launch_bounds__(HESS_TB) void k_gather_hess_tiled(HessArgs a) {
     using K = HessGather<N, CT, C>;
     __shared__ u32x4 lds[tile_lds_bytes<K>() / 16];
-    tiled_gather<K, HESS_TB>([&](uint32_t, HessArgs& x) { x = a; }, a.src, uint32_t(blockIdx.x) % ITEM_RANGES, lds,
+    tiled_gather<K, HESS_TB>([&](uint32_t, HessArgs& x) { x = a; }, a.src, true, lds,
                              nullptr, nullptr);
 }
 
