@@ -257,12 +257,12 @@ constexpr bool tile_ok() {
 // FP64 order 6 instances hold up to 376 registers, one wavefront a SIMD: 128, so that
 // two workgroups share a CU and one copies while the other evaluates (300007
 // particles at 192 x 128 x 256: 270 us; with 64 threads 287, with 256 364).  FP64
-// below order 6, whose blocks let four workgroups share a CU: 64 (10^6 particles at
-// 256^3, order 4: 229 us, with 128 threads 261, clustered 266 / 298; for the dense tiles of
-// 64^3 it is the other way round, 105 / 94).
+// scalars and below order 6, whose blocks let four workgroups or more share a CU: 64
+// (10^6 particles at 256^3, order 4: 229 us, with 128 threads 261, clustered 266 / 298, scalar
+// order 6 168 / 262; for the dense tiles of 64^3 order 4 it is the other way round, 105 / 94).
 template <int N, typename CT, int C, int T>
 constexpr int tile_block() {
-    if (sizeof(CT) == 8) return N < 6 ? 64 : 128;
+    if (sizeof(CT) == 8) return N == 6 && C == 3 ? 128 : 64;
     return TileGeom<N, CT, C, T>::SLOTS >= 3072 ? 256 : TileGeom<N, CT, C, T>::SLOTS >= 2048 ? 128 : 64;
 }
 
