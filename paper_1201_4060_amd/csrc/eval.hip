@@ -198,17 +198,21 @@ CellArgs cell_args(const bsi_field* f, const double* pos, long P) {
 
 // Several lanes per particle (k_gather_split) or one (k_gather).  Unbinned: several
 // while the particles do not fill the chip's wavefronts one lane each (64^3 FP32
-// order 6: 10^4 particles 22 against 32 us, 2 * 10^4 27 / 33, 4 * 10^4 37 / 35).
+// order 6: 10^4 particles 22 against 32 us, 2 * 10^4 27 / 33, 4 * 10^4 37 / 35; 256^3
+// BF16 order 6, whose rows are read four bytes at a time: 2 * 10^4 23 / 28, 2.5 * 10^4
+// 29 / 28, 3 * 10^4 34 / 29).
 // Binned: several for a sparse cloud, whose particles share little in the cache
 // (whole evaluations; 1024^3 BF16 scalar, 4 * 10^6: 1502 / 2070 us, 256^3 FP32 order
 // 6, 1.6 * 10^5: 122 / 167; from one particle in eight cells on one lane does with
 // fewer instructions: 128^3 FP32 scalar, 10^6: 178 / 158), but one again for the
 // largest stencils below one particle in 256 cells, bound by memory pages (512^3
-// FP32 order 6, 3.2 * 10^5: 421 / 379, 256^3, 8 * 10^4: 88 / 113).
+// FP32 order 6, 3.2 * 10^5: 421 / 379, 256^3, 8 * 10^4: 88 / 113; 256^3 FP64 order 4,
+// 6 * 10^4: 72 / 66).
 bool split_lanes(const bsi_field* f, long P, bool binned) {
-    if (!binned) return P < 32768;
+    const int stencil = f->N * f->N * f->N * f->C;
+    if (!binned) return P < (f->desc.coef == BSI_BF16 && stencil >= 512 ? 24576 : 32768);
     const double dens = double(P) / (double(f->n[0]) * f->n[1] * f->n[2]);
-    const bool large = f->N * f->N * f->N * f->C >= 512;
+    const bool large = stencil >= (f->desc.coef == BSI_F64 ? 192 : 512);
     return dens < 1.0 / 8 && (!large || dens >= 1.0 / 256);
 }
 

@@ -120,19 +120,25 @@ bsi_status lookup_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_c
     return BSI_OK;
 }
 
-// A single evaluation that nothing else runs beside: below some 10^5 particles it is
-// bound by the latency of its launches and of one item or particle, not by what
-// the LDS tiles save (whole evaluations, us, unbinned / binned and direct / tiled):
-//   64^3 FP32 order 6:     2 * 10^4  27 / 41 / 67,  1.6 * 10^5  72 / 84 / 111,
-//                          3.2 * 10^5  104 / 119 / 121,  10^6  292 / 281 / 175
-//   32^3 FP64 scalar:      10^4  19 / 35 / 59,  10^6  90 / 110 / 123
-//   256^3 FP32 order 4:    4 * 10^4  33 / 49 / -,  3.2 * 10^5  139 / 112 / 137,
-//                          10^6  397 / 271 / 214
-//   256^3 FP32 order 6:    4 * 10^4  57 / 67 / -,  3.2 * 10^5  322 / 191 / 180
-//   256^3 BF16 scalar:     3.2 * 10^5  206 / 86 / 143,  10^6  610 / 168 / 167
-//   64^3 FP64 order 6:     2 * 10^4  48 / 56 / 64,  4 * 10^4  81 / 63 / 73
+// A single evaluation (the server's too, whose requests overlap): below some 10^5
+// particles it is bound by the latency of its launches and of one item or particle,
+// not by what the LDS tiles save (whole evaluations of uniform particles, us, unbinned /
+// binned and direct / tiled):
+//   64^3 FP32 order 6:     1.6 * 10^5  58 / 70 / 86,  3.2 * 10^5  90 / 104 / 105,
+//                          6.4 * 10^5  188 / 180 / 128
+//   32^3 FP32 order 4:     6.4 * 10^5  62 / 84 / 68,  1.28 * 10^6  118 / 139 / 118
+//   256^3 FP32 order 4:    8 * 10^4  37 / 44 / 119,  3.2 * 10^5  139 / 112 / 137
+//   512^3 FP32 order 4:    8 * 10^4  43 / 57 / 331
+//   256^3 FP32 linear:     8 * 10^4  9 / 31 / 121,  1.28 * 10^6  121 / 205 / 239, scalar
+//                          2 * 10^7  1502 / 1866 / 1979
+//   64^3 FP64 order 6:     4 * 10^4  84 / 48 / 41; scalar 1.6 * 10^5  57 / 53 / 78,
+//                          3.2 * 10^5  104 / 77 / 91,  6.4 * 10^5  203 / 126 / 117
+//   32^3 FP64 order 4:     1.6 * 10^5  46 / 54 / 48,  3.2 * 10^5  90 / 79 / 70
+//   128^3 FP64 order 4:    8 * 10^4  61 / 51 / 45,  1.6 * 10^5  97 / 71 / 54
+//   256^3 FP64 order 4:    3.2 * 10^5  224 / 237 / 206,  6.4 * 10^5  445 / 375 / 242
 // So: no binning up to 48 Ki particles (half for the largest FP64 stencils), nor for
-// a grid that fits an XCD's L2 up to 2^28 stencil values; no tiles below 3 * 2^25.
+// a grid that fits an XCD's L2 up to 2^28 stencil values, FP64 (whose direct kernels
+// take several times as long a value) 2^25; no tiles below 3 * 2^25, FP64 2^24.
 bsi_status one_shot_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval_config* out,
                            bsi_eval_config* looked_up) {
     const bool tuned = tuned_config(ctx, f, P, out);
@@ -140,12 +146,13 @@ bsi_status one_shot_config(bsi_ctx* ctx, const bsi_field* f, int64_t P, bsi_eval
     if (looked_up) *looked_up = *out;
     if (tuned) return BSI_OK;
     const int64_t stencil = int64_t(f->N) * f->N * f->N * f->C;
-    const int64_t few = f->desc.coef == BSI_F64 && stencil >= 512 ? 24576 : 49152;
+    const bool f64 = f->desc.coef == BSI_F64;
+    const int64_t few = f64 && stencil >= 512 ? 24576 : 49152;
     const bool resident = f->grid_bytes <= (size_t(4) << 20);
-    if (P <= few || (resident && P <= (int64_t(1) << 28) / stencil)) {
+    if (P <= few || (resident && P <= (int64_t(1) << (f64 ? 25 : 28)) / stencil)) {
         out->variant = 1;
         out->sort_tile = 0;
-    } else if (P <= (int64_t(3) << 25) / stencil) {
+    } else if (P <= (f64 ? int64_t(1) << 24 : int64_t(3) << 25) / stencil) {
         out->variant = 1;
     }
     return BSI_OK;
