@@ -254,7 +254,8 @@ bsi_status bsi_debug_cells(bsi_field* field, const double* pos_dev, int64_t P,
                            int32_t* cell_dev, double* t_dev, void* hip_stream);
 
 /* The binning of the evaluation path, for tests (not part of the method: a
- * locality device).  Buckets are Morton tiles of `tile` cells per edge (tile
+ * locality device), collected into one table from the work items and binned
+ * particles that a tiled evaluation would read.  Buckets are Morton tiles of `tile` cells per edge (tile
  * >= 1 and >= ceil(max(n) / 256), else BSI_E_INVAL): bucket b < nbuckets - 1
  * holds the particles whose cell (bsi_debug_cells) lies in the tile with
  * coordinates (cell_d / tile) whose bits interleave into b, axis 0 highest of

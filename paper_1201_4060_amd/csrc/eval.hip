@@ -25,10 +25,8 @@ __global__ void k_debug_cells(CellArgs a, int32_t* cell, double* t) {
 
 // ---------------------------------------------------------------- binning ---
 
-// Key of a particle: that of its sort tile (MORTON: the tile's Morton index,
-// else tile_key), or nbuckets_finite for a non-finite position; its coarse range
-// is key >> shift.
-template <bool MORTON>
+// Key of a particle: that of its sort tile (tile_key), or nbuckets_finite for a
+// non-finite position; its coarse range is key >> shift.
 struct TileKey {
     CellArgs a;
     int tile;
@@ -52,90 +50,94 @@ struct TileKey {
         pl.key = nbuckets_finite;
         if (pl.ok) {
             const uint32_t T = uint32_t(tile);
-            const uint32_t i = uint32_t(pl.cell[0]) / T, j = uint32_t(pl.cell[1]) / T, k = uint32_t(pl.cell[2]) / T;
-            pl.key = MORTON ? (spread3(i) << 2) | (spread3(j) << 1) | spread3(k) : tile_key(i, j, k);
+            pl.key = tile_key(uint32_t(pl.cell[0]) / T, uint32_t(pl.cell[1]) / T, uint32_t(pl.cell[2]) / T);
         }
         pl.coarse = pl.key >> shift;
     }
 };
 
-// The grouping finished as one table over all buckets (bsi_debug_bins): the
-// chunks' keys are counted into per-key counters, one workgroup per coarse
-// range turns them into the bucket table and per-key cursors, and every chunk
-// reserves its keys' slots there.
+// The binning read back as one table over all tiles in Morton order (bsi_debug_bins),
+// from what a gather reads: chunk descriptors, work items, binned particles.
 
-__device__ __forceinline__ bool table_chunk(const ShiftCoarse& cm, const u32x4* desc, const uint32_t* nchunks,
-                                            const GrpRec* __restrict__ rec, uint32_t* lh, uint32_t& klo, uint32_t& nf,
-                                            uint32_t& j0, uint32_t& n) {
-    if (blockIdx.x >= __builtin_amdgcn_readfirstlane(*nchunks)) return false;
-    const u32x4 d = desc[blockIdx.x];
-    if (__builtin_amdgcn_readfirstlane(d.x) & GRP_FOLLOWS) return false;
-    uint32_t khi;
-    cm.range(d.x, klo, khi);
-    nf = khi - klo;
-    j0 = d.y;
-    n = d.z;
-    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK) lh[f] = 0;
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < n; j += GRP_FINE_BLOCK) atomicAdd(&lh[rec[j0 + j].key - klo], 1u);
-    __syncthreads();
-    return true;
+// Bucket of an item in the table of nb buckets (the last one: no cell).
+__device__ __forceinline__ uint32_t item_bucket(const u32x4& it, uint32_t tile, uint32_t nb) {
+    if (it.x == NO_CELL) return nb - 1;
+    return (spread3((it.x >> 20) / tile) << 2) | (spread3(((it.x >> 10) & 1023u) / tile) << 1) |
+           spread3((it.x & 1023u) / tile);
 }
 
-__global__ __launch_bounds__(GRP_FINE_BLOCK) void k_table_count(ShiftCoarse cm, const GrpRec* __restrict__ rec,
-                                                               const u32x4* __restrict__ desc,
-                                                               const uint32_t* __restrict__ nchunks,
-                                                               uint32_t* __restrict__ kcount) {
-    extern __shared__ uint32_t lh[];
-    uint32_t klo, nf, j0, n;
-    if (!table_chunk(cm, desc, nchunks, rec, lh, klo, nf, j0, n)) return;
-    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK)
-        if (lh[f]) atomicAdd(&kcount[klo + f], lh[f]);
-}
-
-__global__ __launch_bounds__(GRP_FINE_BLOCK) void k_table_offsets(ShiftCoarse cm, const uint32_t* __restrict__ base,
-                                                                 uint32_t* __restrict__ kcount,
-                                                                 uint32_t* __restrict__ hist,
-                                                                 uint32_t* __restrict__ offs) {
-    __shared__ uint32_t sh[GRP_FINE_BLOCK / 64];
-    uint32_t klo, khi;
-    cm.range(blockIdx.x, klo, khi);
-    const uint32_t nf = khi - klo;
-    const uint32_t per = (nf + GRP_FINE_BLOCK - 1) / GRP_FINE_BLOCK;
-    const uint32_t f0 = threadIdx.x * per;
-    uint32_t sum = 0;
-    for (uint32_t q = 0; q < per; ++q)
-        if (f0 + q < nf) sum += kcount[klo + f0 + q];
-    uint32_t total;
-    uint32_t run = block_scan<GRP_FINE_BLOCK>(sum, sh, &total) + base[blockIdx.x];
-    for (uint32_t q = 0; q < per; ++q) {
-        const uint32_t f = f0 + q;
-        if (f < nf) {
-            const uint32_t cnt = kcount[klo + f];
-            hist[klo + f] = cnt;
-            offs[klo + f] = run;
-            kcount[klo + f] = run;
-            run += cnt;
-        }
+// One workgroup per chunk: the items' particles into their buckets' counts.
+__global__ __launch_bounds__(256) void k_table_count(ItemSource src, uint32_t tile, uint32_t nb,
+                                                    uint32_t* __restrict__ count) {
+    if (blockIdx.x >= *src.g1) return;
+    const u32x4 d = src.desc[blockIdx.x];
+    for (uint32_t i = threadIdx.x; i < d.z; i += 256) {
+        const u32x4 it = src.items[d.w + i];
+        const uint32_t b = item_bucket(it, tile, nb);
+        if (b < nb) atomicAdd(&count[b], it.z);
     }
 }
 
-__global__ __launch_bounds__(GRP_FINE_BLOCK) void k_table_scatter(ShiftCoarse cm, const GrpRec* __restrict__ rec,
-                                                                 const u32x4* __restrict__ desc,
-                                                                 const uint32_t* __restrict__ nchunks,
-                                                                 uint32_t* __restrict__ kcursor,
-                                                                 uint32_t* __restrict__ perm,
-                                                                 double* __restrict__ pos_sorted) {
-    extern __shared__ uint32_t lh[];
-    uint32_t klo, nf, j0, n;
-    if (!table_chunk(cm, desc, nchunks, rec, lh, klo, nf, j0, n)) return;
-    for (uint32_t f = threadIdx.x; f < nf; f += GRP_FINE_BLOCK)
-        if (lh[f]) lh[f] = atomicAdd(&kcursor[klo + f], lh[f]);
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < n; j += GRP_FINE_BLOCK) {
-        const u32x4* r = reinterpret_cast<const u32x4*>(rec + j0 + j);
-        const u32x4 a = load_global16(r), b = load_global16(r + 1);
-        grp_put<false>(pos_sorted, perm, atomicAdd(&lh[a.x - klo], 1u), a, b);
+// One workgroup: counts to hist, their exclusive scan to offs and, as cursors, to count.
+__global__ __launch_bounds__(1024) void k_table_offsets(uint32_t nb, uint32_t* __restrict__ count,
+                                                       uint32_t* __restrict__ hist, uint32_t* __restrict__ offs) {
+    __shared__ uint32_t sh[1024 / 64];
+    uint32_t before = 0;
+    for (uint32_t k0 = 0; k0 < nb; k0 += 1024) {
+        const uint32_t k = k0 + threadIdx.x;
+        const uint32_t v = k < nb ? count[k] : 0u;
+        uint32_t total;
+        const uint32_t at = before + block_scan<1024>(v, sh, &total);
+        if (k < nb) {
+            hist[k] = v;
+            offs[k] = at;
+            count[k] = at;
+        }
+        before += total;
+    }
+}
+
+// One workgroup per chunk: the items' particles to their buckets' slots, with the
+// position that the binned particle stands for: an FP64 one's own, for an FP32
+// record that of the particle it names if the record is that particle's (else NaN).
+template <typename AT>
+__global__ __launch_bounds__(256) void k_table_scatter(ItemSource src, CellArgs a, uint32_t tile, uint32_t nb,
+                                                      const void* __restrict__ binned,
+                                                      const uint32_t* __restrict__ perm,
+                                                      uint32_t* __restrict__ cursor, uint32_t* __restrict__ perm_out,
+                                                      double* __restrict__ pos_sorted) {
+    __shared__ uint32_t first;
+    if (blockIdx.x >= *src.g1) return;
+    const u32x4 d = src.desc[blockIdx.x];
+    for (uint32_t i = 0; i < d.z; ++i) {
+        const u32x4 it = src.items[d.w + i];
+        const uint32_t b = item_bucket(it, tile, nb);
+        if (threadIdx.x == 0) first = b < nb ? atomicAdd(&cursor[b], it.z) : 0u;
+        __syncthreads();
+        const uint32_t at = first;
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < it.z; j += 256) {
+            if (b >= nb || long(at) + j >= a.P || long(it.y) + j >= a.P) continue;
+            const uint32_t p = perm[it.y + j];
+            perm_out[at + j] = p;
+            RawParticle<AT> raw;
+            raw.load(binned, long(it.y) + j);
+            double x[3] = {__builtin_nan(""), __builtin_nan(""), __builtin_nan("")};
+            if constexpr (sizeof(AT) == 8) {
+                for (int k = 0; k < 3; ++k) x[k] = raw.x[k];
+            } else if (long(p) < a.P) {
+                const int n[3] = {a.n0, a.n1, a.n2};
+                const double ih[3] = {a.ih0, a.ih1, a.ih2};
+                const double* y = a.pos + 3 * long(p);
+                int cell[3];
+                AT t[3];
+                const bool ok = locate<AT>(y, n, ih, cell, t);
+                bool same = raw.r.w == (ok ? pack_cell(cell) : NO_CELL);
+                for (int k = 0; k < 3 && ok; ++k) same = same && raw.r[k] == __float_as_uint(t[k]);
+                for (int k = 0; k < 3 && same; ++k) x[k] = y[k];
+            }
+            for (int k = 0; k < 3; ++k) pos_sorted[3 * (long(at) + j) + k] = x[k];
+        }
     }
 }
 
@@ -450,7 +452,7 @@ bsi_status bin_run(bsi_field* f, const double* pos, long P, int tile, const BinL
     const GrpPlan g = bin_plan(nbf, P, &shift);
     const GrpBuffers gb = grp_buffers(g, reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + l.grp));
     const BinArrays b = bin_arrays(f, P, tile, l, ws);
-    const TileKey<false> mk{cell_args(f, pos, P), tile, uint32_t(nbf), shift};
+    const TileKey mk{cell_args(f, pos, P), tile, uint32_t(nbf), shift};
     const ShiftCoarse cm{shift, uint32_t(nbf + 1)};
     const OneField ls{b.ctl != nullptr, uint32_t(tile), uint32_t(nbf)};
     const uint32_t ichunk = l.ichunk ? l.ichunk : GRP_CHUNK;
@@ -641,26 +643,24 @@ bsi_status debug_bins_run(bsi_field* f, const double* pos, int64_t P, int tile, 
         BSI_HIP(hipMemsetAsync(offs, 0, nb * sizeof(uint32_t), s));
         return BSI_OK;
     }
-    int shift = 0;
-    const GrpPlan g = bin_plan(nb - 1, P, &shift);
-    const size_t words = (grp_scratch_words(g) + 3) / 4 * 4;
+    const BinLayout l = bin_layout(f, long(P), tile, 512u);
+    const size_t table = (l.bytes + 15) / 16 * 16;
     void* ws = nullptr;
-    BSI_TRY(get_workspace(f->ctx->eval_ws, s, (words + nb) * sizeof(uint32_t), &ws));
-    uint32_t* kcount = static_cast<uint32_t*>(ws) + words;
-    const GrpBuffers gb = grp_buffers(g, static_cast<uint32_t*>(ws));
-    const TileKey<true> mk{cell_args(f, pos, P), tile, uint32_t(nb - 1), shift};
-    const ShiftCoarse cm{shift, uint32_t(nb)};
-    const size_t lf = size_t(g.fine_max) * sizeof(uint32_t);
-    grp_count(mk, g, gb, nullptr, 0, s);
-    grp_scan(g, gb, s);
-    grp_coarse<false>(mk, cm, OneField{}, g, gb, GRP_CHUNK, s);
-    hipLaunchKernelGGL(k_fill_u32, dim3(unsigned(std::min<size_t>((nb + 255) / 256, 4096))), dim3(256), 0, s, kcount,
+    BSI_TRY(get_workspace(f->ctx->eval_ws, s, table + nb * sizeof(uint32_t), &ws));
+    uint32_t* count = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + table);
+    BSI_TRY(bin_run(f, pos, long(P), tile, l, ws, s));
+    const BinArrays b = bin_arrays(f, long(P), tile, l, ws);
+    const ItemSource src = item_source(b);
+    const CellArgs ca = cell_args(f, pos, long(P));
+    int shift = 0;
+    const unsigned chunks = bin_plan(bin_key_count(f, tile), long(P), &shift).mmax;
+    hipLaunchKernelGGL(k_fill_u32, dim3(unsigned(std::min<size_t>((nb + 255) / 256, 4096))), dim3(256), 0, s, count,
                        long(nb), 0u);
-    hipLaunchKernelGGL(k_table_count, dim3(g.mmax), dim3(GRP_FINE_BLOCK), lf, s, cm, gb.rec, gb.desc, gb.nchunks,
-                       kcount);
-    hipLaunchKernelGGL(k_table_offsets, dim3(g.ncoarse), dim3(GRP_FINE_BLOCK), 0, s, cm, gb.base, kcount, hist, offs);
-    hipLaunchKernelGGL(k_table_scatter, dim3(g.mmax), dim3(GRP_FINE_BLOCK), lf, s, cm, gb.rec, gb.desc, gb.nchunks,
-                       kcount, perm, pos_sorted);
+    hipLaunchKernelGGL(k_table_count, dim3(chunks), dim3(256), 0, s, src, uint32_t(tile), uint32_t(nb), count);
+    hipLaunchKernelGGL(k_table_offsets, dim3(1), dim3(1024), 0, s, uint32_t(nb), count, hist, offs);
+    auto scatter = f->desc.coef == BSI_F64 ? k_table_scatter<double> : k_table_scatter<float>;
+    hipLaunchKernelGGL(scatter, dim3(chunks), dim3(256), 0, s, src, ca, uint32_t(tile), uint32_t(nb), b.binned, b.perm,
+                       count, perm, pos_sorted);
     BSI_HIP(hipGetLastError());
     return BSI_OK;
 }

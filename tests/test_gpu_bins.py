@@ -121,3 +121,19 @@ def test_bins_full_size(ctx, case):
     log(f"bins full size {case}")
     with Field(ctx, n, 3, 6, BSI_F32) as f:
         check_bins(f, pos, (n, n, n), 8)
+
+
+@pytest.mark.parametrize("coef", ["f32", "f64"])
+def test_bins_are_those_of_the_evaluation(coef):
+    # read back from the binning that an evaluation runs (its stages are launched and timed), for both
+    # forms of binned particles, with ranges of every kind: sparse, crowded, one without a cell
+    from paper_1201_4060_amd import Context, Field, BSI_F32, BSI_F64, _bsi
+    pos = np.concatenate([synth.uniform_positions(700_001, seed=64),
+                          synth.clustered_positions(1000, 30, 9000, 0.06, seed=65), np.full((3000, 3), np.inf)])
+    pos = np.ascontiguousarray(pos[np.random.default_rng(66).permutation(pos.shape[0])])
+    with Context(0) as c, Field(c, 256, 1, 4, BSI_F32 if coef == "f32" else BSI_F64) as f:
+        _bsi.bsi_ctx_set_timing(c.handle, 1)
+        for tile in (4, 8):
+            check_bins(f, pos, (256, 256, 256), tile)
+        for stage in ("bin_count", "bin_scan", "bin_scatter"):
+            assert _bsi.bsi_ctx_read_timing(c.handle, stage)[1] == 2, stage
