@@ -198,9 +198,9 @@ bsi_status bsi_eval_ex(bsi_field* field, const double* pos_dev, int64_t P,
  * process ends; its address is looked up once per device by bsi_ctx_create).
  * The call allocates nothing and creates no events (the context's stage
  * timing does not record it).  BSI_E_INVAL, with the bytes needed in
- * bsi_last_error(), when the call's workspace (about 70 bytes per particle
- * plus 8 per tile of the field, for binned configurations) exceeds the
- * array; use fewer particles per call or bsi_eval_ex then.  Every call on a
+ * bsi_last_error(), when the call's workspace (for binned configurations 52
+ * bytes per particle, FP64 fields 60; 16 per tile with particles, at most; and
+ * up to 16 MiB of counts) exceeds the array; use fewer particles per call or bsi_eval_ex then.  Every call on a
  * GPU shares that GPU's array: calls that overlap on one GPU (other streams or
  * host threads) race and must not be issued; consecutive calls on one stream
  * are ordered and safe.  Nothing in the array needs clearing between calls. */
@@ -210,7 +210,7 @@ bsi_status bsi_eval_static(bsi_field* field, const double* pos_dev, int64_t P,
 
 /* An evaluation in two halves (the same work and results as bsi_eval_ex, bitwise):
  * bsi_eval_plan_bin does everything that depends on the positions only (cell,
- * Morton binning, work items: Section 5's stencil rule), bsi_eval_plan_run the
+ * binning by tiles, work items: Section 5's stencil rule), bsi_eval_plan_run the
  * gather and contraction from that binning and the field's grid as it is when
  * the run executes.  The binning can thus run on another stream while the
  * field's prefilter (bsi_field_set_spectrum) runs, and one binning serves

@@ -11,8 +11,8 @@
 // cells) or one lane per particle from global memory.
 //
 // Device work (one stream, no host synchronisation in between):
-//   grouping    cell and Morton bucket of every particle (all items at once),
-//               grouped by bucket without global atomics (gather.hpp): binned
+//   grouping    cell and tile of every particle (all items at once),
+//               grouped by tile without global atomics (gather.hpp): binned
 //               particles, and the work items of the tiled items (runs of one
 //               tile, cut into pieces), (order, components) class by class
 //   gather      per class present: a persistent grid of resident one-wavefront
@@ -422,7 +422,6 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
         g.n1 = f->n[1];
         g.n2 = f->n[2];
         g.P1 = f->P[1];
-        g.P2 = f->P[2];
         g.pitch2 = f->pitch2;
         g.ih0 = f->inv_h[0];
         g.ih1 = f->inv_h[1];
@@ -431,7 +430,6 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
         g.basis = BSI_BASIS_BSPLINE;
         g.cs = 1;
         const size_t nbf = bin_key_count(f, tile);
-        g.nbuckets_finite = uint32_t(nbf);
         x.N = f->N;
         x.C = f->C;
         x.cls = class_of(f->N, f->C);
@@ -481,7 +479,7 @@ bsi_status bsi_batch_create(bsi_ctx* ctx, const bsi_eval_item* items, int32_t co
     for (auto& x : hi)
         if (x.mode == MODE_DIRECT) x.ubase += b->dbeg[x.cls];
     uint32_t fine_max = 1;
-    uint64_t nwork = 0;   // item slots the chunk plan reserves at most (direct items too)
+    uint64_t nwork = 0;   // item slots of the tiled items (the direct ones come last and write none)
     for (size_t i = 0; i < hi.size(); ++i) {
         const BatchItem& x = hi[i];
         for (uint64_t lo = 0; lo < x.nb; lo += uint64_t(1) << x.cshift) {

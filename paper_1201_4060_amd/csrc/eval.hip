@@ -1,4 +1,4 @@
-// Evaluation on the GPU: position -> cell/offset, Morton binning, and the
+// Evaluation on the GPU: position -> cell/offset, binning by tiles, and the
 // per-particle gather + tensor contraction (Sections 2, 3, 5; Table 1).
 #include <algorithm>
 
@@ -560,7 +560,6 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
     ga.perm = nullptr;
     ga.binned = nullptr;
     ga.src = ItemSource{};
-    size_t nbf = 0;
     if (tile > 0) {
         BSI_CHECK(ws != nullptr && reinterpret_cast<uintptr_t>(ws) % 16 == 0, BSI_E_INVAL,
                   "binned evaluation needs a 16-byte aligned workspace");
@@ -568,7 +567,6 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
         ga.perm = b.perm;
         ga.binned = b.binned;
         ga.src = item_source(b);
-        nbf = bin_key_count(f, tile);
     }
     ga.u = u;
     ga.grad = grad;
@@ -578,13 +576,11 @@ bsi_status eval_gather_ws(bsi_field* f, const double* pos, int64_t P, void* u, v
     ga.n1 = f->n[1];
     ga.n2 = f->n[2];
     ga.P1 = f->P[1];
-    ga.P2 = f->P[2];
     ga.pitch2 = f->pitch2;
     ga.ih0 = f->inv_h[0];
     ga.ih1 = f->inv_h[1];
     ga.ih2 = f->inv_h[2];
     ga.xcd_remap = (ga.perm && cfg.xcd_remap) ? 1 : 0;
-    ga.nbuckets_finite = uint32_t(nbf);
     ga.basis = f->basis;
     ga.cs = f->cs;
     const bool g = grad != nullptr;

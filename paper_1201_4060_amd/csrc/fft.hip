@@ -412,7 +412,7 @@ struct C2rCfg {
 };
 
 // Pieces of pass C.  A workgroup holds NL lines of M + 1 half-spectrum values in
-// zb, LP = M + 2 apart, with the twiddles tw[m] = exp(+2 pi i m / (2M)), m < 2M.
+// zb, LP apart (M + 2, FP64 ones spread), with the twiddles tw[m] = exp(+2 pi i m / (2M)), m < 2M.
 
 // The lines from work[c][g0][g1][k2] (rows of Hp, at least M + 2): line l of the
 // block is zb line l * C + c.  All loads of a thread are issued before its stores;

@@ -1,6 +1,6 @@
 // Device-side building blocks of the evaluation shared by the single-field
 // kernels (eval.hip) and the persistent multi-field kernel (batch.hip):
-// position -> cell/offset, Morton keys, prefix scans, B-spline weights and the
+// position -> cell/offset, tile keys, the grouping by key, B-spline weights and the
 // per-particle tensor contraction (Sections 2, 3, 5; Table 1).  Both callers
 // run exactly these functions, so a particle's result does not depend on which
 // kernel evaluated it.
@@ -49,7 +49,7 @@ struct CellArgs {
 };
 
 // ---------------------------------------------------------------- binning ---
-// Particles are counting-sorted by the Morton code of the tile (cell / T) that
+// Particles are counting-sorted by the key (tile_key) of the tile (cell / T) that
 // holds their cell; non-finite particles go to one extra bucket at the end.
 
 __device__ __forceinline__ uint32_t spread3(uint32_t v) {  // 10 bits -> every third bit
@@ -829,11 +829,10 @@ struct GatherArgs {
     unsigned long long* nonfinite;
     long P;
     int n0, n1, n2;
-    int P1, P2;  // padded extents of axes 1 and 2
+    int P1;      // padded extent of axis 1
     int pitch2;  // elements between consecutive (p0, p1) rows of the grid
     double ih0, ih1, ih2;
     int xcd_remap;
-    uint32_t nbuckets_finite;
     int basis;   // bsi_basis of the field
     int cs;      // stored grid entries per cell along an axis: 1, or 2 for Hermite (direct gather only)
     ItemSource src;      // work items (tiled kernel)
@@ -1658,8 +1657,9 @@ struct SplitSlots {
 
 // Weights of a particle on N lanes: each lane forms those of stencil index `part`
 // along the three axes (the Horner steps of bspline_weights) and reads the others'
-// through LDS; w[0][i], i < N / 2, is plane i of the lane's half from the lane on
-// (split_sum).
+// through LDS (a wavefront's LDS instructions go in order; a fence and a wave barrier
+// between the pairs' writes and reads cost 7 % at 10^3 .. 1.6 * 10^5 particles); w[0][i],
+// i < N / 2, is plane i of the lane's half from the lane on (split_sum).
 template <int N, typename AT>
 __device__ __forceinline__ void split_weights(const GatherArgs& a, const AT* t, int part, AT (*slot)[N][2],
                                               AT (*w)[N], AT (*wd)[N]) {

@@ -54,7 +54,6 @@ struct HessArgs {
     const void* grid;
     const void* binned;        // the particles in binned order (RawParticle)
     const uint32_t* perm;      // particle of every binned slot
-    uint32_t nbuckets_finite;  // finite tiles; the next one holds the particles without a cell
     long P;
     int n0, n1, n2, P1;
     int pitch2;
@@ -461,7 +460,6 @@ bsi_status hessian_run(bsi_field* f, const double* pos, int64_t P, void* u, void
     a.grid = f->grid;
     a.binned = b.binned;
     a.perm = b.perm;
-    a.nbuckets_finite = uint32_t(bin_key_count(f, tile));
     a.P = long(P);
     a.n0 = f->n[0];
     a.n1 = f->n[1];

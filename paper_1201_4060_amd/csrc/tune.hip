@@ -84,7 +84,6 @@ bool json_int(const std::string& line, const char* key, long long* v) {
 
 }  // namespace
 
-size_t bin_bucket_count(const bsi_field* f, int tile);
 bool tiled_supported(const bsi_field* f, int tile);
 
 namespace {
