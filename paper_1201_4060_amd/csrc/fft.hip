@@ -566,9 +566,10 @@ __global__ __launch_bounds__(256) void k_c2r(const cplx<T>* __restrict__ work, i
 // doubled grid entry 2 g + a2 (+ the offsets a0, a1 of axes 0 and 1) holds
 // field a2 at grid point g, so whole rows are written.  dtab[k] = 2 pi k / n2
 // for k < M, 0 at the Nyquist index M.
+// (Three components of 1024 points take six teams of 64 threads.)
 template <typename T, typename OutT, int M, int C>
-__global__ __launch_bounds__(256) void k_c2r_dual(const cplx<T>* __restrict__ work, int Hp,
-                                                  OutT* __restrict__ grid, int n0, int n1, int P0, int P1, int P2,
+__global__ __launch_bounds__((C2rCfg<T, M, 2 * C>::THREADS > 256 ? C2rCfg<T, M, 2 * C>::THREADS : 256)) void
+k_c2r_dual(const cplx<T>* __restrict__ work, int Hp, OutT* __restrict__ grid, int n0, int n1, int P0, int P1, int P2,
                                                   int pitch2, const cplx<T>* __restrict__ twg,
                                                   const double* __restrict__ dtab, int a0, int a1) {
     using Cfg = C2rCfg<T, M, 2 * C>;

@@ -238,3 +238,19 @@ def test_method_validation(ctx):
         with pytest.raises(bsi.BsiError) as e:
             bsi.Batch(ctx, [(f, pos, u, None)])
         assert e.value.status == 3
+
+
+@pytest.mark.parametrize("coef", ["f32", "f64"])
+def test_hermite_grid_of_the_longest_rows(ctx, coef):
+    # 1024 points along axis 2, three components: the largest workgroup of the last pass
+    import paper_1201_4060_amd as bsi
+    from oracle import hermite
+    rng = np.random.default_rng(41)
+    shape = (8, 12, 1024)
+    uhat = rng.standard_normal((3, 8, 12, 513)) + 1j * rng.standard_normal((3, 8, 12, 513))
+    want = hermite.interleaved(hermite.derivative_grids(uhat, shape))
+    with bsi.Field(ctx, shape, 3, 4, bsi.BSI_F32 if coef == "f32" else bsi.BSI_F64, bsi.BSI_PREFILTER_NONE,
+                   basis=bsi.BSI_BASIS_HERMITE) as f:
+        f.set_spectrum(dev(uhat))
+        got = host(f.get_coefficients())
+    assert np.max(np.abs(got - want)) < (2e-6 if coef == "f32" else TOL_F64) * np.max(np.abs(want))
