@@ -1,6 +1,5 @@
-// Batched evaluation: many fields with uneven particle sets evaluated by one
-// persistent gather launch, optionally captured once into a HIP graph and
-// replayed.  The per-particle arithmetic is the single-field one
+// Batched evaluation: many fields with uneven particle sets evaluated by a few
+// launches, optionally captured once into a HIP graph and replayed.  The per-particle arithmetic is the single-field one
 // (gather.hpp), so every item's result is bitwise the result of bsi_eval_ex
 // with the same configuration.
 //
