@@ -97,26 +97,23 @@ __global__ __launch_bounds__(1024) void k_table_offsets(uint32_t nb, uint32_t* _
     }
 }
 
-// One workgroup per chunk: the items' particles to their buckets' slots, with the
+// One wavefront per chunk: the items' particles to their buckets' slots, with the
 // position that the binned particle stands for: an FP64 one's own, for an FP32
 // record that of the particle it names if the record is that particle's (else NaN).
 template <typename AT>
-__global__ __launch_bounds__(256) void k_table_scatter(ItemSource src, CellArgs a, uint32_t tile, uint32_t nb,
+__global__ __launch_bounds__(64) void k_table_scatter(ItemSource src, CellArgs a, uint32_t tile, uint32_t nb,
                                                       const void* __restrict__ binned,
                                                       const uint32_t* __restrict__ perm,
                                                       uint32_t* __restrict__ cursor, uint32_t* __restrict__ perm_out,
                                                       double* __restrict__ pos_sorted) {
-    __shared__ uint32_t first;
     if (blockIdx.x >= *src.g1) return;
     const u32x4 d = src.desc[blockIdx.x];
     for (uint32_t i = 0; i < d.z; ++i) {
         const u32x4 it = src.items[d.w + i];
         const uint32_t b = item_bucket(it, tile, nb);
-        if (threadIdx.x == 0) first = b < nb ? atomicAdd(&cursor[b], it.z) : 0u;
-        __syncthreads();
-        const uint32_t at = first;
-        __syncthreads();
-        for (uint32_t j = threadIdx.x; j < it.z; j += 256) {
+        const uint32_t at =
+            __builtin_amdgcn_readfirstlane(threadIdx.x == 0 && b < nb ? atomicAdd(&cursor[b], it.z) : 0u);
+        for (uint32_t j = threadIdx.x; j < it.z; j += 64) {
             if (b >= nb || long(at) + j >= a.P || long(it.y) + j >= a.P) continue;
             const uint32_t p = perm[it.y + j];
             perm_out[at + j] = p;
@@ -655,7 +652,7 @@ bsi_status debug_bins_run(bsi_field* f, const double* pos, int64_t P, int tile, 
     hipLaunchKernelGGL(k_table_count, dim3(chunks), dim3(256), 0, s, src, uint32_t(tile), uint32_t(nb), count);
     hipLaunchKernelGGL(k_table_offsets, dim3(1), dim3(1024), 0, s, uint32_t(nb), count, hist, offs);
     auto scatter = f->desc.coef == BSI_F64 ? k_table_scatter<double> : k_table_scatter<float>;
-    hipLaunchKernelGGL(scatter, dim3(chunks), dim3(256), 0, s, src, ca, uint32_t(tile), uint32_t(nb), b.binned, b.perm,
+    hipLaunchKernelGGL(scatter, dim3(chunks), dim3(64), 0, s, src, ca, uint32_t(tile), uint32_t(nb), b.binned, b.perm,
                        count, perm, pos_sorted);
     BSI_HIP(hipGetLastError());
     return BSI_OK;
